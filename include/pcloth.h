@@ -411,7 +411,11 @@ pc_status pc_mfma_probe(pc_ctx *ctx, float *out_host);
  *   fewer, larger work items cost less per iteration on large instances.
  * PC_OPT_LDS_WINDOW: 1 (default): each SpMV work item whose block columns
  *   span at most 4096 rows first copies that window of the search direction
- *   to LDS and gathers from there; 0: all gathers from global memory.
+ *   to LDS and gathers from there; 0: all gathers from global memory.  With
+ *   it on and the other schedule options at their defaults, instances of at
+ *   most about 1,000 rows per compute unit (of all instances together) whose
+ *   rows' columns stay close together run each sweep's iterations in one
+ *   launch, with the same sums and bits.
  * PC_OPT_NARROW_COLUMNS: 1 (default): when every block column lies within
  *   +-32767 rows of its 64-row slice (true for meshes numbered in grid
  *   order), the CG SpMV reads 16-bit column offsets instead of 32-bit

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "pc_mlp.h"
+#include "pc_resident.h"
 
 using namespace pc;
 
@@ -112,8 +113,10 @@ static void free_all(Ctx *c) {
                     c->p, c->partials, c->partials_u, c->res2, c->counter, c->st, c->scan_tmp, c->jval_hi, c->slice_row0, c->slice_psize, c->slice_vbase, c->sitem_win, c->cverts, c->cw, c->cn, c->jdel, c->cg_pd, c->cg_s, c->e32, c->r32, c->q32,
                     c->row_slice, c->sitem, c->vitem, c->inst_sitem0, c->inst_vitem0, c->restart, c->maxit_d,
                     c->slot_off, c->rowlen_s, c->f16_scale, c->f16_part, c->inst_slice0, c->row_state, c->wide_rows, c->trec, c->hrec, c->crec, c->row_npairs,
-                    c->cols_tmp, c->pairs_tmp};
+                    c->cols_tmp, c->pairs_tmp, c->win_info};
     for (void *p : ptrs) dev_free(c, p);
+    resident_free(c);
+    if (c->win_info_h) (void)hipHostFree(c->win_info_h);
     if (c->st_host) (void)hipHostFree(c->st_host);
     if (c->restart_h) (void)hipHostFree(c->restart_h);
     if (c->status_host) (void)hipHostFree(c->status_host);

@@ -56,10 +56,42 @@ __device__ __forceinline__ int xcd_remap(int b, int nblocks) {
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 
+// Sum over the wavefront, the same in every lane: the butterfly over lane
+// distances 32, 16, 8, 4, 2, 1.  The halves and the rows are exchanged with
+// gfx950's lane swaps and the distances within a 16-lane row with rotations
+// (once distance 8 is done the values have period 8, so rotating by 4 is the
+// exchange with the lane at distance 4, and so on); no LDS traffic, where the
+// shuffles of the same butterfly are 12 LDS operations in six dependent steps.
+__device__ __forceinline__ double join64(unsigned lo, unsigned hi) { return __hiloint2double((int)hi, (int)lo); }
+template <int CTRL>
+__device__ __forceinline__ double row_rotated(double v) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, WAVE);
+    unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    v = join64(l[0], h[0]) + join64(l[1], h[1]);
+    lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = join64(l[0], h[0]) + join64(l[1], h[1]);
+    v += row_rotated<0x128>(v);   // row_ror:8
+    v += row_rotated<0x124>(v);
+    v += row_rotated<0x122>(v);
+    v += row_rotated<0x121>(v);
     return v;
+}
+
+// a0 b0 + a1 b1 + a2 b2 with the roundings fixed: the product of the middle
+// terms, then two fused multiply-adds.  The CG kernels write their sums with
+// it (and with explicit fma) where two kernels have to give the same bits.
+__device__ __forceinline__ double dot3(double a0, double b0, double a1, double b1, double a2, double b2) {
+    return __builtin_fma(a2, b2, __builtin_fma(a0, b0, a1 * b1));
+}
+__device__ __forceinline__ float dot3(float a0, float b0, float a1, float b1, float a2, float b2) {
+    return __builtin_fmaf(a2, b2, __builtin_fmaf(a0, b0, a1 * b1));
 }
 
 __device__ __forceinline__ int wave_sum_int(int v) {

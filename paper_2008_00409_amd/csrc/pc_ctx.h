@@ -110,6 +110,31 @@ struct Prof {
 
 struct MlpState;
 
+// Resident CG (resident.hip): one instance's rows, slices, teams and slots.
+struct ResInst {
+    int row0, nrows, slice0, nsl;
+    int ngroups, nitems;   // 8-slice SpMV items, 32-slice vector items
+    int k;                 // pairs of slices per workgroup: 1, 2, 4 or 8
+    int team;              // workgroups
+    int pq_off, rz_off;    // first slots
+};
+
+// Teams of all instances (built with the schedule) and, per assembly, their
+// block-column windows.
+struct ResPlan {
+    bool valid = false, coop = false;
+    int ns = 1, threads = 1024, nwg = 0;
+    int slot_n = 0, slot_rep = 0, slot_rz = 0;
+    ResInst *inst = nullptr;
+    int4 *wg = nullptr;
+    int2 *win = nullptr;
+    unsigned long long *slots = nullptr;
+    size_t inst_bytes = 0, wg_bytes = 0, win_bytes = 0, slot_bytes = 0;
+    const int *inst_win = nullptr;             // per instance: largest window (in Ctx::win_info)
+    int win_rows = 0;                          // LDS rows of the launches (0: no instance fits)
+    bool all = false;                          // every instance fits
+};
+
 // The paper's sparse-matrix filling and BELL layout (built beside the
 // solver's assembly for comparison): index table (nv x Wi), compacted
 // column table and value planes (slot k of row i at k nv + i).
@@ -285,6 +310,11 @@ struct Ctx {
     bool win_valid = false;
     bool use_win = true;          // PC_OPT_LDS_WINDOW
     int win_cap = 0;              // LDS window rows of the SpMV launches (0: global gathers)
+    // window summary of an assembly: {largest window within PC_WIN_MAX, items
+    // whose columns do not fit 16-bit offsets, largest resident window of
+    // each instance}, and its pinned copy
+    int *win_info = nullptr, *win_info_h = nullptr;
+    ResPlan res;
 
     BellState bell;
 };

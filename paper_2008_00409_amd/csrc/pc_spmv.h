@@ -125,9 +125,9 @@ struct SlotGroup {
             d0 = act[u] ? d0 : A(0);
             d1 = act[u] ? d1 : A(0);
             d2 = act[u] ? d2 : A(0);
-            a0 += (A)v[u][0] * d0 + (A)v[u][1] * d1 + (A)v[u][2] * d2;
-            a1 += (A)v[u][3] * d0 + (A)v[u][4] * d1 + (A)v[u][5] * d2;
-            a2 += (A)v[u][6] * d0 + (A)v[u][7] * d1 + (A)v[u][8] * d2;
+            a0 += dot3((A)v[u][0], d0, (A)v[u][1], d1, (A)v[u][2], d2);
+            a1 += dot3((A)v[u][3], d0, (A)v[u][4], d1, (A)v[u][5], d2);
+            a2 += dot3((A)v[u][6], d0, (A)v[u][7], d1, (A)v[u][8], d2);
         }
     }
 };
@@ -172,9 +172,9 @@ __device__ __forceinline__ int spmv_row(const SpmvArgs &M, int slice, int lane, 
             const double vi = M.vscale[2 * slice + 1];   // a power of two: exact
             s0 *= vi; s1 *= vi; s2 *= vi;
         }
-        y[0] = s0 + m * (double)x0;
-        y[1] = s1 + m * (double)x1;
-        y[2] = s2 + m * (double)x2;
+        y[0] = __builtin_fma(m, (double)x0, s0);
+        y[1] = __builtin_fma(m, (double)x1, s1);
+        y[2] = __builtin_fma(m, (double)x2, s2);
     } else {
         y[0] = y[1] = y[2] = 0.0;
     }
@@ -222,6 +222,30 @@ __device__ __forceinline__ void block_partials(double (&v)[NV], double *partials
     }
 }
 
+// Sums of one row of the CG update, with fixed roundings (the three-launch
+// update and the resident kernel give the same bits): r.r, which starts with
+// the square of the second component at a thread's first row and goes on
+// component by component after that; r.z for Jacobi, r.P^-1 r; and z = P^-1 r
+// for block Jacobi (b6: xx, xy, xz, yy, yz, zz), whose r.z is dot3(r, z).
+__device__ __forceinline__ void sum_rr(double &rr, const double rk[3], bool first) {
+    if (first)
+        rr = __builtin_fma(rk[0], rk[0], rk[1] * rk[1]);
+    else
+        rr = __builtin_fma(rk[1], rk[1], __builtin_fma(rk[0], rk[0], rr));
+    rr = __builtin_fma(rk[2], rk[2], rr);
+}
+__device__ __forceinline__ void sum_rz_jacobi(double &rz, const double rk[3], const float d[3]) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rz = __builtin_fma(rk[c] * rk[c], (double)d[c], rz);
+}
+__device__ __forceinline__ void block_times(const float b6[6], const double rk[3], double &z0, double &z1,
+                                            double &z2) {
+    const double xx = b6[0], xy = b6[1], xz = b6[2], yy = b6[3], yz = b6[4], zz = b6[5];
+    z0 = dot3(xx, rk[0], xy, rk[1], xz, rk[2]);
+    z1 = dot3(xy, rk[0], yy, rk[1], yz, rk[2]);
+    z2 = dot3(xz, rk[0], yz, rk[1], zz, rk[2]);
+}
+
 // q = A p (stored as TQ) and per-item partials of p.q.  When the item's column window fits
 // in win_cap rows, p[window] is first copied to LDS with coalesced loads and
 // the rows gather from there; otherwise they gather from global memory.
@@ -256,7 +280,7 @@ __global__ void __launch_bounds__(1024) k_pcg_spmv(SpmvArgs M, Sched S, const fl
             q[3 * row] = q0;
             q[3 * row + 1] = q1;
             q[3 * row + 2] = q2;
-            pq = xi[0] * (double)q0 + xi[1] * (double)q1 + xi[2] * (double)q2;
+            pq = dot3(xi[0], (double)q0, xi[1], (double)q1, xi[2], (double)q2);
         }
     }
     double v[1] = {pq};

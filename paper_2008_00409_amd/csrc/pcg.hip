@@ -29,6 +29,7 @@
 #include <cmath>
 
 #include "pc_mlp.h"
+#include "pc_resident.h"
 #include "pc_spmv.h"
 
 namespace pc {
@@ -113,8 +114,11 @@ __global__ void k_state_init(int ninst, PcgState *st, const uint8_t *restart, do
 // Column window of every SpMV work item: the smallest and largest block
 // column of its rows (block-CSR columns are ascending, so the first and last
 // of each row suffice).  One block per item.
+// The summary takes the largest window of at most win_max rows and whether a
+// column lies outside 16-bit offsets: every column of an item's slices lies
+// in [lo, hi], and the slices' first rows in [r_first, r_last].
 __global__ void __launch_bounds__(256) k_item_windows(Sched S, const int *slice_row0, const int *rowptr,
-                                                      const int *colidx, int2 *win) {
+                                                      const int *colidx, int2 *win, int win_max, int *info) {
     __shared__ int sh[2][4];
     const int it = blockIdx.x;
     if (it >= S.n_sitems) return;
@@ -141,7 +145,15 @@ __global__ void __launch_bounds__(256) k_item_windows(Sched S, const int *slice_
             hi = max(hi, sh[1][k]);
         }
         win[it] = make_int2(lo, hi);
+        if (hi - lo + 1 <= win_max) atomicMax(&info[0], hi - lo + 1);
+        const int r_last = slice_row0[I.y + I.z - 1];
+        if (hi - r0 > 32767 || lo - r_last < -32768) atomicOr(&info[1], 1);
     }
+}
+
+__global__ void k_clear_ints(int *p, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0;
 }
 
 // Rows i0 + t + u VT (u < U) of an update item, as thread t sees them: the
@@ -223,22 +235,20 @@ __global__ void __launch_bounds__(VT) k_pcg_update(Sched S, int par, TV *r, cons
                 double rk[3];
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    rv[c] = (TV)((double)cur.r[u][c] - alpha * (double)cur.q[u][c]);
+                    rv[c] = (TV)__builtin_fma(-alpha, (double)cur.q[u][c], (double)cur.r[u][c]);
                     rk[c] = rv[c];
-                    rr += rk[c] * rk[c];
                 }
+                sum_rr(rr, rk, i0 == I.y && u == 0);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) r[3 * i + c] = rv[c];
                 if (P.kind == 0) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) rz += rk[c] * rk[c] * (double)cur.d[u][c];
+                    sum_rz_jacobi(rz, rk, cur.d[u]);
                 } else {
-                    const double xx = cur.b[u][0].x, xy = cur.b[u][0].y, xz = cur.b[u][1].x;
-                    const double yy = cur.b[u][1].y, yz = cur.b[u][2].x, zz = cur.b[u][2].y;
-                    const double z0 = xx * rk[0] + xy * rk[1] + xz * rk[2];
-                    const double z1 = xy * rk[0] + yy * rk[1] + yz * rk[2];
-                    const double z2 = xz * rk[0] + yz * rk[1] + zz * rk[2];
-                    rz += rk[0] * z0 + rk[1] * z1 + rk[2] * z2;
+                    const float b6[6] = {cur.b[u][0].x, cur.b[u][0].y, cur.b[u][1].x,
+                                         cur.b[u][1].y, cur.b[u][2].x, cur.b[u][2].y};
+                    double z0, z1, z2;
+                    block_times(b6, rk, z0, z1, z2);
+                    rz += dot3(rk[0], z0, rk[1], z1, rk[2], z2);
                     st3(P.z, i, (float)z0, (float)z1, (float)z2);
                 }
             }
@@ -317,9 +327,9 @@ __global__ void __launch_bounds__(VT) k_pcg_dir(Sched S, int par, TV *x, const T
     for (; i < I.z; i += VT) {
         if (i != I.y + (int)threadIdx.x) row.load(i, x, r, p, P);
         const float4 pv = row.p;
-        x[3 * i] = (TV)((double)row.x[0] + alpha * (double)pv.x);
-        x[3 * i + 1] = (TV)((double)row.x[1] + alpha * (double)pv.y);
-        x[3 * i + 2] = (TV)((double)row.x[2] + alpha * (double)pv.z);
+        x[3 * i] = (TV)__builtin_fma(alpha, (double)pv.x, (double)row.x[0]);
+        x[3 * i + 1] = (TV)__builtin_fma(alpha, (double)pv.y, (double)row.x[1]);
+        x[3 * i + 2] = (TV)__builtin_fma(alpha, (double)pv.z, (double)row.x[2]);
         if (new_dir) {
             double z[3];
             if (P.kind == 0) {
@@ -328,7 +338,8 @@ __global__ void __launch_bounds__(VT) k_pcg_dir(Sched S, int par, TV *x, const T
             } else {
                 z[0] = row.z.x; z[1] = row.z.y; z[2] = row.z.z;
             }
-            st3(p, i, (float)(z[0] + beta * pv.x), (float)(z[1] + beta * pv.y), (float)(z[2] + beta * pv.z));
+            st3(p, i, (float)__builtin_fma(beta, (double)pv.x, z[0]), (float)__builtin_fma(beta, (double)pv.y, z[1]),
+                (float)__builtin_fma(beta, (double)pv.z, z[2]));
         }
     }
 }
@@ -755,8 +766,12 @@ pc_status build_schedule(Ctx *ctx) {
         if ((st = realloc((void **)&ctx->maxit_d, sizeof(int) * ninst))) return st;
         if (ctx->st_host) (void)hipHostFree(ctx->st_host);
         if (ctx->restart_h) (void)hipHostFree(ctx->restart_h);
+        if (ctx->win_info_h) (void)hipHostFree(ctx->win_info_h);
         ctx->st_host = nullptr;
         ctx->restart_h = nullptr;
+        ctx->win_info_h = nullptr;
+        if ((st = realloc((void **)&ctx->win_info, sizeof(int) * (2 + (size_t)ninst)))) return st;
+        PC_HIP(hipHostMalloc((void **)&ctx->win_info_h, sizeof(int) * (2 + (size_t)ninst), hipHostMallocDefault));
         PC_HIP(hipHostMalloc((void **)&ctx->st_host, sizeof(PcgState) * ninst, hipHostMallocDefault));
         PC_HIP(hipHostMalloc((void **)&ctx->restart_h, (size_t)ninst, hipHostMallocDefault));
     }
@@ -776,7 +791,7 @@ pc_status build_schedule(Ctx *ctx) {
     ctx->sched_version += 1;
     ctx->win_valid = false;
     ctx->assembled = false;  // the solver layout depends on the slices
-    return PC_OK;
+    return resident_plan(ctx);
 }
 
 struct Grids {
@@ -809,30 +824,27 @@ static pc_status ensure_windows(Ctx *ctx, hipStream_t s) {
         ctx->win_items = ctx->n_sitems;
     }
     const Sched S = sched_args(ctx);
+    const int ni = 2 + ctx->ninst;
+    hipLaunchKernelGGL(k_clear_ints, dim3((ni + 255) / 256), dim3(256), 0, s, ctx->win_info, ni);
     hipLaunchKernelGGL(k_item_windows, dim3(ctx->n_sitems), dim3(256), 0, s, S, ctx->slice_row0, ctx->rowptr,
-                       ctx->colidx, ctx->sitem_win);
+                       ctx->colidx, ctx->sitem_win, PC_WIN_MAX, ctx->win_info);
+    if (ctx->res.valid) resident_windows(ctx, ctx->win_info + 2, s);
     PC_HIP(hipGetLastError());
-    std::vector<int2> w(ctx->n_sitems);
-    PC_HIP(hipMemcpyAsync(w.data(), ctx->sitem_win, sizeof(int2) * w.size(), hipMemcpyDeviceToHost, s));
+    PC_HIP(hipMemcpyAsync(ctx->win_info_h, ctx->win_info, sizeof(int) * ni, hipMemcpyDeviceToHost, s));
     PC_HIP(hipStreamSynchronize(s));
-    int cap = 0;
-    for (const int2 &v : w) {
-        const int n = v.y - v.x + 1;
-        if (n <= PC_WIN_MAX) cap = std::max(cap, n);
+    ctx->win_cap = ctx->use_win ? ctx->win_info_h[0] : 0;
+    ctx->narrow = ctx->win_info_h[1] == 0;
+    ResPlan &P = ctx->res;
+    P.inst_win = ctx->win_info + 2;
+    P.win_rows = 0;
+    P.all = P.valid;
+    const int rmax = P.valid ? resident_win_max(ctx) : 0;
+    for (int i = 0; i < ctx->ninst && P.valid; ++i) {
+        if (ctx->win_info_h[2 + i] <= rmax)
+            P.win_rows = std::max(P.win_rows, ctx->win_info_h[2 + i]);
+        else
+            P.all = false;
     }
-    ctx->win_cap = ctx->use_win ? cap : 0;
-    // 16-bit column offsets: every column of an item's slices lies in
-    // [lo, hi], and the slices' first rows in [first row, first row + 64 spb)
-    bool narrow = true;
-    std::vector<int4> items(ctx->n_sitems);
-    std::vector<int> row0(ctx->nslices + 1);
-    PC_HIP(hipMemcpy(items.data(), ctx->sitem, sizeof(int4) * items.size(), hipMemcpyDeviceToHost));
-    PC_HIP(hipMemcpy(row0.data(), ctx->slice_row0, sizeof(int) * row0.size(), hipMemcpyDeviceToHost));
-    for (size_t k = 0; k < items.size() && narrow; ++k) {
-        const int r_first = row0[items[k].y], r_last = row0[items[k].y + items[k].z - 1];
-        narrow = (long long)w[k].y - r_first <= 32767 && (long long)w[k].x - r_last >= -32768;
-    }
-    ctx->narrow = narrow;
     ctx->win_valid = true;
     return PC_OK;
 }
@@ -900,6 +912,14 @@ static void launch_one(Ctx *ctx, const SpmvArgs &M, const Sched &S, const Grids 
         launch_iter_cgcg<TB>(ctx, M, S, g, s);
     else
         launch_iter<TB>(ctx, M, S, g, s, par);
+}
+
+// Whether the solve's iterations run as resident launches (resident.hip): the
+// textbook recurrences at the default schedule, whose order of sums the
+// resident kernel reproduces, with some instance's windows fitting its LDS.
+// Other schedules keep the order of sums their options ask for.
+static bool use_resident(const Ctx *ctx) {
+    return ctx->method == 0 && ctx->use_win && ctx->use_narrow && ctx->spb == 8 && ctx->rpb == 2048 && resident_fits(ctx);
 }
 
 // Plain launches of n iterations continuing the context's parity.
@@ -1167,14 +1187,15 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
     }
     PC_HIP(hipGetLastError());
     for (int i = 0; i < ninst; ++i) sweeps[i] = 1;
-    bool inner_hi = false;
+    bool inner_hi = false, lost = false;   // lost: a resident launch's wait gave up (its device was shared)
     int guard = 0;
     long long nchunk = 0;
     for (;;) {
         if ((st = read_states(ctx, s))) return st;
         // iterate until every instance is done
         const int variant = inner_hi ? 1 : 0;
-        const bool graph = ctx->graph_chunk > 0;
+        const bool resident = use_resident(ctx) && !lost;
+        const bool graph = ctx->graph_chunk > 0 && !(resident && ctx->res.all);
         if (graph) {
             const SpmvArgs &Mv = inner_hi ? Mhi : M;
             const int want_code = inner_hi ? dtype_code<double>() : dtype_code<TB>();
@@ -1199,7 +1220,17 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
             // that they add little to the solve's time; with graph replay that
             // chunk runs as plain launches, which the events time
             const bool sample = ctx->prof.every > 0 && (nchunk++ % 8) == 0;
-            if (graph && !sample && ctx->cg_par == 0) {
+            bool fits = false;   // an unfinished instance whose iterations run resident
+            for (int i = 0; i < ninst && resident; ++i)
+                fits = fits || (!ctx->st_host[i].done && ctx->win_info_h[2 + i] <= ctx->res.win_rows);
+            if (fits && !sample) {
+                // to the end of the sweep; with profiling on, about seven chunks' iterations
+                const int most_iters = ctx->prof.every > 0 ? 7 * std::min(256, std::max(16, most / 4)) : 1 << 30;
+                st = inner_hi ? resident_launch<double>(ctx, Mhi, most_iters, s)
+                              : resident_launch<TB>(ctx, M, most_iters, s);
+                if (st) return st;
+                if (ctx->prof.every > 0) nchunk += 6;
+            } else if (graph && !sample && ctx->cg_par == 0) {
                 PC_HIP(hipGraphLaunch(ctx->gexec[variant], s));
             } else {
                 int chunk = graph ? ctx->graph_chunk : (check > 0 ? check : std::min(256, std::max(16, most / 4)));
@@ -1228,14 +1259,18 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
         PC_HIP(hipMemcpyAsync(res2.data(), ctx->res2, sizeof(double) * 2 * ninst, hipMemcpyDeviceToHost, s));
         PC_HIP(hipStreamSynchronize(s));
         std::vector<uint8_t> again(ninst, 0);
-        bool any = false, any_breakdown = false;
+        bool any = false, any_breakdown = false, any_lost = false;
         for (int i = 0; i < ninst; ++i) {
             const PcgState &h = ctx->st_host[i];
             const bool was_active = active[i] != 0;
             active[i] = 0;
             const bool ok = res2[2 * i] <= tol * tol * res2[2 * i + 1];
             if (ok || res2[2 * i + 1] == 0.0 || (h.flags & 2) || iters[i] >= maxit) continue;
-            if (h.flags & 1) {
+            if (h.flags & 4) {
+                // part of the launch's rows may hold its results: a start like
+                // any other, continued with three launches per iteration
+                lost = any_lost = true;
+            } else if (h.flags & 1) {
                 if (!inner_hi && ctx->hi_valid) {
                     any_breakdown = true;
                     fallback[i] = 1;
@@ -1271,8 +1306,9 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
         if ((st = upload_flags(ctx, again, s))) return st;
         hipLaunchKernelGGL(k_state_init, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, ctx->st, ctx->restart, tol,
                            rho, ctx->maxit_d);
-        // a breakdown or the switch to the FP64 blocks restarts from P^-1 r
-        launch_residual(ctx, Mhi, S, g, ctx->restart, b, ctx->x, (keep && !any_breakdown) ? 2 : 0, nullptr, s);
+        // a breakdown, the switch to the FP64 blocks or a lost launch restarts
+        // from P^-1 r
+        launch_residual(ctx, Mhi, S, g, ctx->restart, b, ctx->x, (keep && !any_breakdown && !any_lost) ? 2 : 0, nullptr, s);
         PC_HIP(hipGetLastError());
     }
     // b = 0: the solution is 0 whatever the start
@@ -1349,7 +1385,8 @@ static pc_status time_iters(Ctx *ctx, const double *b, int iters, float *ms, hip
     if (wst) return wst;
     ctx->cg_par = 0;
     launch_start_zero(ctx, S, g, nullptr, b, s);
-    if (ctx->graph_chunk > 0 && graph_stale(ctx, 0, M, dtype_code<TB>())) {
+    const bool resident = use_resident(ctx) && ctx->res.all;
+    if (!resident && ctx->graph_chunk > 0 && graph_stale(ctx, 0, M, dtype_code<TB>())) {
         pc_status st = capture_chunk<TB>(ctx, M, S, g, ctx->graph_chunk, 0);
         if (st) return st;
     }
@@ -1357,7 +1394,10 @@ static pc_status time_iters(Ctx *ctx, const double *b, int iters, float *ms, hip
     PC_HIP(hipEventCreate(&e0));
     PC_HIP(hipEventCreate(&e1));
     PC_HIP(hipEventRecord(e0, s));
-    if (ctx->graph_chunk > 0) {
+    if (resident) {
+        pc_status st = resident_launch<TB>(ctx, M, iters, s);
+        if (st) return st;
+    } else if (ctx->graph_chunk > 0) {
         for (int done = 0; done < iters; done += ctx->graph_chunk) PC_HIP(hipGraphLaunch(ctx->gexec[0], s));
     } else {
         const int saved = ctx->prof.every;

@@ -1,0 +1,1064 @@
+// Resident CG: a whole sweep of the textbook recurrences in one launch.  The
+// workgroups of an instance (its team) stay on their compute units for all
+// iterations, keep the search direction's window and the iterate in LDS, the
+// first blocks of every row in registers, and meet twice per iteration to
+// exchange the partial sums of p.q and of (r.z, r.r).
+//
+// What bounds it: the two meetings, about 2 us each, the vector instructions
+// of the product (about 34 a stored block) and, at the top of the range, the
+// blocks that do not fit the registers.  Three launches per iteration (SpMV,
+// update, direction) pay each launch's fill and drain, move every vector
+// through memory between them and stream all blocks.  Per iteration, three
+// launches -> resident, with the solve's other work spread over 64-96
+// iterations (FP16 and FP32 blocks with block Jacobi and Jacobi, in us):
+//   rows       256        2,560       33k         66k         131k        262k
+//   FP16   15.0 ->  8.0  18.4 ->  9.8  19.7 -> 10.7  24.7 -> 15.2  25.5 -> 15.9  30.9 -> 20.0
+//   FP32   14.8 ->  7.2  21.5 -> 10.4  22.7 -> 11.6  26.5 -> 12.6  32.5 -> 23.3  40.1 -> 27.4
+//   FP64   14.8 ->  7.4  22.0 ->  9.5  27.0 -> 10.4  29.7 -> 17.6  42.3 -> 33.5  61.3 -> 41.2
+// An iteration of the 262k-row FP16 case (15.9 us of its own) is 4.3 product,
+// 1.3 wait for the workgroup's slowest wavefront, 2-4 p.q meeting, 1 update,
+// 1.5 sums and stores, 3.5 (r.z, r.r) meeting, 1.8 direction.
+//
+// The sums are formed in exactly the order of the three-launch iteration at
+// its default schedule (8-slice SpMV items, 2048-row vector items), so both
+// give the same bits: a slice's p.q lanes are summed by the wavefront
+// butterfly, eight slices in order make an SpMV item, thread t of 1024 adds
+// items t, t + 1024, ...; the update's thread adds row t and row t + 1024 of
+// its item, 16 wavefronts in order make a vector item.  The pair of 64-row
+// slices (w, w + 16) of a 32-slice item is therefore the smallest unit of
+// work; a workgroup owns 1, 2, 4 or 8 consecutive pairs of one item.
+//
+// Memory shared between workgroups during the launch (the partial sums and
+// the halo rows' z) goes through relaxed agent-scope atomics, which bypass
+// the caches that are not coherent across the XCDs: no fence writes back or
+// invalidates an L2.  A value is published after every wavefront of the
+// workgroup has waited for its earlier stores (s_waitcnt vmcnt(0), then the
+// workgroup barrier), so a workgroup that has seen it also finds those
+// stores.  Slots hold EMPTY until written; each set of slots has two buffers,
+// and the buffer of the next iteration is emptied at a point where every
+// workgroup is known to have read it.  Every wait is bounded (SPIN_LIMIT
+// polls); a workgroup that gives up marks the instance (flag 4) and leaves
+// without writing its results, and so do the others in turn; the solver then
+// restarts the instance from its iterate with the three launches.  Teams of
+// more than one workgroup are launched cooperatively, so all of them are
+// resident at once.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "pc_resident.h"
+#include "pc_spmv.h"
+
+namespace pc {
+
+typedef unsigned long long u64;
+constexpr u64 EMPTY = 0xfff7a5a5a5a5a5a5ull;   // a NaN that publish() never writes
+constexpr int REPLICAS = 8;                    // copies of the slots: 256 workgroups polling one copy measured
+                                               // 3.7-4.2 us per meeting, eight copies 2.8 us
+constexpr int SPIN_LIMIT = 2000000;            // polls of about 1 us
+
+__device__ __forceinline__ void agent_store(u64 *p, u64 v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ u64 agent_load(const u64 *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_store_f(float *p, float v) {
+    __hip_atomic_store((unsigned *)p, __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float agent_load_f(const float *p) {
+    return __uint_as_float(__hip_atomic_load((const unsigned *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void agent_store_f(double *p, double v) {
+    agent_store((u64 *)p, __builtin_bit_cast(u64, v));
+}
+__device__ __forceinline__ double agent_load_f(const double *p) {
+    return __builtin_bit_cast(double, agent_load((const u64 *)p));
+}
+__device__ __forceinline__ u64 sum_bits(double v) {
+    const u64 b = __builtin_bit_cast(u64, v);
+    return b == EMPTY ? 0x7ff8000000000000ull : b;
+}
+// every earlier memory operation of this wavefront has completed
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+struct ResArgs {
+    // solver layout (pc_spmv.h)
+    const int *slice_vbase, *lane_row, *row_lane;
+    const uint8_t *slot_cnt;
+    const int16_t *jdel;
+    const void *jval;
+    const double *mass;
+    const double *vscale_inv;   // FP16 blocks: 1 / S of slice s at [2 s]
+    int nv;
+    // teams
+    ResInst const *inst;
+    const int4 *wg;        // instance, first pair, pairs, rank in the team
+    const int2 *win;       // block-column window of each workgroup
+    const int *inst_win;   // largest window of each instance's workgroups
+    int win_rows;          // LDS rows of the window
+    int win_cap;           // instances with a wider window are left to the three-launch iteration
+    PcgState *st;
+    float *p;
+    void *x, *r;           // iterate and residual (TV)
+    const float *pre;      // preconditioner: 3 (Jacobi) or 6 (block Jacobi) per row
+    void *exch;            // three planes of nv: z (block Jacobi, FP32) or r (Jacobi, TV)
+    u64 *slots;
+    int slot_n;            // slots of one buffer (p.q, then r.z and r.r)
+    int slot_rep;          // distance between copies
+    int slot_rz;           // first (r.z, r.r) slot
+    int par, max_iters;
+};
+
+// One stored block of a lane as it lies in memory, with its column (row of
+// the window, DIAG set for the row's own diagonal block): 5 registers for the
+// 16-bit types, 10 for FP32, 19 for FP64.  load() reads lane l of a slot of
+// width w whose values start at `seg` (uniform) and whose columns start at
+// `cols`: scalar bases with 32-bit lane offsets.
+constexpr unsigned DIAG = 0x8000u;
+template <typename TB> struct RawBlock;
+template <typename TB> struct RawHalf {
+    uint4 a;
+    unsigned b;   // value 8, column in the upper half
+    __device__ __forceinline__ void load(const char *seg, int w, unsigned l) {
+        a = *reinterpret_cast<const uint4 *>(seg + 16u * l);
+        b = *reinterpret_cast<const uint16_t *>(seg + 16 * w + 2u * l);
+    }
+    __device__ __forceinline__ void set_col(unsigned c) { b = (b & 0xffffu) | c << 16; }
+    __device__ __forceinline__ unsigned col() const { return b >> 16; }
+    __device__ __forceinline__ void clear() { a = make_uint4(0u, 0u, 0u, 0u); b = 0u; }
+    // to the compiler, new values: what is unpacked from kept blocks is not
+    // carried through the iterations in registers of its own
+    __device__ __forceinline__ void refresh() {
+        asm volatile("" : "+v"(a.x), "+v"(a.y), "+v"(a.z), "+v"(a.w), "+v"(b));
+    }
+};
+template <> struct RawBlock<f16_t> : RawHalf<f16_t> {
+    __device__ __forceinline__ void get(float v[9]) const {
+        v[0] = f16_to_f32(a.x & 0xffffu); v[1] = f16_to_f32(a.x >> 16);
+        v[2] = f16_to_f32(a.y & 0xffffu); v[3] = f16_to_f32(a.y >> 16);
+        v[4] = f16_to_f32(a.z & 0xffffu); v[5] = f16_to_f32(a.z >> 16);
+        v[6] = f16_to_f32(a.w & 0xffffu); v[7] = f16_to_f32(a.w >> 16);
+        v[8] = f16_to_f32(b & 0xffffu);
+    }
+};
+template <> struct RawBlock<bf16_t> : RawHalf<bf16_t> {
+    __device__ __forceinline__ void get(float v[9]) const {
+        v[0] = __uint_as_float(a.x << 16); v[1] = __uint_as_float(a.x & 0xffff0000u);
+        v[2] = __uint_as_float(a.y << 16); v[3] = __uint_as_float(a.y & 0xffff0000u);
+        v[4] = __uint_as_float(a.z << 16); v[5] = __uint_as_float(a.z & 0xffff0000u);
+        v[6] = __uint_as_float(a.w << 16); v[7] = __uint_as_float(a.w & 0xffff0000u);
+        v[8] = __uint_as_float(b << 16);
+    }
+};
+template <typename R> struct RawWide {
+    R v9[9];
+    unsigned c;
+    __device__ __forceinline__ void load(const char *seg, int w, unsigned l) {
+        constexpr int CE = 16 / (int)sizeof(R);
+#pragma unroll
+        for (int q = 0; q < 8 / CE; ++q) {
+            const uint4 u = *reinterpret_cast<const uint4 *>(seg + 16 * q * w + 16u * l);
+            if constexpr (CE == 4) {
+                v9[4 * q] = __uint_as_float(u.x); v9[4 * q + 1] = __uint_as_float(u.y);
+                v9[4 * q + 2] = __uint_as_float(u.z); v9[4 * q + 3] = __uint_as_float(u.w);
+            } else {
+                v9[2 * q] = join64(u.x, u.y);
+                v9[2 * q + 1] = join64(u.z, u.w);
+            }
+        }
+        v9[8] = *reinterpret_cast<const R *>(seg + 8 * (int)sizeof(R) * w + (unsigned)sizeof(R) * l);
+    }
+    __device__ __forceinline__ void set_col(unsigned col) { c = col; }
+    __device__ __forceinline__ unsigned col() const { return c; }
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) v9[q] = R(0);
+    }
+    __device__ __forceinline__ void refresh() {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) asm volatile("" : "+v"(v9[q]));
+        asm volatile("" : "+v"(c));
+    }
+    __device__ __forceinline__ void get(R v[9]) const {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) v[q] = v9[q];
+    }
+};
+template <> struct RawBlock<float> : RawWide<float> {};
+template <> struct RawBlock<double> : RawWide<double> {};
+
+// Slots per slice whose blocks stay in registers for the whole launch (K)
+// and per group in flight of those that stream (U), by slices per wavefront
+// (512 threads: 256 registers a thread; 256 threads: 512).  A regular
+// triangulation has 12 stored blocks a row, 13 with the diagonal.  G: blocks
+// applied between two reads of window rows.
+template <typename TB, int NS, int NT> struct Keep;
+template <int NS, int NT> struct Keep<f16_t, NS, NT> {
+    static constexpr int K = NS == 1 ? 18 : 12, U = 2, G = 3;
+};
+template <int NS, int NT> struct Keep<bf16_t, NS, NT> : Keep<f16_t, NS, NT> {};
+template <int NS, int NT> struct Keep<float, NS, NT> {
+    static constexpr int K = NS == 1 ? 12 : 5, U = 2, G = 3;
+};
+template <int NS, int NT> struct Keep<double, NS, NT> {
+    static constexpr int K = NT == 256 ? 14 : (NS == 1 ? 5 : 2), U = 1, G = 2;
+};
+
+// Vectors a workgroup keeps in LDS: the iterate, and with two slices per
+// wavefront, whose blocks take the registers, the residual.
+constexpr int res_vectors(int ns) { return ns; }
+
+// Doubles of LDS that hold an exchange's values while they are summed in
+// order: 256 chains of 8 (p.q) or 2 x 128 of 9 or 2 x 64 of 16, padded.
+constexpr int RAW = 2304;
+
+// Slots of a slice: lane k of `meta` holds slot k's count in bits 6..12 and
+// its offset from the slice's first stored block above.
+struct SliceSlots {
+    unsigned meta;
+    int base, n;
+};
+
+// Slot k's block of this lane.  Branch-free: lanes past the slot's count and
+// slots past the slice's last load a valid neighbour and get the lane's own
+// row as their column, so they contribute a product with x_i - x_i = 0.
+template <typename TB>
+__device__ __forceinline__ void load_slot(RawBlock<TB> &B, const ResArgs &A, const SliceSlots &S, int k, int lane,
+                                          int shift, unsigned self) {
+    const unsigned m = (unsigned)__builtin_amdgcn_readlane((int)S.meta, min(k, S.n - 1));
+    const int c = (int)(m >> 6) & 127, off = S.base + (int)(m >> 13);
+    const unsigned l = (unsigned)min(lane, c - 1);
+    B.load((const char *)A.jval + (int64_t)off * (9 * (int)sizeof(TB)), slot_width(c), l);
+    const int16_t d = *reinterpret_cast<const int16_t *>((const char *)A.jdel + 2 * (int64_t)off + 2u * l);
+    unsigned col = (unsigned)(shift + (int)d);
+    const bool act = lane < (k < S.n ? c : 0);
+    B.set_col(act ? (col == self ? col | DIAG : col) : self);
+}
+
+// the block's row of the window
+template <typename TB>
+__device__ __forceinline__ float3 block_p(const RawBlock<TB> &B, const float4 *pw) {
+    const float4 v = pw[B.col() & (DIAG - 1)];
+    return make_float3(v.x, v.y, v.z);
+}
+
+// a += block (x_j - x_i), or block x_i for the diagonal block (j = i)
+template <typename TB, typename A>
+__device__ __forceinline__ void apply_block(const RawBlock<TB> &B, const float3 &pj, A x0, A x1, A x2, A &a0, A &a1,
+                                            A &a2) {
+    typename BlockIO<TB>::R v[9];
+    B.get(v);
+    const A f = (B.col() & DIAG) ? A(0) : A(-1);
+    const A d0 = __builtin_fma(f, x0, (A)pj.x), d1 = __builtin_fma(f, x1, (A)pj.y), d2 = __builtin_fma(f, x2, (A)pj.z);
+    a0 += dot3((A)v[0], d0, (A)v[1], d1, (A)v[2], d2);
+    a1 += dot3((A)v[3], d0, (A)v[4], d1, (A)v[5], d2);
+    a2 += dot3((A)v[6], d0, (A)v[7], d1, (A)v[8], d2);
+}
+
+// The lane's N published values: `at(c)` gives the slot of value c, or null
+// where the lane has none (its value is 0).  Polls until all are there; false
+// when the wait gave up.
+template <int N, typename F>
+__device__ __forceinline__ bool poll(F at, double (&v)[N]) {
+    u64 b[N];
+    for (int spin = 0; spin < SPIN_LIMIT; ++spin) {
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            const u64 *p = at(c);
+            b[c] = 0ull;
+            if (p) b[c] = agent_load(p);
+        }
+        bool all = true;
+#pragma unroll
+        for (int c = 0; c < N; ++c) all = all && b[c] != EMPTY;
+        if (__all(all)) {
+#pragma unroll
+            for (int c = 0; c < N; ++c) v[c] = __builtin_bit_cast(double, b[c]);
+            return true;
+        }
+    }
+    return false;
+}
+
+// Sum in order of L values that poll() left in LDS, by the lane of their
+// chain (chains an odd number of doubles apart, so the lanes' reads spread
+// over the banks).
+template <int L>
+__device__ __forceinline__ double chain_sum(const double *v) {
+    double val[L], s = 0.0;
+#pragma unroll
+    for (int i = 0; i < L; ++i) val[i] = v[i];
+#pragma unroll
+    for (int i = 0; i < L; ++i) s += val[i];
+    return s;
+}
+
+// NS: 64-row slices per wavefront.  NS = 1 (SPLIT): the two slices of a pair
+// are on two wavefronts (w and w + pairs); NS = 2: one pair per wavefront.
+// KIND: 0 Jacobi, 1 block Jacobi.
+template <typename TB, typename TV, int NS, int NT, int KIND>
+__global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
+    extern __shared__ float4 pwin[];
+    constexpr bool SPLIT = NS == 1;
+    constexpr int NPL = SPLIT ? NT / 128 : 8;   // pairs per workgroup
+    constexpr int K = Keep<TB, NS, NT>::K, U = Keep<TB, NS, NT>::U, GR = Keep<TB, NS, NT>::G;
+    // the iterate, and for the kernels that keep most blocks in registers the
+    // residual too, in LDS behind the window: component c of slice j's row of
+    // thread t at (c NS + j) NT + t
+    constexpr bool RLDS = NS == 2;
+    typedef typename SpmvAcc<TB>::T Acc;
+    typedef typename std::conditional<KIND == 0, TV, float>::type TE;   // exchanged planes
+    __shared__ double ssum[2][NPL];    // slice sums of p.q, [half][local pair]
+    __shared__ double wsum[2][NPL + 8];   // pair sums of r.z and r.r
+    __shared__ double P1[16], P2[2][4];    // wavefront sums
+    __shared__ double2 pass[SPLIT ? NPL : 1][WAVE];
+    __shared__ int bad;
+    const int4 G = A.wg[blockIdx.x];
+    const ResInst I = A.inst[G.x];
+    if (A.inst_win[G.x] > A.win_cap) return;
+    PcgState &T = A.st[G.x];
+    if (T.done) return;   // written by the team's first workgroup at its end, after everyone has started
+    const int par = A.par;
+    double rz = T.rzp[par];
+    const double thresh = T.thresh;
+    const int maxit = T.maxit;
+    int iters = T.iters, flags = 0;
+    const int t0 = threadIdx.x, nt = blockDim.x;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)), nw = nt / WAVE;
+    const int np = G.z;
+    const int2 W = A.win[blockIdx.x];
+    const int lo = W.x, wn = W.y - W.x + 1;
+    if (t0 == 0) bad = 0;
+    for (int k = t0; k < wn; k += nt) pwin[k] = ld3(A.p, lo + k);
+    // rows of this workgroup: [a0, a1) and [b0, b1); the other rows of its
+    // window are its halo
+    const int it0 = G.y / 16, w0 = G.y % 16, rend = I.row0 + I.nrows;
+    const int a0 = min(rend, I.row0 + 2048 * it0 + 64 * w0), a1 = min(rend, a0 + 64 * np);
+    const int b0 = min(rend, I.row0 + 2048 * it0 + 1024 + 64 * w0), b1 = min(rend, b0 + 64 * np);
+    const int h0 = max(0, a0 - lo), h1 = max(0, min(b0, W.y + 1) - a1), h2 = max(0, W.y + 1 - max(a1, b1));
+    const int hb = max(a1, b1), nh = h0 + h1 + h2;
+
+    // the wavefront's slices j: local pair, half; first row r0 (rend: none);
+    // the lane's row in stored order, relative to the window (-1 none)
+    int r0[NS], srel[NS];
+    SliceSlots slots[NS];
+    RawBlock<TB> keep[NS][K > 0 ? K : 1];
+    TV rv_[RLDS ? 1 : NS][3], q[NS][3];
+    TV *const X = (TV *)A.x, *const R = (TV *)A.r;
+    TE *const E = (TE *)A.exch;
+    TV *const LX = (TV *)(pwin + A.win_rows);
+    TV *const LR = LX + 3 * NS * NT;
+    double *const raw = (double *)(LX + 3 * NS * NT * res_vectors(NS));   // published values, RAW of them
+    auto pair_of = [&](int j) { return SPLIT ? (w < np ? w : w - np) : w; };
+    auto half_of = [&](int j) { return SPLIT ? (w < np ? 0 : 1) : j; };
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const int lane = lane_id();
+        const int pl = pair_of(j), pg = G.y + pl;
+        const int sl = 32 * (pg / 16) + 16 * half_of(j) + pg % 16;
+        const bool have = pl < np && sl < I.nsl && (!SPLIT || w < 2 * np);
+        r0[j] = have ? I.row0 + 64 * sl : rend;
+        srel[j] = -1;
+        slots[j].meta = 0u;
+        slots[j].base = slots[j].n = 0;
+        const int row = r0[j] + lane;
+        if (have) {
+            const int s = I.slice0 + sl;
+            const int srow = A.lane_row[s * WAVE + lane], cnt = (int)A.slot_cnt[s * WAVE + lane];
+            srel[j] = srow >= 0 ? srow - lo : -1;
+            slots[j].base = A.slice_vbase[s];
+            slots[j].n = __popcll(__ballot(cnt > 0));
+            slots[j].meta = (row < rend ? (unsigned)A.row_lane[row] : 0u) | (unsigned)cnt << 6 |
+                            (unsigned)wave_excl_scan(slot_width(cnt)) << 13;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            keep[j][k].clear();
+            keep[j][k].set_col((unsigned)max(srel[j], 0));
+            if (slots[j].n > 0)
+                load_slot<TB>(keep[j][k], A, slots[j], k, lane, r0[j] - lo, (unsigned)max(srel[j], 0));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const bool in = row < rend;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            LX[(c * NS + j) * NT + t0] = in ? X[3 * row + c] : TV(0);
+            const TV rc = in ? R[3 * row + c] : TV(0);
+            if constexpr (RLDS)
+                LR[(c * NS + j) * NT + t0] = rc;
+            else
+                rv_[j][c] = rc;
+            q[j][c] = TV(0);
+        }
+    }
+    // Published values.  A workgroup's values of a meeting are consecutive
+    // slots, written by one store instruction of its first wavefront(s) with
+    // each copy's values on consecutive lanes: written one by one by the
+    // wavefronts that form them, 8 values a workgroup took 5.0 us per meeting
+    // of 256 workgroups against 2.65 us.
+    //   p.q: SPLIT: slices, at 2 pair + half; else 8-slice sums, at 2 (8-pair
+    //        run) + half;
+    //   r.z, r.r: SPLIT: pairs, at 2 pair + which; else the run that starts an
+    //        item as one sum, the other's pairs (32 slots an item).
+    const int vq = SPLIT ? 2 * I.k : 2;
+    const int vr = SPLIT ? 2 * I.k : (w0 == 0 ? 2 : 16);
+    const int cq = t0 % vq, cr = t0 % vr;
+    const int dq = t0 < vq * REPLICAS ? t0 / vq * A.slot_rep + I.pq_off + G.w * vq + cq : -1;
+    const int dr = t0 < vr * REPLICAS
+                       ? t0 / vr * A.slot_rep + A.slot_rz + I.rz_off + (SPLIT ? G.w * vr : 32 * it0 + 2 * w0) + cr
+                       : -1;
+    const u64 *const mine = A.slots + (size_t)(blockIdx.x % REPLICAS) * A.slot_rep;
+    wait_stores();
+    __syncthreads();
+
+    int done = 0;
+    for (int it = 0;; ++it) {
+        const int buf = (it & 1) * A.slot_n, nbuf = A.slot_n - buf;
+        // the lane as a new value each iteration: no address formed from it is
+        // carried through the loop in registers of its own
+        int lane = lane_id();
+        asm volatile("" : "+v"(lane));
+        const int t = WAVE * w + lane;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) asm volatile("" : "+v"(srel[j]));
+        // every workgroup has read the previous iteration's p.q
+        if (dq >= 0) agent_store(A.slots + dq + nbuf, EMPTY);
+        // ---- q = A p, slice sums of p.q.  Blocks past the kept ones stream
+        // from memory: while a group is applied the next one's loads are in
+        // flight, over the end of a slice into the wavefront's next one.
+        RawBlock<TB> cur[U];
+        bool ahead = false;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            __builtin_amdgcn_sched_barrier(0);   // one slice's loads at a time
+            if (r0[j] >= rend) continue;         // uniform per wavefront
+            const int self = max(srel[j], 0), n = slots[j].n;
+            const float4 ps = pwin[self];
+            const Acc x0 = ps.x, x1 = ps.y, x2 = ps.z;
+            Acc s0 = 0, s1 = 0, s2 = 0;
+            const double m = A.mass[lo + self];
+            if (n > K && !ahead) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) load_slot<TB>(cur[u], A, slots[j], K + u, lane, r0[j] - lo, (unsigned)self);
+            }
+            // kept blocks, GR at a time; the next ones' rows of the window
+            // are read while these are applied
+            float3 pj[2][GR];
+#pragma unroll
+            for (int k = 0; k < K + GR; k += GR) {
+                if (SPLIT && k >= n + GR) break;   // uniform
+#pragma unroll
+                for (int u = k; u < k + GR; ++u)
+                    if (u < K) {
+                        keep[j][u].refresh();
+                        pj[k / GR & 1][u - k] = block_p(keep[j][u], pwin);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+                if (k == 0) continue;
+#pragma unroll
+                for (int u = k - GR; u < k; ++u)
+                    if (u < K)
+                        apply_block<TB, Acc>(keep[j][u], pj[(k / GR & 1) ^ 1][u - k + GR], x0, x1, x2, s0, s1, s2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            constexpr int J1 = NS - 1;
+            const int jn = j < J1 ? j + 1 : j;
+            const bool cross = j < J1 && r0[jn] < rend && slots[jn].n > K;
+            ahead = cross && n > K;
+            for (int k = K; k < n; k += U) {
+                RawBlock<TB> nxt[U];
+                float3 ps4[U];
+                const bool over = cross && k + U >= n;
+                SliceSlots S = slots[j];
+                S.meta = over ? slots[jn].meta : S.meta;
+                S.base = over ? slots[jn].base : S.base;
+                S.n = over ? slots[jn].n : S.n;
+                const int sf = over ? max(srel[jn], 0) : self, rr = over ? r0[jn] : r0[j], kn = over ? K : k + U;
+#pragma unroll
+                for (int u = 0; u < U; ++u) load_slot<TB>(nxt[u], A, S, kn + u, lane, rr - lo, (unsigned)sf);
+#pragma unroll
+                for (int u = 0; u < U; ++u) ps4[u] = block_p(cur[u], pwin);
+#pragma unroll
+                for (int u = 0; u < U; ++u) apply_block<TB, Acc>(cur[u], ps4[u], x0, x1, x2, s0, s1, s2);
+#pragma unroll
+                for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+            }
+            double y0 = (double)s0, y1 = (double)s1, y2 = (double)s2;
+            if constexpr (BlockIO<TB>::SCALED) {
+                const double vi = A.vscale_inv[2 * (I.slice0 + (r0[j] - I.row0) / WAVE)];
+                y0 *= vi; y1 *= vi; y2 *= vi;
+            }
+            const TV q0 = (TV)__builtin_fma(m, (double)x0, y0), q1 = (TV)__builtin_fma(m, (double)x1, y1),
+                     q2 = (TV)__builtin_fma(m, (double)x2, y2);
+            double pq = dot3((double)x0, (double)q0, (double)x1, (double)q1, (double)x2, (double)q2);
+            if (srel[j] < 0) pq = 0.0;
+            const double s64 = wave_sum(pq);
+            if (lane == 0) ssum[half_of(j)][pair_of(j)] = s64;
+            // natural row order for the vector updates
+            const int perm = (int)(slots[j].meta & 63u);
+            q[j][0] = __shfl(q0, perm, WAVE);
+            q[j][1] = __shfl(q1, perm, WAVE);
+            q[j][2] = __shfl(q2, perm, WAVE);
+        }
+        __syncthreads();
+        if (dq >= 0) {
+            double sum;
+            if constexpr (SPLIT) {
+                sum = ssum[cq & 1][cq / 2];
+            } else {
+                // an SpMV item: eight slices in order
+                const int sl = 32 * it0 + 16 * cq + w0;
+                double val[8];
+                sum = 0.0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) val[i] = ssum[cq][i];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sum += sl + i < I.nsl ? val[i] : 0.0;
+            }
+            agent_store(A.slots + dq + buf, sum_bits(sum));
+        }
+        // preconditioner entries, in flight while the sums are exchanged
+        float pre[NS][KIND == 0 ? 3 : 6];
+        auto load_pre = [&](int j) {
+            const int row = r0[j] + lane;
+            if (row >= rend) return;
+            if constexpr (KIND == 0) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) pre[j][c] = A.pre[3 * row + c];
+            } else {
+                const float2 *b = (const float2 *)(A.pre + 6 * (int64_t)row);
+                const float2 u = b[0], v = b[1], z = b[2];
+                pre[j][0] = u.x; pre[j][1] = u.y; pre[j][2] = v.x;
+                pre[j][3] = v.y; pre[j][4] = z.x; pre[j][5] = z.y;
+            }
+        };
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < NS; ++j) load_pre(j);
+        __builtin_amdgcn_sched_barrier(0);
+        // ---- p.q of the instance
+        double pq;
+        if constexpr (SPLIT) {
+            // chunk c of this wavefront: slices 64 (w + nw c) ..
+            double v[4];
+            if (!poll<4>(
+                    [&](int c) {
+                        const int s = 64 * (w + nw * c) + lane;
+                        return s < I.nsl ? mine + buf + I.pq_off + 2 * (16 * (s / 32) + s % 16) + (s / 16 & 1) : nullptr;
+                    },
+                    v))
+                bad = 1;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int s = 64 * (w + nw * c) + lane;
+                if (s < 8 * I.ngroups) raw[9 * (s / 8) + s % 8] = v[c];
+            }
+            __syncthreads();
+            // lane: an SpMV item; wavefront: 64 of them
+            if (64 * w < I.ngroups) {
+                const double s = wave_sum(64 * w + lane < I.ngroups ? chain_sum<8>(raw + 9 * (64 * w + lane)) : 0.0);
+                if (lane == 0) P1[w] = s;
+            }
+        } else {
+            // thread t: SpMV item t
+            double v[1];
+            if (!poll<1>(
+                    [&](int) {
+                        return t < I.ngroups ? mine + buf + I.pq_off + ((t & ~3) | (t & 1) << 1 | (t >> 1 & 1)) : nullptr;
+                    },
+                    v))
+                bad = 1;
+            if (64 * w < I.ngroups) {
+                const double s = wave_sum(0.0 + v[0]);
+                if (lane == 0) P1[w] = s;
+            }
+        }
+        __syncthreads();
+        pq = 0.0;
+        for (int k = 0; 64 * k < I.ngroups; ++k) pq += P1[k];
+        if (bad) {
+            if (t == 0) {
+                atomicOr(&T.flags, 4);
+                T.done = 1;
+            }
+            return;
+        }
+        const double alpha = rz / pq;
+        if (!(pq > 0.0) || !isfinite(alpha)) {
+            flags |= isfinite(pq) ? 1 : 2;
+            done = 1;
+            break;
+        }
+        // every workgroup has read the previous iteration's r.z
+        if (dr >= 0) agent_store(A.slots + dr + nbuf, EMPTY);
+        // ---- r -= alpha q, z = P^-1 r, partial sums; x += alpha p
+        float zf[NS][3];
+        double arz = 0.0, arr = 0.0;
+        // slice j's rows, and their part of the sums, which continue those of
+        // the pair's first slice
+        auto update_rows = [&](int j, double (&rk)[3], double (&zk)[3]) {
+            const int row = r0[j] + lane;
+            if (row >= rend) return;
+            TV rv[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int l = (c * NS + j) * NT + t;
+                rv[c] = (TV)__builtin_fma(-alpha, (double)q[j][c], (double)(RLDS ? LR[l] : rv_[RLDS ? 0 : j][c]));
+                rk[c] = rv[c];
+                if constexpr (RLDS)
+                    LR[l] = rv[c];
+                else
+                    rv_[j][c] = rv[c];
+            }
+            if constexpr (KIND != 0) {
+                block_times(pre[j], rk, zk[0], zk[1], zk[2]);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) zf[j][c] = (float)zk[c];
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                if constexpr (KIND == 0)
+                    agent_store_f(E + (size_t)c * A.nv + row, rv[c]);
+                else
+                    agent_store_f(E + (size_t)c * A.nv + row, zf[j][c]);
+            }
+            const float4 po = pwin[row - lo];
+            const float pc[3] = {po.x, po.y, po.z};
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                TV &xc = LX[(c * NS + j) * NT + t];
+                xc = (TV)__builtin_fma(alpha, (double)pc[c], (double)xc);
+            }
+        };
+        auto add_rows = [&](int j, bool first, const double (&rk)[3], const double (&zk)[3], double &rzs, double &rrs) {
+            if (r0[j] + lane >= rend) return;
+            sum_rr(rrs, rk, first);
+            if constexpr (KIND == 0)
+                sum_rz_jacobi(rzs, rk, pre[j]);
+            else
+                rzs += dot3(rk[0], zk[0], rk[1], zk[1], rk[2], zk[2]);
+        };
+        if constexpr (SPLIT) {
+            // the second slice's wavefront continues the first one's sums
+            double rk[3], zk[3];
+            update_rows(0, rk, zk);
+            if (w < np) {
+                add_rows(0, true, rk, zk, arz, arr);
+                pass[w][lane] = make_double2(arz, arr);
+            }
+            __syncthreads();
+            if (w >= np && w < 2 * np) {
+                const double2 c = pass[w - np][lane];
+                arz = c.x;
+                arr = c.y;
+                add_rows(0, false, rk, zk, arz, arr);
+                const double s0 = wave_sum(arz), s1 = wave_sum(arr);
+                if (lane == 0) {
+                    wsum[0][w - np] = s0;
+                    wsum[1][w - np] = s1;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NS; ++j) {
+                double rk[3], zk[3];
+                __builtin_amdgcn_sched_barrier(0);   // one slice's values at a time
+                update_rows(j, rk, zk);
+                add_rows(j, j == 0, rk, zk, arz, arr);
+            }
+            const double s0 = wave_sum(arz), s1 = wave_sum(arr);
+            if (lane == 0) {
+                wsum[0][w] = s0;
+                wsum[1][w] = s1;
+            }
+        }
+        wait_stores();
+        __syncthreads();
+        if (dr >= 0) {
+            double sum;
+            if constexpr (SPLIT) {
+                sum = wsum[cr & 1][cr / 2];
+            } else {
+                // the item's first eight pairs in order, or one pair
+                const int pl = cr / 2, nr = w0 == 0 ? min(8, np) : 1;
+                double val[8];
+                sum = 0.0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) val[i] = wsum[cr & 1][pl + i];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sum += i < nr ? val[i] : 0.0;
+            }
+            agent_store(A.slots + dr + buf, sum_bits(sum));
+        }
+        // ---- r.z and r.r of the instance
+        // value e: SPLIT: pair e / 2; else (32 slots an item) the sum of the
+        // item's first eight pairs, then each of the others
+        constexpr int PER = SPLIT ? 32 : 18, ST = SPLIT ? 17 : 9, NC = SPLIT ? 4 : 5;
+        double v[NC];
+        const int ne = PER * I.nitems;
+        if (!poll<NC>(
+                [&](int c) {
+                    const int e = t + nt * c, i = e / PER, k = e % PER;
+                    const bool on = e < ne && (SPLIT ? 32 * i + k / 2 < I.nsl : k < 2 || 32 * i + 7 + k / 2 < I.nsl);
+                    return on ? mine + buf + A.slot_rz + I.rz_off + 32 * i + (SPLIT || k < 2 ? k : 14 + k) : nullptr;
+                },
+                v))
+            bad = 1;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int e = t + nt * c;
+            if (e < ne) raw[(e & 1) * (RAW / 2) + ST * (e / PER) + e % PER / 2] = v[c];
+        }
+        __syncthreads();
+        // lane: an item; wavefronts: r.z and r.r of 64 items
+        const int i = 64 * (w / 2) + lane;
+        if (64 * (w / 2) < I.nitems) {
+            const double s = wave_sum(i < I.nitems ? chain_sum<PER / 2>(raw + (w & 1) * (RAW / 2) + ST * i) : 0.0);
+            if (lane == 0) P2[w & 1][w / 2] = s;
+        }
+        __syncthreads();
+        double tz = 0.0, tr = 0.0;
+        for (int k = 0; 64 * k < I.nitems; ++k) {
+            tz += P2[0][k];
+            tr += P2[1][k];
+        }
+        if (bad) {
+            if (t == 0) {
+                atomicOr(&T.flags, 4);
+                T.done = 1;
+            }
+            return;
+        }
+        // ---- convergence, beta, p = z + beta p over the window
+        const double beta = tz / rz;
+        const bool notfinite = !isfinite(tr) || !isfinite(tz);
+        const bool conv = tr <= thresh;
+        const bool new_dir = !(notfinite || conv);
+        rz = tz;
+        ++iters;
+        if (notfinite) {
+            flags |= 2;
+            done = 1;
+        } else if (conv || iters >= maxit) {
+            done = 1;
+        }
+        const bool finished = done || it + 1 >= A.max_iters;
+        if (t == 0 && G.w == 0) {
+            T.rr = tr;
+            if (new_dir) T.rzd = tz;
+        }
+        auto direct = [&](int row, double z0, double z1, double z2) {
+            const float4 po = pwin[row - lo];
+            pwin[row - lo] = make_float4((float)__builtin_fma(beta, (double)po.x, z0),
+                                         (float)__builtin_fma(beta, (double)po.y, z1),
+                                         (float)__builtin_fma(beta, (double)po.z, z2), 0.0f);
+        };
+        if (new_dir) {
+            if (!finished) {
+                // four rows' loads in flight per thread
+                for (int hh = t; hh < nh; hh += 4 * nt) {
+                    TE e[4][3];
+                    int row[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int h = min(hh + u * nt, nh - 1);
+                        row[u] = h < h0 ? lo + h : (h < h0 + h1 ? a1 + h - h0 : hb + h - h0 - h1);
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) e[u][c] = agent_load_f(E + (size_t)c * A.nv + row[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (hh + u * nt >= nh) break;
+                        double z[3];
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            z[c] = (double)e[u][c];
+                            if constexpr (KIND == 0) z[c] *= (double)A.pre[3 * row[u] + c];
+                        }
+                        direct(row[u], z[0], z[1], z[2]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NS; ++j) {
+                const int row = r0[j] + lane;
+                if (row >= rend) continue;
+                if constexpr (KIND == 0) {
+                        double z[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        z[c] = (double)(RLDS ? LR[(c * NS + j) * NT + t] : rv_[RLDS ? 0 : j][c]) * (double)pre[j][c];
+                    direct(row, z[0], z[1], z[2]);
+                } else {
+                    direct(row, (double)zf[j][0], (double)zf[j][1], (double)zf[j][2]);
+                }
+            }
+        }
+        if (finished) break;
+        __syncthreads();
+    }
+    // ---- results: r, x and the own rows of p
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const int row = r0[j] + lane_id();
+        if (row < rend) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                R[3 * row + c] = RLDS ? LR[(c * NS + j) * NT + t0] : rv_[RLDS ? 0 : j][c];
+                X[3 * row + c] = LX[(c * NS + j) * NT + t0];
+            }
+            const float4 po = pwin[row - lo];
+            st3(A.p, row, po.x, po.y, po.z);
+        }
+    }
+    if (t0 == 0 && G.w == 0) {
+        T.rzp[par] = rz;
+        T.live[0] = T.live[1] = 0;
+        T.iters = iters;
+        T.flags |= flags;
+        T.done = done;
+    }
+}
+
+// Block-column window of every resident workgroup and the largest one of each
+// instance (block-CSR columns are ascending, so the ends of each row suffice).
+__global__ void __launch_bounds__(256) k_res_windows(const ResInst *inst, const int4 *wg, const int *rowptr,
+                                                     const int *colidx, int2 *win, int *inst_win) {
+    __shared__ int sh[2][4];
+    const int4 G = wg[blockIdx.x];
+    const ResInst I = inst[G.x];
+    const int rend = I.row0 + I.nrows;
+    int lo = 0x7fffffff, hi = -1;
+    for (int k = threadIdx.x; k < 128 * G.z; k += blockDim.x) {
+        const int pg = G.y + k / 128, half = (k / 64) & 1;
+        const int i = I.row0 + 2048 * (pg / 16) + 1024 * half + 64 * (pg % 16) + k % 64;
+        if (i >= rend) continue;
+        lo = min(lo, colidx[rowptr[i]]);
+        hi = max(hi, colidx[rowptr[i + 1] - 1]);
+    }
+    for (int m = 32; m >= 1; m >>= 1) {
+        lo = min(lo, __shfl_xor(lo, m, WAVE));
+        hi = max(hi, __shfl_xor(hi, m, WAVE));
+    }
+    const int w = threadIdx.x / WAVE;
+    if (lane_id() == 0) {
+        sh[0][w] = lo;
+        sh[1][w] = hi;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < (int)blockDim.x / WAVE; ++k) {
+            lo = min(lo, sh[0][k]);
+            hi = max(hi, sh[1][k]);
+        }
+        win[blockIdx.x] = make_int2(lo, hi);
+        atomicMax(&inst_win[G.x], hi - lo + 1);
+    }
+}
+
+__global__ void k_res_clear(u64 *slots, size_t n) {
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) slots[i] = EMPTY;
+}
+
+// ---------------------------------------------------------------- host side
+// Teams.  With P = 1, 2 or 4 pairs per workgroup (one slice per wavefront,
+// 2 P wavefronts) or 8 (two slices per wavefront of 8), the smallest P whose
+// teams fit the compute units at once is taken: one workgroup per unit, on as
+// many units as there is work for.  Beyond (more than 1,024 rows a unit) the
+// three-launch iteration runs: whole items per workgroup kept 4 of 12 blocks a
+// row in registers and streamed the rest with 8 wavefronts in flight, 41.0 us
+// against 43.3 us at 420k rows but 62 -> 73 us for a batch in two rounds, and
+// half of the chip idle just past 262k rows.
+pc_status resident_plan(Ctx *ctx) {
+    ResPlan &P = ctx->res;
+    P.valid = false;
+    const int ninst = (int)ctx->inst_row0_h.size() - 1;
+    int dev = 0, ncu = 0;
+    PC_HIP(hipGetDevice(&dev));
+    PC_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    if (ncu < 1) return PC_OK;
+    ncu = std::min(ncu, 256);   // P1, P2 and RAW hold the sums of 256 workgroups
+    std::vector<ResInst> inst(ninst);
+    int slice0 = 0;
+    for (int i = 0; i < ninst; ++i) {
+        ResInst &I = inst[i];
+        I.row0 = ctx->inst_row0_h[i];
+        I.nrows = ctx->inst_row0_h[i + 1] - I.row0;
+        I.slice0 = slice0;
+        I.nsl = (I.nrows + WAVE - 1) / WAVE;
+        slice0 += I.nsl;
+        I.ngroups = (I.nsl + 7) / 8;
+        I.nitems = (I.nsl + 31) / 32;
+    }
+    auto pairs_of = [](const ResInst &I) { return 16 * (I.nitems - 1) + std::min(16, I.nsl - 32 * (I.nitems - 1)); };
+    auto team_of = [&](const ResInst &I, int per) { return (pairs_of(I) + per - 1) / per; };
+    int per = 0;
+    for (int cand : {1, 2, 4, 8}) {
+        int64_t sum = 0;
+        for (const ResInst &I : inst) sum += team_of(I, cand);
+        if (sum <= ncu) {
+            per = cand;
+            break;
+        }
+    }
+    if (per == 0) return PC_OK;
+    P.ns = per <= 4 ? 1 : 2;
+    P.threads = per <= 4 ? 2 * per * WAVE : 512;
+    std::vector<int4> wg;
+    int npq = 0, nrz = 0;
+    for (int i = 0; i < ninst; ++i) {
+        ResInst &I = inst[i];
+        I.k = per;
+        I.team = team_of(I, per);
+        const int pairs = pairs_of(I);
+        for (int g = 0; g < I.team; ++g) wg.push_back(int4{i, g * per, std::min(per, pairs - g * per), g});
+        I.pq_off = npq;
+        I.rz_off = nrz;
+        npq += per <= 4 ? 32 * I.nitems : (4 * I.nitems + 15) / 16 * 16;   // whole cache lines
+        nrz += 32 * I.nitems;
+    }
+    P.slot_rz = npq;
+    P.slot_n = npq + nrz;
+    P.slot_rep = 2 * P.slot_n + 32;
+    P.coop = false;
+    for (const ResInst &I : inst) P.coop = P.coop || I.team > 1;
+    pc_status st;
+    auto grow = [&](void **p, size_t &have, size_t bytes) -> pc_status {
+        if (bytes <= have) return PC_OK;
+        if (*p) dev_free(ctx, *p);
+        *p = nullptr;
+        have = 0;
+        pc_status s = dev_alloc(ctx, p, bytes);
+        if (s == PC_OK) have = bytes;
+        return s;
+    };
+    if ((st = grow((void **)&P.inst, P.inst_bytes, sizeof(ResInst) * ninst))) return st;
+    if ((st = grow((void **)&P.wg, P.wg_bytes, sizeof(int4) * wg.size()))) return st;
+    if ((st = grow((void **)&P.win, P.win_bytes, sizeof(int2) * wg.size()))) return st;
+    if ((st = grow((void **)&P.slots, P.slot_bytes, sizeof(u64) * (size_t)REPLICAS * P.slot_rep))) return st;
+    PC_HIP(hipMemcpy(P.inst, inst.data(), sizeof(ResInst) * ninst, hipMemcpyHostToDevice));
+    PC_HIP(hipMemcpy(P.wg, wg.data(), sizeof(int4) * wg.size(), hipMemcpyHostToDevice));
+    P.nwg = (int)wg.size();
+    P.valid = true;
+    return PC_OK;
+}
+
+void resident_free(Ctx *ctx) {
+    ResPlan &P = ctx->res;
+    dev_free(ctx, P.inst);
+    dev_free(ctx, P.wg);
+    dev_free(ctx, P.win);
+    dev_free(ctx, P.slots);
+    P = ResPlan{};
+}
+
+void resident_windows(Ctx *ctx, int *inst_win, hipStream_t s) {
+    const ResPlan &P = ctx->res;
+    hipLaunchKernelGGL(k_res_windows, dim3(P.nwg), dim3(256), 0, s, P.inst, P.wg, ctx->rowptr, ctx->colidx, P.win,
+                       inst_win);
+}
+
+template <typename TB, typename TV, int NS, int NT, int KIND>
+static pc_status launch_kind(Ctx *ctx, ResArgs &A, hipStream_t s) {
+    const ResPlan &P = ctx->res;
+    const size_t lds = sizeof(float4) * (size_t)P.win_rows + sizeof(TV) * (size_t)(3 * NS * NT * res_vectors(NS)) +
+                       sizeof(double) * RAW;
+    const void *fn = (const void *)k_pcg_resident<TB, TV, NS, NT, KIND>;
+    PC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const size_t nslots = (size_t)REPLICAS * P.slot_rep;
+    hipLaunchKernelGGL(k_res_clear, dim3((nslots + 255) / 256), dim3(256), 0, s, A.slots, nslots);
+    if (P.coop) {
+        void *args[] = {&A};
+        PC_HIP(hipLaunchCooperativeKernel(fn, dim3(P.nwg), dim3(P.threads), args, (unsigned)lds, s));
+    } else {
+        hipLaunchKernelGGL((k_pcg_resident<TB, TV, NS, NT, KIND>), dim3(P.nwg), dim3(P.threads), lds, s, A);
+    }
+    PC_HIP(hipGetLastError());
+    return PC_OK;
+}
+
+template <typename TB, typename TV, int NS, int NT>
+static pc_status launch_ns(Ctx *ctx, ResArgs &A, hipStream_t s) {
+    return ctx->precond == 0 ? launch_kind<TB, TV, NS, NT, 0>(ctx, A, s) : launch_kind<TB, TV, NS, NT, 1>(ctx, A, s);
+}
+
+int resident_win_max(const Ctx *ctx) {
+    const ResPlan &P = ctx->res;
+    const int bytes = ctx->inner32 ? 4 : 8;
+    const int kept = 3 * P.ns * 512 * res_vectors(P.ns) * bytes + (int)sizeof(double) * RAW;
+    return (RES_LDS - kept) / (int)sizeof(float4);
+}
+
+// Storage and vector types the resident kernel is built for: FP16 and BF16
+// blocks with FP32 inner vectors (their refinement sweeps), FP32 and FP64
+// blocks with FP64 vectors, and FP64 blocks with FP32 inner vectors (a sweep
+// after a fallback).  Wider types keep at most four slices per wavefront in
+// registers.
+bool resident_fits(const Ctx *ctx) {
+    const bool low = ctx->dtype == PC_BF16 || ctx->dtype == PC_F16;
+    return ctx->res.valid && ctx->res.win_rows > 0 && (!low || ctx->inner32);
+}
+
+template <typename TB>
+pc_status resident_launch(Ctx *ctx, const SpmvArgs &M, int max_iters, hipStream_t s) {
+    const ResPlan &P = ctx->res;
+    ResArgs A{};
+    A.slice_vbase = M.slice_vbase;
+    A.lane_row = M.lane_row;
+    A.row_lane = ctx->row_lane;
+    A.slot_cnt = M.slot_cnt;
+    A.jdel = ctx->jdel;   // offsets within a window of at most 9,728 rows always fit 16 bits
+    A.jval = M.jval;
+    A.mass = M.mass;
+    A.vscale_inv = ctx->f16_scale ? ctx->f16_scale + 1 : nullptr;
+    A.nv = ctx->nv;
+    A.inst = P.inst;
+    A.wg = P.wg;
+    A.win = P.win;
+    A.inst_win = P.inst_win;
+    A.win_rows = A.win_cap = P.win_rows;
+    A.st = ctx->st;
+    A.p = ctx->p;
+    A.pre = ctx->precond == 0 ? ctx->dinv : ctx->binv;
+    A.exch = ctx->precond == 0 && !ctx->inner32 ? (void *)ctx->q : (void *)ctx->zb;
+    A.slots = P.slots;
+    A.slot_n = P.slot_n;
+    A.slot_rep = P.slot_rep;
+    A.slot_rz = P.slot_rz;
+    A.par = ctx->cg_par;
+    A.max_iters = max_iters;
+    A.x = ctx->inner32 ? (void *)ctx->e32 : (void *)ctx->x;
+    A.r = ctx->inner32 ? (void *)ctx->r32 : (void *)ctx->r;
+    constexpr bool low = std::is_same<TB, f16_t>::value || std::is_same<TB, bf16_t>::value;
+    constexpr bool f64 = std::is_same<TB, double>::value;
+    if constexpr (low || f64) {
+        if (ctx->inner32) {
+            if constexpr (f64) {   // 512 registers where 256 threads do
+                if (P.threads <= 256) return launch_ns<TB, float, 1, 256>(ctx, A, s);
+            }
+            if (P.ns == 1) return launch_ns<TB, float, 1, 512>(ctx, A, s);
+            if (P.ns == 2) return launch_ns<TB, float, 2, 512>(ctx, A, s);
+        }
+    }
+    if constexpr (!low) {
+        if (!ctx->inner32) {
+            if constexpr (f64) {
+                if (P.threads <= 256) return launch_ns<TB, double, 1, 256>(ctx, A, s);
+            }
+            if (P.ns == 1) return launch_ns<TB, double, 1, 512>(ctx, A, s);
+            if (P.ns == 2) return launch_ns<TB, double, 2, 512>(ctx, A, s);
+        }
+    }
+    ctx->err = "internal: resident CG variant";
+    return PC_ERR_ARG;
+}
+
+template pc_status resident_launch<double>(Ctx *, const SpmvArgs &, int, hipStream_t);
+template pc_status resident_launch<float>(Ctx *, const SpmvArgs &, int, hipStream_t);
+template pc_status resident_launch<bf16_t>(Ctx *, const SpmvArgs &, int, hipStream_t);
+template pc_status resident_launch<f16_t>(Ctx *, const SpmvArgs &, int, hipStream_t);
+
+}  // namespace pc
