@@ -113,7 +113,7 @@ static void free_all(Ctx *c) {
                     c->p, c->partials, c->partials_u, c->res2, c->counter, c->st, c->scan_tmp, c->jval_hi, c->slice_row0, c->slice_psize, c->slice_vbase, c->sitem_win, c->cverts, c->cw, c->cn, c->jdel, c->cg_pd, c->cg_s, c->e32, c->r32, c->q32,
                     c->row_slice, c->sitem, c->vitem, c->inst_sitem0, c->inst_vitem0, c->restart, c->maxit_d,
                     c->slot_off, c->rowlen_s, c->f16_scale, c->f16_part, c->inst_slice0, c->row_state, c->wide_rows, c->trec, c->hrec, c->crec, c->row_npairs,
-                    c->cols_tmp, c->pairs_tmp, c->win_info};
+                    c->cols_tmp, c->pairs_tmp, c->starts_tmp, c->win_info};
     for (void *p : ptrs) dev_free(c, p);
     resident_free(c);
     if (c->win_info_h) (void)hipHostFree(c->win_info_h);
@@ -217,8 +217,7 @@ pc_status pc_create(const pc_mesh *mesh, const pc_params *params, pc_ctx **out) 
         ctx->err = "more than 2^28 triangles or hinges";
         return fail(PC_ERR_ARG);
     }
-    // element records are indexed with 32-bit plane offsets (36 planes per
-    // triangle, up to 25 per hinge)
+    // 32-bit counts of element values (36 per triangle, up to 25 per hinge)
     if ((int64_t)36 * nt >= ((int64_t)1 << 31) || (int64_t)25 * nh >= ((int64_t)1 << 31)) {
         ctx->err = "more than 59,652,323 triangles or 85,899,345 hinges";
         return fail(PC_ERR_ARG);

@@ -5,17 +5,19 @@
 //   1. count the element corners incident to each vertex, scan, and fill the
 //      per-vertex incidence buckets (integer atomics only: the contents of a
 //      bucket are fixed, their order is not);
-//   2. one wavefront per row sorts its incidences (type, element, corner),
-//      derives the row's distinct block columns (sort + unique of the element
-//      neighbours) and its length; a scan gives the block-CSR row pointers;
+//   2. 16 lanes per row sort its incidences (type, element, corner), derive
+//      the row's distinct block columns (sort + unique of the element
+//      neighbours), its length and the elements that meet each column; a scan
+//      gives the block-CSR row pointers;
 //   3. per 64-row slice, rows are ordered by length for the solver layout;
-//   4. one wavefront per row evaluates its incident elements (one lane each),
-//      then lane s sums, in incidence order, the contributions of every
-//      element to block (i, cols[s]), in FP64 -- a deterministic segmented
-//      reduce with no floating-point atomics -- and writes the row's blocks,
-//      b_i, diag(A)_i and the pinned-neighbour remainder D_i.
+//   4. one workgroup per slice, lane r of every wavefront its row r: per
+//      column of the row, the contributions of every element to the block are
+//      summed in incidence order, in FP64 -- a deterministic segmented reduce
+//      with no floating-point atomics -- and the row's blocks, b_i, diag(A)_i
+//      and the pinned-neighbour remainder D_i are written.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "pc_ctx.h"
@@ -361,22 +363,46 @@ __global__ void k_check_contacts(int nc, int nv, const int *cv, const double *w,
 
 // ---------------------------------------------------------------- element records
 // Every element is evaluated once per assembly, one thread per element, into
-// SoA planes of FP64 (plane q of element e at rec[q * n + e]):
+// one record of FP64 values (a multiple of 16 bytes, written through LDS so
+// that a wavefront stores whole lines):
 //   triangle  the three off-diagonal stiffness blocks K_01, K_02, K_12 at x
-//             (planes 9 p .. 9 p + 8 for pair p = (0,1), (0,2), (1,2), 3x3
+//             (values 10 p .. 10 p + 8 for pair p = (0,1), (0,2), (1,2), 3x3
 //             row-major; K_lk = K_kl^T), then the forces on corners 0, 1, 2
-//             at the force state (planes 27 + 3 k .. 29 + 3 k);
+//             at the force state (values 30 + 4 k .. 32 + 4 k);
 //   hinge     0..11 G = sqrt(2 k_b c_h) grad theta at x (corner-major xyz),
 //             12 phi = -sqrt(2 k_b c_h) (theta - theta_bar) at the force
-//             state, and with the lookahead force 13..24 G at the force
-//             state; the force on corner k is phi G_k (of the force state),
-//             the stiffness block (k, l) is G_k G_l^T;
+//             state, and with the lookahead force 14 + 4 k .. 16 + 4 k G_k at
+//             the force state; the force on corner k is phi G_k (of the force
+//             state), the stiffness block (k, l) is G_k G_l^T;
 //   contact   0 k_c while the gap at x is below the thickness (else 0),
-//             1 k_c (eta - g) at the force state while below it (else 0).
+//             1 k_c (eta - g) at the force state while below it (else 0), as
+//             two planes.
 // The force state is x + h v with the lookahead force (rhs_mode 0), else x.
-constexpr int TREC = 36;
-constexpr int HREC = 13, HREC_LOOK = 25;
+// Bound by the writes (336 and 112 bytes an element): 155 and 96 us for 1.65M
+// triangles and 2.5M hinges, 4.4 TB/s with the reads.  Planes over all
+// elements took 102 and 83 us, but cost the value pass more (see there).
+constexpr int TREC = 42;
+constexpr int HREC = 14, HREC_LOOK = 30;
 constexpr int CREC = 2;
+constexpr int EVAL_THREADS = 64;   // one wavefront and its LDS per workgroup
+
+// The wavefront's records of N values (N even) at out + stride e, from lane
+// values v, through LDS (rows of N + 1 values).
+template <int N>
+__device__ __forceinline__ void store_records(double *lds, const double (&v)[N], double *out, int stride, int ne) {
+    const int lane = lane_id();
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < N; ++q) lds[lane * (N + 1) + q] = v[q];
+    __syncthreads();
+    for (int c = lane; c < ne * (N / 2); c += WAVE) {
+        const int e = c / (N / 2), q = 2 * (c % (N / 2));
+        double2 u;
+        u.x = lds[e * (N + 1) + q];
+        u.y = lds[e * (N + 1) + q + 1];
+        *reinterpret_cast<double2 *>(out + (int64_t)e * stride + q) = u;
+    }
+}
 
 // Membrane stiffness block K_kl (Sec. 2.5, solver Jacobian of Eq. 3):
 //   A0 [mu (b_k.b_l) F F^T + mu u_l u_k^T + lam u_k u_l^T + (b_k^T S+ b_l) I],  u_k = F b_k.
@@ -401,10 +427,11 @@ __device__ __forceinline__ void tri_block(const double F[3][2], const double Sp[
         }
 }
 
-__global__ void __launch_bounds__(256) k_tri_eval(int nt, const int *tri, const double *Bm, const double *A0,
-                                                  const double *x, const double *v, DevParams P, double *rec) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nt) return;
+__global__ void __launch_bounds__(EVAL_THREADS) k_tri_eval(int nt, const int *tri, const double *Bm, const double *A0,
+                                                           const double *x, const double *v, DevParams P,
+                                                           double *rec) {
+    __shared__ double lds[WAVE * 31];
+    const int e0 = blockIdx.x * EVAL_THREADS, ne = min(WAVE, nt - e0), e = e0 + min((int)threadIdx.x, ne - 1);
     TriShape sh;
     const double B0 = Bm[e], B1 = Bm[nt + e], B2 = Bm[2 * nt + e], B3 = Bm[3 * nt + e];
     sh.b[1][0] = B0; sh.b[1][1] = B1;
@@ -422,15 +449,18 @@ __global__ void __launch_bounds__(256) k_tri_eval(int nt, const int *tri, const 
     tri_F(xs, sh, F);
     tri_stress(F, P.mu, P.lam, S);
     psd_part(S, Sp);
-    const int64_t n = nt;
+    double blocks[30];
     const int pk[3] = {0, 0, 1}, pl[3] = {1, 2, 2};
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
         double K[9];
         tri_block(F, Sp, sh.b[pk[p]], sh.b[pl[p]], a0, P.mu, P.lam, K);
 #pragma unroll
-        for (int q = 0; q < 9; ++q) rec[(9 * p + q) * n + e] = K[q];
+        for (int q = 0; q < 9; ++q) blocks[10 * p + q] = K[q];
+        blocks[10 * p + 9] = 0.0;
     }
+    rec += (int64_t)e0 * TREC;
+    store_records(lds, blocks, rec, TREC, ne);
     // forces f_k = -A0 F S beta_k at the force state
     if (P.s_look != 0.0) {
         d3 ys[3];
@@ -439,20 +469,23 @@ __global__ void __launch_bounds__(256) k_tri_eval(int nt, const int *tri, const 
         tri_F(ys, sh, F);
         tri_stress(F, P.mu, P.lam, S);
     }
+    double f[12];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const double sb0 = S[0] * sh.b[k][0] + S[1] * sh.b[k][1];
         const double sb1 = S[1] * sh.b[k][0] + S[2] * sh.b[k][1];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) rec[(27 + 3 * k + a) * n + e] = -a0 * (F[a][0] * sb0 + F[a][1] * sb1);
+        for (int a = 0; a < 3; ++a) f[4 * k + a] = -a0 * (F[a][0] * sb0 + F[a][1] * sb1);
+        f[4 * k + 3] = 0.0;
     }
+    store_records(lds, f, rec + 30, TREC, ne);
 }
 
-__global__ void __launch_bounds__(256) k_hinge_eval(int nh, const int *hinge, const double *hcoef,
-                                                    const double *htbar, const double *x, const double *v,
-                                                    DevParams P, double *rec) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nh) return;
+__global__ void __launch_bounds__(EVAL_THREADS) k_hinge_eval(int nh, const int *hinge, const double *hcoef,
+                                                             const double *htbar, const double *x, const double *v,
+                                                             DevParams P, double *rec) {
+    __shared__ double lds[WAVE * 17];
+    const int e0 = blockIdx.x * EVAL_THREADS, ne = min(WAVE, nh - e0), e = e0 + min((int)threadIdx.x, ne - 1);
     const double sc = sqrt(2.0 * P.kb * hcoef[e]), tb = htbar[e];
     d3 xs[4], g[4];
     int vid[4];
@@ -461,31 +494,36 @@ __global__ void __launch_bounds__(256) k_hinge_eval(int nh, const int *hinge, co
         vid[q] = hinge[q * nh + e];
         xs[q] = ld3(x, vid[q]);
     }
-    const int64_t n = nh;
-    double th = 0.0;
+    const bool look = P.s_look != 0.0;
+    const int stride = look ? HREC_LOOK : HREC;
+    rec += (int64_t)e0 * stride;
+    double th = 0.0, r[14];
     const bool ok = hinge_eval(xs, th, g);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        rec[(3 * q) * n + e] = ok ? sc * g[q].x : 0.0;
-        rec[(3 * q + 1) * n + e] = ok ? sc * g[q].y : 0.0;
-        rec[(3 * q + 2) * n + e] = ok ? sc * g[q].z : 0.0;
+        r[3 * q] = ok ? sc * g[q].x : 0.0;
+        r[3 * q + 1] = ok ? sc * g[q].y : 0.0;
+        r[3 * q + 2] = ok ? sc * g[q].z : 0.0;
     }
-    if (P.s_look != 0.0) {
+    r[12] = ok ? -sc * (th - tb) : 0.0;
+    r[13] = 0.0;
+    if (look) {
         d3 ys[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) ys[q] = xs[q] + (P.s_look * P.h) * ld3(v, vid[q]);
-        double thf = 0.0;
+        double thf = 0.0, gf[16];
         const bool okf = hinge_eval(ys, thf, g);
-        rec[12 * n + e] = okf ? -sc * (thf - tb) : 0.0;
+        r[12] = okf ? -sc * (thf - tb) : 0.0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            rec[(13 + 3 * q) * n + e] = okf ? sc * g[q].x : 0.0;
-            rec[(14 + 3 * q) * n + e] = okf ? sc * g[q].y : 0.0;
-            rec[(15 + 3 * q) * n + e] = okf ? sc * g[q].z : 0.0;
+            gf[4 * q] = okf ? sc * g[q].x : 0.0;
+            gf[4 * q + 1] = okf ? sc * g[q].y : 0.0;
+            gf[4 * q + 2] = okf ? sc * g[q].z : 0.0;
+            gf[4 * q + 3] = 0.0;
         }
-    } else {
-        rec[12 * n + e] = ok ? -sc * (th - tb) : 0.0;
+        store_records(lds, gf, rec + 14, stride, ne);
     }
+    store_records(lds, r, rec, stride, ne);
 }
 
 __global__ void __launch_bounds__(256) k_contact_eval(int nc, const int *cverts, const double *cw, const double *cn,
@@ -533,11 +571,12 @@ struct AsmArgs {
     int nslices;
     // per row of the row group pass, from the pattern pass to the value pass:
     // its columns at cols_tmp[3 p0 + i ..] (p0 = inc_ptr[i]; at most 3 n + 1),
-    // its (incidence, corner) pairs sorted by column slot then incidence at
-    // pairs_tmp[3 p0 ..] (key slot << 7 | m << 2 | l), and their number
+    // its (incidence m, corner l) pairs sorted by column slot then incidence
+    // at pairs_tmp[4 p0 ..] (byte m << 2 | l; at most 96), the first pair of
+    // each column slot at starts_tmp[3 p0 + i ..], and the pairs' number
     int *cols_tmp;
-    int *pairs_tmp;
-    int *row_npairs;
+    uint8_t *pairs_tmp, *starts_tmp, *row_npairs;
+    unsigned long long *f16_max;   // per slice: bits of the largest |a| (FP16 blocks; else nullptr)
     void *jval;
     double *jval_hi;   // FP64 copy (nullptr when the solver copy is FP64)
     double *b, *diag;
@@ -588,21 +627,20 @@ __device__ __forceinline__ int4 element_vertices(const AsmArgs &A, unsigned code
 // opposite wing of a hinge in which the row's vertex is a wing (the edge's
 // endpoints already share a triangle with both wings), the other three
 // vertices of a contact, appended to the group's list.
-template <int NI>
-__device__ __forceinline__ void push_candidates(RowGroupLDS<NI> &L, unsigned code, int4 ev) {
+__device__ __forceinline__ void push_candidates(int *cand, int *ncand, unsigned code, int4 ev) {
     const int k = inc_corner(code);
     const unsigned type = inc_type(code);
     if (type == INC_TRI) {
-        const int pos = atomicAdd(&L.ncand, 2);
-        L.cand[pos] = k == 0 ? ev.y : (k == 1 ? ev.z : ev.x);
-        L.cand[pos + 1] = k == 0 ? ev.z : (k == 1 ? ev.x : ev.y);
+        const int pos = atomicAdd(ncand, 2);
+        cand[pos] = k == 0 ? ev.y : (k == 1 ? ev.z : ev.x);
+        cand[pos + 1] = k == 0 ? ev.z : (k == 1 ? ev.x : ev.y);
     } else if (type == INC_HINGE) {
-        if (k >= 2) L.cand[atomicAdd(&L.ncand, 1)] = k == 2 ? ev.w : ev.z;
+        if (k >= 2) cand[atomicAdd(ncand, 1)] = k == 2 ? ev.w : ev.z;
     } else {
-        const int pos = atomicAdd(&L.ncand, 3);
-        L.cand[pos] = k == 0 ? ev.y : ev.x;
-        L.cand[pos + 1] = k <= 1 ? ev.z : ev.y;
-        L.cand[pos + 2] = k <= 2 ? ev.w : ev.z;
+        const int pos = atomicAdd(ncand, 3);
+        cand[pos] = k == 0 ? ev.y : ev.x;
+        cand[pos + 1] = k <= 1 ? ev.z : ev.y;
+        cand[pos + 2] = k <= 2 ? ev.w : ev.z;
     }
 }
 
@@ -637,7 +675,7 @@ __device__ __forceinline__ int row_columns_g(RowGroupLDS<NI> &L, const AsmArgs &
             const unsigned code = L.code[m];
             const int4 ev = element_vertices(A, code);
             L.ev[m] = ev;
-            push_candidates(L, code, ev);
+            push_candidates(L.cand, &L.ncand, code, ev);
         }
     }
     __syncthreads();
@@ -727,64 +765,142 @@ __device__ __forceinline__ void row_record(const AsmArgs &A, int i, int len, boo
     }
 }
 
-// For the value pass of a row group row: its columns, and every (incidence
-// m, corner l != k) pair grouped by the column slot of corner l's vertex,
-// slots ascending and each slot's pairs in incidence order.  Lane t takes
-// the slots s = t, t + 16, ...: it counts the pairs of each slot by scanning
-// the row's incidences, the counts give each slot's first position, and a
-// second scan writes the pairs.  Called by every lane.
-__device__ __forceinline__ int slot_pairs(const RowGroupLDS<RG_NI> &L, int n, int c, int q0, int *out, int s) {
-    int cnt = 0;
-#pragma unroll 4
-    for (int m = 0; m < n; ++m) {
-        const int4 ev = L.ev[m];
-        const int k = inc_corner(L.code[m]);
-        const int l = ev.x == c ? 0 : (ev.y == c ? 1 : (ev.z == c ? 2 : (ev.w == c ? 3 : -1)));
-        if (l >= 0 && l != k) {
-            if (out) out[q0 + cnt] = (s << 7) | (m << 2) | l;
-            ++cnt;
-        }
-    }
-    return cnt;
+// The pattern pass of four rows per wavefront, 16 lanes (one DPP row) each.
+// What bounds it is the instructions of its loops over LDS: the columns come
+// from one rank sort of the candidates and a scan of the first ones, and the
+// pairs from one scan of the element vertices per column (bit masks over the
+// incidences): 395 us for 828k rows, against 695 us with three quadratic loops
+// over the candidates and two scans per column.
+struct RowPatternLDS {
+    unsigned code[RG_NI];
+    int4 ev[RG_NI];               // element vertices (w = -1 for triangles)
+    int4 cand[(3 * RG_NI + 4) / 4];   // column candidates and the row itself, padded with INT_MAX
+    int sorted[3 * RG_NI + 1];    // the candidates ascending (the pattern pass also stages the unsorted codes here)
+    int cols[3 * RG_NI + 1];      // distinct columns ascending, diagonal included
+    int ncand;
+};
+
+// Inclusive scan over the 16 lanes of a DPP row.
+__device__ __forceinline__ int row_incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    return v;
 }
 
-__device__ __forceinline__ void row_pairs_g(RowGroupLDS<RG_NI> &L, const AsmArgs &A, int i, int len, bool act,
-                                            int t) {
-    int p0 = 0, n = 0;
-    if (act) {
-        p0 = A.inc_ptr[i];
-        n = A.inc_ptr[i + 1] - p0;
-        for (int s = t; s < len; s += RG) {
-            const int c = L.cols[s];
-            A.cols_tmp[3 * p0 + i + s] = c;
-            L.cand[s] = c == i ? 0 : slot_pairs(L, n, c, 0, nullptr, s);   // pairs per slot
-        }
-    }
-    __syncthreads();
-    if (act) {
-        for (int s = t; s < len; s += RG) {
-            int q0 = 0;
-            for (int r = 0; r < s; ++r) q0 += L.cand[r];
-            const int c = L.cols[s];
-            if (c != i) slot_pairs(L, n, c, q0, A.pairs_tmp + 3 * (int64_t)p0, s);
-        }
-        if (t == 0) {
-            int np = 0;
-            for (int r = 0; r < len; ++r) np += L.cand[r];
-            A.row_npairs[i] = np;
-        }
-    }
+// Sum over the 16 lanes of a DPP row, in every lane: rotations by 8, 4, 2, 1
+// add the same pairs as the butterfly over lane numbers (after the rotation
+// by r the values repeat every r lanes).
+__device__ __forceinline__ double row_sum(double v) {
+    v += row_rotated<0x128>(v);
+    v += row_rotated<0x124>(v);
+    v += row_rotated<0x122>(v);
+    v += row_rotated<0x121>(v);
+    return v;
+}
+__device__ __forceinline__ double row_max(double v) {
+    v = fmax(v, row_rotated<0x128>(v));
+    v = fmax(v, row_rotated<0x124>(v));
+    v = fmax(v, row_rotated<0x122>(v));
+    v = fmax(v, row_rotated<0x121>(v));
+    return v;
 }
 
 __global__ void __launch_bounds__(64) k_row_pattern(AsmArgs A) {
-    __shared__ RowGroupLDS<RG_NI> Ls[RG_ROWS];
+    __shared__ RowPatternLDS Ls[RG_ROWS];
     const int g = threadIdx.x / RG, t = threadIdx.x % RG;
     const int i = xcd_remap(blockIdx.x, gridDim.x) * RG_ROWS + g;
-    const bool act = i < A.nv;
-    bool keep = false;
-    const int len = row_pattern_g<RG, RG_NI>(Ls[g], A, i, act, t, keep);
-    if (act && t == 0) row_record(A, i, len, keep, false);
-    row_pairs_g(Ls[g], A, i, len, act && len > 0 && len <= MAX_COLS, t);
+    RowPatternLDS &L = Ls[g];
+    int *const cand = (int *)L.cand;
+    int p0 = 0, n = 0;
+    if (i < A.nv) {
+        p0 = A.inc_ptr[i];
+        n = A.inc_ptr[i + 1] - p0;
+    }
+    const bool act = i < A.nv && n <= RG_NI;
+    if (!act) n = 0;
+    // incidence codes ascending (distinct: rank sort), written back in place
+    for (int m = t; m < n; m += RG) L.sorted[m] = A.inc[p0 + m];
+    if (t == 0) L.ncand = 0;
+    __syncthreads();
+    for (int m = t; m < n; m += RG) {
+        const unsigned key = (unsigned)L.sorted[m];
+        int r = 0;
+#pragma unroll 4
+        for (int q = 0; q < n; ++q) r += (unsigned)L.sorted[q] < key;
+        L.code[r] = key;
+        A.inc[p0 + r] = (int)key;
+        const int4 ev = element_vertices(A, key);
+        L.ev[r] = ev;
+        push_candidates(cand, &L.ncand, key, ev);
+    }
+    __syncthreads();
+    // candidates (with the row itself) by rank, ties by position
+    const int nc = act ? L.ncand + 1 : 0;
+    if (act && t < 4) cand[nc - 1 + t] = t == 0 ? i : 0x7fffffff;
+    __syncthreads();
+    for (int p = t; p < nc; p += RG) {
+        const int c = cand[p];
+        int r = 0;
+        for (int q = 0; q < nc; q += 4) {
+            const int4 u = L.cand[q / 4];
+            r += u.x < c + (q < p ? 1 : 0);
+            r += u.y < c + (q + 1 < p ? 1 : 0);
+            r += u.z < c + (q + 2 < p ? 1 : 0);
+            r += u.w < c + (q + 3 < p ? 1 : 0);
+        }
+        L.sorted[r] = c;
+    }
+    __syncthreads();
+    // distinct ones: the columns
+    int len = 0;
+    for (int q = 0; q < nc; q += RG) {
+        const int r = q + t, c = r < nc ? L.sorted[r] : 0;
+        const int first = r < nc && (r == 0 || L.sorted[r - 1] != c) ? 1 : 0;
+        const int at = len + row_incl_scan(first);
+        if (first) L.cols[at - 1] = c;
+        len = __shfl(at, RG - 1, RG);
+    }
+    __syncthreads();
+    // does the row keep its diagonal block: free, with a pinned column
+    int anyp = 0;
+    const bool fits = act && len <= MAX_COLS;
+    for (int q = t; q < (act ? len : 0); q += RG) {
+        const int c = L.cols[q];
+        anyp |= (c != i && A.pinned[c]) ? 1 : 0;
+    }
+    anyp = group_sum_int<RG>(anyp);
+    if (i < A.nv && t == 0) row_record(A, i, act ? len : 0, act && anyp > 0 && !A.pinned[i], false);
+    // columns and pairs for the value pass; lane t takes the slots t, t + 16, ...
+    int np = 0;
+    for (int s0 = 0; s0 < (fits ? len : 0); s0 += RG) {
+        const int sl = s0 + t, c = sl < len ? L.cols[sl] : i;
+        unsigned mask = 0u, l0 = 0u, l1 = 0u;   // incidences that meet c, and the bits of c's corner
+        if (c != i) {
+#pragma unroll 2
+            for (int m = 0; m < n; ++m) {
+                const int4 ev = L.ev[m];
+                const bool y = ev.y == c, z = ev.z == c, w = ev.w == c;
+                mask |= (unsigned)(y || z || w || ev.x == c) << m;
+                l0 |= (unsigned)(y || w) << m;
+                l1 |= (unsigned)(z || w) << m;
+            }
+        }
+        const int cnt = __popc(mask), at = np + row_incl_scan(cnt);
+        if (sl < len) {
+            A.cols_tmp[3 * p0 + i + sl] = c;
+            A.starts_tmp[3 * (int64_t)p0 + i + sl] = (uint8_t)(at - cnt);
+            uint8_t *out = A.pairs_tmp + 4 * (int64_t)p0 + (at - cnt);
+            while (mask) {
+                const int m = __ffs((int)mask) - 1;
+                mask &= mask - 1;
+                *out++ = (uint8_t)(m << 2 | (l1 >> m & 1u) << 1 | (l0 >> m & 1u));
+            }
+        }
+        np = __shfl(at, RG - 1, RG);
+    }
+    if (fits && t == 0) A.row_npairs[i] = (uint8_t)np;
 }
 
 // Wide rows: one workgroup per row, a grid-stride loop over the list the
@@ -810,7 +926,7 @@ __global__ void __launch_bounds__(64) k_row_pattern_wide(AsmArgs A) {
 // slice_psize, the padded block count of each slice).
 __global__ void __launch_bounds__(64) k_slice_layout(int nslices, const int *slice_row0, const int *rowlen,
                                                      int *lane_row, int *row_lane, uint8_t *slot_cnt,
-                                                     int *slot_off, int *slice_psize) {
+                                                     int *slot_off, int *slice_psize, unsigned long long *f16_max) {
     const int s = blockIdx.x;
     if (s >= nslices) return;
     const int t = threadIdx.x;
@@ -832,6 +948,7 @@ __global__ void __launch_bounds__(64) k_slice_layout(int nslices, const int *sli
     slot_off[s * WAVE + t] = wave_excl_scan(slot_width(c));
     const int padded = wave_sum_int(slot_width(c));
     if (t == 0) slice_psize[s] = padded;
+    if (t == 0 && f16_max) f16_max[s] = 0ull;
 }
 
 // A row that overflowed the per-row limits has length 1 (set by the pattern
@@ -860,23 +977,19 @@ __device__ void write_overflow_row(const AsmArgs &A, int i) {
     bi[0] = im; bi[1] = 0.0f; bi[2] = 0.0f; bi[3] = im; bi[4] = 0.0f; bi[5] = im;
 }
 
-// Inverse of the symmetric 3x3 block [[a, b, c], [b, d, e], [c, e, f]] by its
-// adjugate, written as (xx, xy, xz, yy, yz, zz).  A block that is not
-// positive definite (impossible for M + c K with K PSD, but guarded) falls
+// Entry t of (xx, xy, xz, yy, yz, zz) of the inverse of the symmetric 3x3
+// block [[a, b, c], [b, d, e], [c, e, f]], by its adjugate.  A block that is
+// not positive definite (impossible for M + c K with K PSD, but guarded) falls
 // back to the inverse of its diagonal.
-__device__ __forceinline__ void store_block_inverse(float *out, double a, double b, double c, double d, double e,
-                                                    double f) {
+__device__ __forceinline__ float block_inverse(double a, double b, double c, double d, double e, double f, int t) {
     const double c00 = d * f - e * e, c01 = c * e - b * f, c02 = b * e - c * d;
     const double c11 = a * f - c * c, c12 = b * c - a * e, c22 = a * d - b * b;
     const double det = a * c00 + b * c01 + c * c02;
     if (det > 0.0 && a > 0.0 && c22 > 0.0 && isfinite(det)) {   // leading minors positive
         const double id = 1.0 / det;
-        out[0] = (float)(c00 * id); out[1] = (float)(c01 * id); out[2] = (float)(c02 * id);
-        out[3] = (float)(c11 * id); out[4] = (float)(c12 * id); out[5] = (float)(c22 * id);
-    } else {
-        out[0] = (float)(1.0 / a); out[1] = 0.0f; out[2] = 0.0f;
-        out[3] = (float)(1.0 / d); out[4] = 0.0f; out[5] = (float)(1.0 / f);
+        return (float)((t == 0 ? c00 : t == 1 ? c01 : t == 2 ? c02 : t == 3 ? c11 : t == 4 ? c12 : c22) * id);
     }
+    return t == 0 || t == 3 || t == 5 ? (float)(1.0 / (t == 0 ? a : t == 3 ? d : f)) : 0.0f;
 }
 
 // ---------------------------------------------------------------- values
@@ -885,6 +998,10 @@ __device__ __forceinline__ void store_block_inverse(float *out, double a, double
 //   triangle  A0 [mu (b_k.b_l) F F^T + mu u_l u_k^T + lam u_k u_l^T + (b_k^T S+ b_l) I],  u = F b
 //   hinge     G_k G_l^T
 //   contact   kc_act c_k c_l n n^T
+__device__ __forceinline__ const double *hinge_rec(const AsmArgs &A, int e) {
+    return A.hrec + (int64_t)e * (A.prm.s_look != 0.0 ? HREC_LOOK : HREC);
+}
+
 __device__ __forceinline__ void add_stiffness(const AsmArgs &A, unsigned code, int l, double acc[9]) {
     const int e = inc_elem(code), k = inc_corner(code);
     const unsigned type = inc_type(code);
@@ -892,11 +1009,10 @@ __device__ __forceinline__ void add_stiffness(const AsmArgs &A, unsigned code, i
         // the record holds K_kl for k < l; K_lk = K_kl^T
         const int lo = k < l ? k : l, hi = k < l ? l : k;
         const int p = lo + hi - 1;   // (0,1) -> 0, (0,2) -> 1, (1,2) -> 2
-        const int n = A.nt;          // 36 n < 2^31 (checked at pc_create)
-        const double *R = A.trec + 9 * p * n + e;
+        const double *R = A.trec + (int64_t)e * TREC + 10 * p;
         double K[9];
 #pragma unroll
-        for (int q = 0; q < 9; ++q) K[q] = R[q * n];
+        for (int q = 0; q < 9; ++q) K[q] = R[q];
         if (k < l) {
 #pragma unroll
             for (int q = 0; q < 9; ++q) acc[q] += K[q];
@@ -907,14 +1023,11 @@ __device__ __forceinline__ void add_stiffness(const AsmArgs &A, unsigned code, i
                 for (int b = 0; b < 3; ++b) acc[3 * a + b] += K[3 * b + a];
         }
     } else if (type == INC_HINGE) {
-        const int n = A.nh;          // 25 n < 2^31 (checked at pc_create)
-        const double *Rk = A.hrec + 3 * k * n + e, *Rl = A.hrec + 3 * l * n + e;
-        const double gk[3] = {Rk[0], Rk[n], Rk[2 * n]};
-        const double gl[3] = {Rl[0], Rl[n], Rl[2 * n]};
+        const double *gk = hinge_rec(A, e) + 3 * k, *gl = hinge_rec(A, e) + 3 * l;
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) acc[3 * a + b] += gk[a] * gl[b];
+            for (int b = 0; b < 3; ++b) acc[3 * a + b] = __builtin_fma(gk[a], gl[b], acc[3 * a + b]);
     } else {
         // written so that the (l, k) block is the exact transpose of (k, l)
         const double nr[3] = {A.cn[3 * e], A.cn[3 * e + 1], A.cn[3 * e + 2]};
@@ -932,21 +1045,28 @@ __device__ __forceinline__ void add_force(const AsmArgs &A, unsigned code, doubl
     const unsigned type = inc_type(code);
     const bool look = A.prm.s_look != 0.0;
     if (type == INC_TRI) {
-        const int n = A.nt;
-        const double *R = A.trec + (27 + 3 * k) * n + e;
+        const double *R = A.trec + (int64_t)e * TREC + 30 + 4 * k;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) f[a] += R[a * n];
+        for (int a = 0; a < 3; ++a) f[a] += R[a];
     } else if (type == INC_HINGE) {
-        const int n = A.nh;
-        const double phi = A.hrec[12 * n + e];
-        const double *R = A.hrec + (look ? 13 + 3 * k : 3 * k) * n + e;
+        const double *H = hinge_rec(A, e), *R = H + (look ? 14 + 4 * k : 3 * k);
+        const double phi = H[12];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) f[a] += phi * R[a * n];
+        for (int a = 0; a < 3; ++a) f[a] = __builtin_fma(phi, R[a], f[a]);
     } else {
         const double m = A.crec[(int64_t)A.nc + e] * A.cw[4 * e + k];
 #pragma unroll
         for (int a = 0; a < 3; ++a) f[a] += m * A.cn[3 * e + a];
     }
+}
+
+// Bits of the largest magnitude of a block (NaN left out); magnitudes order
+// like their bits.
+__device__ __forceinline__ unsigned long long block_max_bits(const double blk[9]) {
+    double m = 0.0;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) m = fmax(m, fabs(blk[q]));
+    return __builtin_bit_cast(unsigned long long, m);
 }
 
 // Block s of row i (column col) into the block-CSR column list and the
@@ -964,6 +1084,7 @@ __device__ __forceinline__ void store_row_block(const AsmArgs &A, int i, int s, 
     A.colidx[A.rowptr[i] + s] = col;
     s = solver_slot(A, i, s, dpos);
     if (s < 0) return;
+    if (A.f16_max) atomicMax(&A.f16_max[A.row_slice[i]], block_max_bits(blk));
     const int si = A.row_slice[i];
     const int w = slot_width((int)A.slot_cnt[si * WAVE + s]);
     const int64_t seg = (int64_t)A.slice_vbase[si] + A.slot_off[si * WAVE + s];
@@ -976,41 +1097,34 @@ __device__ __forceinline__ void store_row_block(const AsmArgs &A, int i, int s, 
     if (A.jval_hi) BlockIO<double>::store(A.jval_hi + 9 * seg, w, lane, blk);
 }
 
-// The row's own outputs: the diagonal slot's block D_i = -c sum_{j pinned}
-// K_ij (0 for a pinned row), b_i = h (f_i + m_i g - kv K v), diag(A)_i,
-// 1 / diag(A)_i and the inverse of the diagonal block A_ii = m_i I - c sum_j
-// K_ij (every element's block rows sum to zero).  red: K v, the diagonal of
-// sum_{j != i} K_ij, its symmetrised off-diagonal entries; pin: sum_{j
-// pinned} K_ij; f: the element forces.
-template <typename TB>
-__device__ __forceinline__ void write_row_diagonal(const AsmArgs &A, int i, int dslot, bool rowpin,
-                                                   const double red[9], const double pin[9], const double f[3]) {
+// The row's totals, component t of each by lane t of the row (t < 6): b_i =
+// h (f_i + m_i g - kv K v), diag(A)_i, 1 / diag(A)_i and the inverse of the
+// diagonal block A_ii = m_i I - c sum_j K_ij (every element's block rows sum to
+// zero).  red: K v, the diagonal of sum_{j != i} K_ij, its symmetrised
+// off-diagonal entries; f: the element forces.
+__device__ __forceinline__ void write_row_totals(const AsmArgs &A, int i, bool rowpin, double mi, const double red[9],
+                                                 const double f[3], int t) {
     const DevParams &P = A.prm;
-    const double mi = A.mass[i];
-    double blk[9];
-#pragma unroll
-    for (int q = 0; q < 9; ++q) blk[q] = rowpin ? 0.0 : -P.c * pin[q];
-    // force: gravity plus the element forces
-    const double f0 = mi * P.g[0] + f[0], f1 = mi * P.g[1] + f[1], f2 = mi * P.g[2] + f[2];
-    double bi0 = P.h * (f0 - P.kv_coef * red[0]);
-    double bi1 = P.h * (f1 - P.kv_coef * red[1]);
-    double bi2 = P.h * (f2 - P.kv_coef * red[2]);
-    double d0 = mi - P.c * red[3], d1 = mi - P.c * red[4], d2 = mi - P.c * red[5];
-    if (rowpin) {
-        bi0 = bi1 = bi2 = 0.0;
-        d0 = d1 = d2 = mi;
+    if (t >= 6) return;
+    const double d0 = rowpin ? mi : mi - P.c * red[3], d1 = rowpin ? mi : mi - P.c * red[4],
+                 d2 = rowpin ? mi : mi - P.c * red[5];
+    if (t < 3) {
+        // force: gravity plus the element forces
+        const double gt = t == 0 ? P.g[0] : (t == 1 ? P.g[1] : P.g[2]);
+        const double ft = mi * gt + (t == 0 ? f[0] : (t == 1 ? f[1] : f[2]));
+        const double kv = t == 0 ? red[0] : (t == 1 ? red[1] : red[2]);
+        const double dt = t == 0 ? d0 : (t == 1 ? d1 : d2);
+        double bi = P.h * (ft - P.kv_coef * kv);
+        if (rowpin) bi = 0.0;
+        if (!isfinite(bi)) atomicOr(A.status, ST_NONFINITE);
+        A.b[3 * i + t] = bi;
+        A.diag[3 * i + t] = dt;
+        A.dinv[3 * i + t] = (float)(1.0 / dt);
     }
-    if (!isfinite(bi0) || !isfinite(bi1) || !isfinite(bi2)) atomicOr(A.status, ST_NONFINITE);
-    A.b[3 * i] = bi0; A.b[3 * i + 1] = bi1; A.b[3 * i + 2] = bi2;
-    A.diag[3 * i] = d0; A.diag[3 * i + 1] = d1; A.diag[3 * i + 2] = d2;
-    A.dinv[3 * i] = (float)(1.0 / d0);
-    A.dinv[3 * i + 1] = (float)(1.0 / d1);
-    A.dinv[3 * i + 2] = (float)(1.0 / d2);
     const double o01 = rowpin ? 0.0 : -P.c * red[6];
     const double o02 = rowpin ? 0.0 : -P.c * red[7];
     const double o12 = rowpin ? 0.0 : -P.c * red[8];
-    store_block_inverse(A.binv + 6 * (int64_t)i, d0, o01, o02, d1, o12, d2);
-    store_row_block<TB>(A, i, dslot, dslot, i, blk);
+    A.binv[6 * (int64_t)i + t] = block_inverse(d0, o01, o02, d1, o12, d2, t);
 }
 
 // Values of one row.  Lane t of the group owns the column slots s = t, t + G,
@@ -1084,13 +1198,13 @@ __device__ __forceinline__ void row_values_g(RowGroupLDS<NI> &L, const AsmArgs &
     npin = group_sum_int<G>(npin);
 #pragma unroll
     for (int a = 0; a < 3; ++a) f[a] = group_sum<G>(f[a]);
-    if (dslot < 0) return;
+    if (!act) return;
     // D_i = -c sum_{j pinned} K_ij for a free row, 0 for a pinned row: the
     // blocks of pinned columns, summed in incidence order (rows next to a pin only)
     double pin[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) pin[q] = 0.0;
-    if (!rowpin && npin > 0)
+    if (dslot >= 0 && !rowpin && npin > 0)
         for (int m = 0; m < n; ++m) {
             const unsigned code = L.code[m];
             const int4 ev = L.ev[m];
@@ -1101,112 +1215,323 @@ __device__ __forceinline__ void row_values_g(RowGroupLDS<NI> &L, const AsmArgs &
                 if (l != k && A.pinned[vl]) add_stiffness(A, code, l, pin);
             }
         }
-    write_row_diagonal<TB>(A, i, dslot, rowpin, red, pin, f);
+    if (dslot >= 0) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) pin[q] = rowpin ? 0.0 : -P.c * pin[q];
+        store_row_block<TB>(A, i, dslot, dslot, i, pin);
+    }
+    write_row_totals(A, i, rowpin, A.mass[i], red, f, t);
 }
 
-// Value pass of the row group rows, four rows per 64-lane workgroup, 16
+// Value pass of the row group rows: one wavefront per group of four rows, 16
 // lanes per row (the pattern pass has left each row's columns and its
-// (incidence, corner) pairs sorted by column slot).  Lane t of a row owns
-// the column slots s = t, t + 16, ...; for each it sums, in incidence order,
-// the stiffness blocks of the pairs of that slot (a contiguous range of the
-// sorted pairs) from the element records: a deterministic segmented reduce
-// with no floating-point atomics.  Row totals and the forces are summed per
-// lane, then over the 16 lanes in a fixed butterfly order; the lane holding
-// the diagonal slot writes the row's own outputs.
+// (incidence, corner) pairs by column slot).  Lane t of a row owns the column
+// slots t, t + 16, ...; for each it sums, in incidence order, the stiffness
+// blocks of the slot's pairs.  Row totals and the forces are summed per lane,
+// then over the row's 16 lanes in a fixed butterfly order; the lane holding
+// the diagonal slot writes the row's own outputs.  With FP16 blocks the
+// slices' largest magnitudes are taken here, from the registers.
+//
+// What bounds it is the latency of its three rounds of dependent loads (the
+// row's state, its lists, the records) at 11 wavefronts a compute unit, and
+// behind it the memory traffic (2 GB).  Reading the records pair by pair from
+// planes took 420 accesses to the L1 a row (1.35 ms for 828k rows; also 64 or
+// 16 rows side by side per load, with 2 to 4 pairs in flight, 1.55 to 1.65
+// ms); so the parts of the records that the group needs come once, 16 bytes a
+// lane, straight into LDS, all in flight together, and the pairs are read
+// from there: 1.02 ms, which replaces the 0.13 ms of a pass over the blocks
+// for their magnitudes too.  Workgroups that stay and fetch the next group's
+// lists ahead measured 1.5 to 1.85 ms: their waits include the stores.
+constexpr int REC_CHUNKS = 704;   // 16-byte chunks of records a group keeps in LDS; the incidences beyond are read directly
+constexpr int TRI_CHUNKS = 12;    // of a triangle: the two blocks and the force of the row's corner
 struct RowPairsLDS {
-    unsigned code[RG_NI];
-    int pair[3 * RG_NI];
-    int cols[MAX_COLS];
+    unsigned code[RG_NI + 1];
+    unsigned pair[3 * RG_NI / 4 + 1];
+    int cols[MAX_COLS + 1];
+    uint8_t start[MAX_COLS + 4];
+};
+struct RowRecordsLDS {
+    uint4 rec[REC_CHUNKS];
+    RowPairsLDS row[RG_ROWS];
 };
 
+// Where a row's incidence records lie: triangles from chunk c0, hinges from
+// chunk h0 (hc chunks each); nt triangles.
+struct RowChunks {
+    int c0, h0, nt, hc;
+    __device__ __forceinline__ int at(int m) const { return m < nt ? c0 + TRI_CHUNKS * m : h0 + hc * (m - nt); }
+    __device__ __forceinline__ bool in_lds(int m, unsigned type) const {
+        return type != INC_CONTACT && at(m) + (m < nt ? TRI_CHUNKS : hc) <= REC_CHUNKS;
+    }
+};
+
+// add_stiffness and add_force from LDS where the record is there.
+__device__ __forceinline__ void add_stiffness_lds(const RowRecordsLDS &L, const AsmArgs &A, const RowChunks &C,
+                                                  unsigned code, int m, int l, double acc[9]) {
+    const int k = inc_corner(code);
+    const unsigned type = inc_type(code);
+    if (!C.in_lds(m, type)) {
+        add_stiffness(A, code, l, acc);
+        return;
+    }
+    const double *R = (const double *)(L.rec + C.at(m));
+    if (type == INC_TRI) {
+        R += l == (k == 2 ? 1 : 2) ? 10 : 0;   // the corner's second block
+        double K[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) K[q] = R[q];
+        if (k < l) {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) acc[q] += K[q];
+        } else {
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) acc[3 * a + b] += K[3 * b + a];
+        }
+    } else {
+        const double *gk = R + 3 * k, *gl = R + 3 * l;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) acc[3 * a + b] = __builtin_fma(gk[a], gl[b], acc[3 * a + b]);
+    }
+}
+
+__device__ __forceinline__ void add_force_lds(const RowRecordsLDS &L, const AsmArgs &A, const RowChunks &C,
+                                              unsigned code, int m, double f[3]) {
+    const int k = inc_corner(code);
+    const unsigned type = inc_type(code);
+    if (!C.in_lds(m, type)) {
+        add_force(A, code, f);
+        return;
+    }
+    const double *R = (const double *)(L.rec + C.at(m));
+    if (type == INC_TRI) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) f[a] += R[20 + a];
+    } else {
+        const double phi = R[12], *G = A.prm.s_look != 0.0 ? R + 14 : R + 3 * k;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) f[a] = __builtin_fma(phi, G[a], f[a]);
+    }
+}
+
 template <typename TB>
-__global__ void __launch_bounds__(64) k_row_values(AsmArgs A) {
-    __shared__ RowPairsLDS Ls[RG_ROWS];
-    const int g = threadIdx.x / RG, t = threadIdx.x % RG;
+__global__ void __launch_bounds__(64, 3) k_row_values(AsmArgs A) {
+    __shared__ RowRecordsLDS L;
+    const int lane = threadIdx.x, g = lane / RG, t = lane % RG;
     const int i = xcd_remap(blockIdx.x, gridDim.x) * RG_ROWS + g;
-    const int st = i < A.nv ? (int)A.row_state[i] : -1;
-    if (st == ROW_OVERFLOW && t == 0) write_overflow_row<TB>(A, i);
-    const bool act = st == ROW_GROUP;
-    RowPairsLDS &L = Ls[g];
-    int p0 = 0, n = 0, np = 0, len = 0;
-    if (act) {
+    RowPairsLDS &W = L.row[g];
+    const DevParams &P = A.prm;
+    // the row's state and what its outputs need
+    int st = -1, p0 = 0, n = 0, len = 0, np = 0, rp = 0, pos = 0, si = 0;
+    bool rowpin = false, keep = false;
+    d3 vi = mk(0.0, 0.0, 0.0);
+    if (i < A.nv) {
+        st = (int)A.row_state[i];
         p0 = A.inc_ptr[i];
         n = A.inc_ptr[i + 1] - p0;
-        np = A.row_npairs[i];
         len = A.rowlen[i];
-        for (int m = t; m < n; m += RG) L.code[m] = (unsigned)A.inc[p0 + m];
-        for (int q = t; q < np; q += RG) L.pair[q] = A.pairs_tmp[3 * p0 + q];
-        for (int q = t; q < len; q += RG) L.cols[q] = A.cols_tmp[3 * p0 + i + q];
+        np = (int)A.row_npairs[i];
+        keep = A.rowlen_s[i] == len;
+        rp = A.rowptr[i];
+        pos = A.row_lane[i];
+        si = A.row_slice[i];
+        rowpin = A.pinned[i] != 0;
+        vi = ld3(A.v, i);
     }
+    if (st == ROW_OVERFLOW && t == 0) write_overflow_row<TB>(A, i);
+    if (st != ROW_GROUP) n = len = np = 0;
+    // its lists
+    const unsigned *pairs = (const unsigned *)A.pairs_tmp + p0;
+    const int l0 = 3 * p0 + i;   // the row's part of cols_tmp and starts_tmp
+    unsigned code[2] = {0u, 0u}, pair[2] = {0u, 0u};
+    int cols[4] = {0, 0, 0, 0}, first[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int m = t + RG * k;
+        if (m < n) code[k] = (unsigned)A.inc[p0 + m];
+        if (4 * m < np) pair[k] = pairs[m];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int q = t + RG * k;
+        if (q < len) {
+            cols[k] = A.cols_tmp[l0 + q];
+            first[k] = (int)A.starts_tmp[l0 + q];
+        }
+    }
+    const int vbase = A.slice_vbase[si], row0 = A.slice_row0[si];
+    int ntri = 0, nhin = 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int m = t + RG * k;
+        if (m < n) W.code[m] = code[k];
+        if (4 * m < np) W.pair[m] = pair[k];
+        const unsigned sh = RG * g;
+        ntri += __popc((unsigned)(__ballot(m < n && inc_type(code[k]) == INC_TRI) >> sh) & 0xffffu);
+        nhin += __popc((unsigned)(__ballot(m < n && inc_type(code[k]) == INC_HINGE) >> sh) & 0xffffu);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int q = t + RG * k;
+        if (q < len) {
+            W.cols[q] = cols[k];
+            W.start[q] = (uint8_t)first[k];
+        }
+    }
+    if (t == 0) W.start[len] = (uint8_t)np;
+    // chunks of the group's records, row after row
+    const bool look = P.s_look != 0.0;
+    RowChunks C;
+    C.hc = look ? 9 : 7;
+    C.nt = ntri;
+    const int mine = TRI_CHUNKS * ntri + C.hc * nhin;
+    int end[RG_ROWS], tris[RG_ROWS], total = 0;
+#pragma unroll
+    for (int k = 0; k < RG_ROWS; ++k) {
+        if (k == g) C.c0 = total;
+        total += __builtin_amdgcn_readlane(mine, RG * k);
+        end[k] = total;
+        tris[k] = __builtin_amdgcn_readlane(ntri, RG * k);
+    }
+    C.h0 = C.c0 + TRI_CHUNKS * ntri;
     __syncthreads();
-    const DevParams &P = A.prm;
+    total = min(total, REC_CHUNKS);
+    for (int b = 0; b < total; b += WAVE) {
+        const int c = b + lane;
+        int row = 0, base = 0, rt = tris[0];
+#pragma unroll
+        for (int k = 1; k < RG_ROWS; ++k)
+            if (c >= end[k - 1]) {
+                row = k;
+                base = end[k - 1];
+                rt = tris[k];
+            }
+        const int x = c - base, hx = x - TRI_CHUNKS * rt;
+        if (c < total) {
+            const char *src;
+            if (hx < 0) {
+                const int m = x / TRI_CHUNKS, part = x % TRI_CHUNKS;
+                const unsigned cd = L.row[row].code[m];
+                const int k = inc_corner(cd);
+                const int ch = part < 5 ? (k == 2 ? 5 : 0) + part
+                                        : (part < 10 ? (k == 0 ? 5 : 10) + part - 5 : 15 + 2 * k + part - 10);
+                src = (const char *)(A.trec + (int64_t)inc_elem(cd) * TREC) + 16 * ch;
+            } else {
+                const int h = look ? hx / 9 : hx / 7, part = hx - h * C.hc;
+                const unsigned cd = L.row[row].code[rt + h];
+                const int ch = part < 7 ? part : 2 * inc_corner(cd) + part;
+                src = (const char *)(A.hrec + (int64_t)inc_elem(cd) * (look ? HREC_LOOK : HREC)) + 16 * ch;
+            }
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                             (__attribute__((address_space(3))) void *)(L.rec + b), 16, 0, 0);
+        }
+    }
+    // what the lane's next slot needs besides the records, in flight with them
+    int col = i, wd = 0, off = 0;
+    bool colpin = false;
+    d3 vc = vi;
+    auto slot_loads = [&](int s, int c) {
+        col = c;
+        if (s >= len || c == i) return;
+        // the diagonal, when left out, precedes the columns above it
+        const int ss = si * WAVE + (keep || c < i ? s : s - 1);
+        wd = slot_width((int)A.slot_cnt[ss]);
+        off = A.slot_off[ss];
+        colpin = A.pinned[c] != 0;
+        vc = ld3(A.v, c);
+    };
+    slot_loads(t, cols[0]);
+    const double mass = i < A.nv ? A.mass[i] : 0.0;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     double red[9];   // K v (3), diagonal of sum_j K_ij (3), its symmetrised off-diagonal entries (3)
 #pragma unroll
     for (int q = 0; q < 9; ++q) red[q] = 0.0;
-    double f[3] = {0.0, 0.0, 0.0};
+    double f[3] = {0.0, 0.0, 0.0}, big = 0.0;
     int dslot = -1, npin = 0;
-    bool rowpin = false;
-    if (act) {
-        rowpin = A.pinned[i] != 0;
-        const d3 vi = ld3(A.v, i);
-        int dpos = 0;
-        for (int q = 0; q < len; ++q) dpos += L.cols[q] < i ? 1 : 0;
-        for (int s = t; s < len; s += RG) {
-            const int col = L.cols[s];
-            if (col == i) {
-                dslot = s;
-                continue;
-            }
-            // first pair of slot s (pairs are sorted by slot)
-            int lo = 0, hi = np;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if ((L.pair[mid] >> 7) < s) lo = mid + 1; else hi = mid;
-            }
-            double acc[9];
-#pragma unroll
-            for (int q = 0; q < 9; ++q) acc[q] = 0.0;
-            for (int q = lo; q < np; ++q) {
-                const int key = L.pair[q];
-                if ((key >> 7) != s) break;
-                add_stiffness(A, L.code[(key >> 2) & 31], key & 3, acc);
-            }
-            const bool colpin = A.pinned[col] != 0;
-            npin += colpin ? 1 : 0;
-            const d3 dvv = ld3(A.v, col) - vi;
-            red[0] += acc[0] * dvv.x + acc[1] * dvv.y + acc[2] * dvv.z;
-            red[1] += acc[3] * dvv.x + acc[4] * dvv.y + acc[5] * dvv.z;
-            red[2] += acc[6] * dvv.x + acc[7] * dvv.y + acc[8] * dvv.z;
-            red[3] += acc[0];
-            red[4] += acc[4];
-            red[5] += acc[8];
-            red[6] += 0.5 * (acc[1] + acc[3]);
-            red[7] += 0.5 * (acc[2] + acc[6]);
-            red[8] += 0.5 * (acc[5] + acc[7]);
-            double blk[9];
-#pragma unroll
-            for (int q = 0; q < 9; ++q) blk[q] = (rowpin || colpin) ? 0.0 : P.c * acc[q];
-            store_row_block<TB>(A, i, s, dpos, col, blk);
+    const uint8_t *const pr = (const uint8_t *)W.pair;
+    for (int s = t; s < len; s += RG) {
+        if (s > t) slot_loads(s, W.cols[s]);
+        if (col == i) {
+            dslot = s;
+            continue;
         }
-        for (int m = t; m < n; m += RG) add_force(A, L.code[m], f);
+        double acc[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) acc[q] = 0.0;
+        const int qe = W.start[s + 1];
+        for (int q = W.start[s]; q < qe; ++q) {
+            const int key = pr[q], m = key >> 2;
+            add_stiffness_lds(L, A, C, W.code[m], m, key & 3, acc);
+        }
+        npin += colpin ? 1 : 0;
+        const d3 dvv = vc - vi;
+        red[0] += acc[0] * dvv.x + acc[1] * dvv.y + acc[2] * dvv.z;
+        red[1] += acc[3] * dvv.x + acc[4] * dvv.y + acc[5] * dvv.z;
+        red[2] += acc[6] * dvv.x + acc[7] * dvv.y + acc[8] * dvv.z;
+        red[3] += acc[0];
+        red[4] += acc[4];
+        red[5] += acc[8];
+        red[6] += 0.5 * (acc[1] + acc[3]);
+        red[7] += 0.5 * (acc[2] + acc[6]);
+        red[8] += 0.5 * (acc[5] + acc[7]);
+        double blk[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) blk[q] = (rowpin || colpin) ? 0.0 : P.c * acc[q];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) big = fmax(big, fabs(blk[q]));
+        const int64_t seg = (int64_t)vbase + off;
+        A.colidx[rp + s] = col;
+        A.jcol[seg + pos] = col;
+        A.jdel[seg + pos] = (int16_t)(col - row0);
+        BlockIO<TB>::store((TB *)A.jval + 9 * seg, wd, pos, blk);
+        if (A.jval_hi) BlockIO<double>::store(A.jval_hi + 9 * seg, wd, pos, blk);
     }
+    for (int m = t; m < n; m += RG) add_force_lds(L, A, C, W.code[m], m, f);
+    // every lane of the row gets the totals
 #pragma unroll
-    for (int q = 0; q < 9; ++q) red[q] = group_sum<RG>(red[q]);
+    for (int q = 0; q < 9; ++q) red[q] = row_sum(red[q]);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) f[a] = group_sum<RG>(f[a]);
-    npin = group_sum_int<RG>(npin);
-    if (dslot < 0) return;
-    // pinned-column sums for D_i, pair by pair in (slot, incidence) order
-    // (rows next to a pin only)
-    double pin[9];
-#pragma unroll
-    for (int q = 0; q < 9; ++q) pin[q] = 0.0;
-    if (!rowpin && npin > 0)
-        for (int q = 0; q < np; ++q) {
-            const int key = L.pair[q];
-            if (A.pinned[L.cols[key >> 7]]) add_stiffness(A, L.code[(key >> 2) & 31], key & 3, pin);
+    for (int a = 0; a < 3; ++a) f[a] = row_sum(f[a]);
+    const unsigned long long pins = __ballot(npin > 0);
+    const bool pinned_near = (unsigned)(pins >> (RG * g) & 0xffffu) != 0u;
+    const unsigned long long dia = __ballot(dslot >= 0);
+    if (A.f16_max) {
+        // one for the group when its rows share a slice
+        big = row_max(big);
+        const int s0 = __builtin_amdgcn_readfirstlane(si);
+        const bool one = __all(n == 0 || si == s0);
+        if (one) {
+            big = fmax(big, __shfl_xor(big, RG, WAVE));
+            big = fmax(big, __shfl_xor(big, 2 * RG, WAVE));
         }
-    write_row_diagonal<TB>(A, i, dslot, rowpin, red, pin, f);
+        if (one ? lane == 0 : t == 0 && n > 0)
+            atomicMax(&A.f16_max[si], __builtin_bit_cast(unsigned long long, big));
+    }
+    if (((unsigned)(dia >> (RG * g)) & 0xffffu) == 0u) return;   // not a row of this pass
+    // the row's own outputs, component t of each by lane t
+    double own[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) own[q] = 0.0;
+    if (dslot >= 0) {
+        // D_i: pinned-column sums, pair by pair in (slot, incidence) order
+        // (rows next to a pin only)
+        if (!rowpin && pinned_near)
+            for (int s = 0; s < len; ++s) {
+                if (!A.pinned[W.cols[s]]) continue;
+                for (int q = W.start[s]; q < W.start[s + 1]; ++q) {
+                    const int m = pr[q] >> 2;
+                    add_stiffness_lds(L, A, C, W.code[m], m, pr[q] & 3, own);
+                }
+            }
+#pragma unroll
+        for (int q = 0; q < 9; ++q) own[q] = rowpin ? 0.0 : -P.c * own[q];
+        store_row_block<TB>(A, i, dslot, dslot, i, own);
+    }
+    write_row_totals(A, i, rowpin, mass, red, f, t);
 }
 
 template <typename TB>
@@ -1285,35 +1610,12 @@ __global__ void __launch_bounds__(64) k_export(int nv, const int *rowptr, const 
 }
 
 // ---------------------------------------------------------------- FP16 blocks
-// With FP16 storage the value pass writes the FP64 copy only.  The largest
-// magnitude over every stored block then fixes a power-of-two scale S with
-// max |S a| in [2^13, 2^14) (FP16's largest finite value is 65504, its
-// smallest normal 2^-14), and the FP16 copy holds S a rounded to nearest.
-// One wavefront per slice walks the slice's slots; lanes past a slot's row
-// count hold padding and are skipped.
-__global__ void __launch_bounds__(64) k_f16_absmax(int nslices, const int *slice_vbase, const uint8_t *slot_cnt,
-                                                   const int *slot_off, const double *hi, double *part) {
-    const int si = blockIdx.x;
-    if (si >= nslices) return;
-    const int lane = threadIdx.x;
-    const int my_cnt = (int)slot_cnt[si * WAVE + lane];
-    const int nslots = __popcll(__ballot(my_cnt > 0));
-    double m = 0.0;
-    for (int k = 0; k < nslots; ++k) {
-        const int c = __shfl(my_cnt, k, WAVE);
-        if (lane < c) {
-            const int64_t off = (int64_t)slice_vbase[si] + slot_off[si * WAVE + k];
-            double v[9];
-            BlockIO<double>::load(hi + 9 * off, slot_width(c), lane, v);
-#pragma unroll
-            for (int q = 0; q < 9; ++q) m = fmax(m, fabs(v[q]));
-        }
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) m = fmax(m, __shfl_xor(m, d, WAVE));
-    if (lane == 0) part[si] = m;
-}
-
+// With FP16 storage the value pass writes the FP64 copy only, with the largest
+// magnitude of each slice's blocks.  The largest over an instance then fixes a
+// power-of-two scale S with max |S a| in [2^13, 2^14) (FP16's largest finite
+// value is 65504, its smallest normal 2^-14), and the FP16 copy holds S a
+// rounded to nearest.  (Lanes past a slot's row count hold padding and are
+// skipped.)
 // One workgroup per instance: S of the instance's slices [inst_slice0[i],
 // inst_slice0[i + 1]) from their maxima (S = 1 for all-zero or non-finite
 // blocks; the solver's own checks report the latter), written to each of
@@ -1439,26 +1741,28 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
         if ((st = dev_alloc(ctx, (void **)&ctx->rowlen_s, sizeof(int) * (size_t)nv))) return st;
         if ((st = dev_alloc(ctx, (void **)&ctx->row_state, (size_t)nv))) return st;
         if ((st = dev_alloc(ctx, (void **)&ctx->wide_rows, sizeof(int) * (size_t)nv))) return st;
-        if ((st = dev_alloc(ctx, (void **)&ctx->row_npairs, sizeof(int) * (size_t)nv))) return st;
+        if ((st = dev_alloc(ctx, (void **)&ctx->row_npairs, (size_t)nv))) return st;
     }
     // per-row columns and pair lists between the two passes: 3 per incidence (+1 column per row)
     if (ctx->pair_incs < ctx->ninc) {
         dev_free(ctx, ctx->cols_tmp);
         dev_free(ctx, ctx->pairs_tmp);
+        dev_free(ctx, ctx->starts_tmp);
         ctx->cols_tmp = nullptr;
-        ctx->pairs_tmp = nullptr;
+        ctx->pairs_tmp = ctx->starts_tmp = nullptr;
         ctx->pair_incs = 0;
         if ((st = dev_alloc(ctx, (void **)&ctx->cols_tmp, sizeof(int) * (3 * (size_t)ctx->ninc + nv)))) return st;
-        if ((st = dev_alloc(ctx, (void **)&ctx->pairs_tmp, sizeof(int) * 3 * (size_t)ctx->ninc))) return st;
+        if ((st = dev_alloc(ctx, (void **)&ctx->pairs_tmp, 4 * (size_t)ctx->ninc))) return st;
+        if ((st = dev_alloc(ctx, (void **)&ctx->starts_tmp, 3 * (size_t)ctx->ninc + nv))) return st;
         ctx->pair_incs = ctx->ninc;
     }
     const int slot_all = ctx->prof.begin(PK_ASM_ALL, s);
     // 1. elements, each evaluated once
     int slot = ctx->prof.begin(PK_ELEMENTS, s);
-    hipLaunchKernelGGL(k_tri_eval, dim3((nt + TB - 1) / TB), dim3(TB), 0, s, nt, ctx->tri, ctx->Bm, ctx->A0, x, v,
+    hipLaunchKernelGGL(k_tri_eval, dim3((nt + EVAL_THREADS - 1) / EVAL_THREADS), dim3(EVAL_THREADS), 0, s, nt, ctx->tri, ctx->Bm, ctx->A0, x, v,
                        ctx->prm, ctx->trec);
     if (nh > 0)
-        hipLaunchKernelGGL(k_hinge_eval, dim3((nh + TB - 1) / TB), dim3(TB), 0, s, nh, ctx->hinge, ctx->hcoef,
+        hipLaunchKernelGGL(k_hinge_eval, dim3((nh + EVAL_THREADS - 1) / EVAL_THREADS), dim3(EVAL_THREADS), 0, s, nh, ctx->hinge, ctx->hcoef,
                            ctx->htbar, x, v, ctx->prm, ctx->hrec);
     if (nc > 0)
         hipLaunchKernelGGL(k_contact_eval, dim3((nc + TB - 1) / TB), dim3(TB), 0, s, nc, ctx->cverts, ctx->cw,
@@ -1486,7 +1790,8 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
     a.row_slice = ctx->row_slice; a.slice_row0 = ctx->slice_row0; a.slice_vbase = ctx->slice_vbase;
     a.row_state = ctx->row_state; a.wide_rows = ctx->wide_rows; a.wide_count = (int *)ctx->counter + 1;
     a.nslices = ctx->nslices;
-    a.cols_tmp = ctx->cols_tmp; a.pairs_tmp = ctx->pairs_tmp; a.row_npairs = ctx->row_npairs;
+    a.cols_tmp = ctx->cols_tmp; a.pairs_tmp = ctx->pairs_tmp; a.starts_tmp = ctx->starts_tmp; a.row_npairs = ctx->row_npairs;
+    a.f16_max = dtype == PC_F16 ? (unsigned long long *)ctx->f16_part : nullptr;
     a.jval_hi = dtype != PC_F64 ? ctx->jval_hi : nullptr;
     if (dtype == PC_F16) {
         // the value pass writes the FP64 copy; the FP16 copy is converted from it
@@ -1504,7 +1809,7 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
     if ((st = scan_excl(ctx, ctx->rowlen, ctx->rowptr, nv, s))) return st;
     // 4. solver layout
     hipLaunchKernelGGL(k_slice_layout, dim3(ctx->nslices), dim3(64), 0, s, ctx->nslices, ctx->slice_row0,
-                       ctx->rowlen_s, ctx->lane_row, ctx->row_lane, ctx->slot_cnt, ctx->slot_off, ctx->slice_psize);
+                       ctx->rowlen_s, ctx->lane_row, ctx->row_lane, ctx->slot_cnt, ctx->slot_off, ctx->slice_psize, a.f16_max);
     if ((st = scan_excl(ctx, ctx->slice_psize, ctx->slice_vbase, ctx->nslices, s))) return st;
     // 5. values
     slot = ctx->prof.begin(PK_ROW_ASM, s);
@@ -1524,8 +1829,6 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
         case PC_F16:
             hipLaunchKernelGGL(k_row_values<double>, dim3(ng), dim3(64), 0, s, a);
             hipLaunchKernelGGL(k_row_values_wide<double>, dim3(nwide), dim3(64), 0, s, a);
-            hipLaunchKernelGGL(k_f16_absmax, dim3(ctx->nslices), dim3(64), 0, s, ctx->nslices, ctx->slice_vbase,
-                               ctx->slot_cnt, ctx->slot_off, ctx->jval_hi, ctx->f16_part);
             hipLaunchKernelGGL(k_f16_scale, dim3(ctx->ninst), dim3(1024), 0, s, ctx->inst_slice0, ctx->f16_part,
                                ctx->f16_scale);
             hipLaunchKernelGGL(k_f16_store, dim3(ctx->nslices), dim3(64), 0, s, ctx->nslices, ctx->slice_vbase,

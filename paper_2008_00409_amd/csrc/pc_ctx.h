@@ -224,9 +224,10 @@ struct Ctx {
     int f16_cap = 0;                  // slices the two arrays can hold
     int *inst_slice0 = nullptr;       // ninst + 1 instance slice ranges (device)      // nv: blocks of each row in the solver layout (a zero diagonal left out)
     int *wide_rows = nullptr;     // nv: rows of the wide-row passes
-    int *row_npairs = nullptr;    // nv: (incidence, corner) pairs of each row
+    uint8_t *row_npairs = nullptr;   // nv: (incidence, corner) pairs of each row
     int *cols_tmp = nullptr;      // 3 ninc + nv: each row's columns, pattern pass -> value pass
-    int *pairs_tmp = nullptr;     // 3 ninc: each row's pairs grouped by column slot
+    uint8_t *pairs_tmp = nullptr;    // 3 ninc: each row's pairs grouped by column slot
+    uint8_t *starts_tmp = nullptr;   // 3 ninc + nv: first pair of each column slot
     int64_t pair_incs = 0;        // incidences the two buffers above can hold
     // element records of the last assembly (FP64 SoA planes; sizes in doubles)
     double *trec = nullptr, *hrec = nullptr, *crec = nullptr;
