@@ -108,7 +108,7 @@ static bool params_ok(const pc_params *p, std::string &err) {
 
 static void free_all(Ctx *c) {
     void *ptrs[] = {c->tri, c->Bm, c->A0, c->hinge, c->hcoef, c->htbar, c->mass, c->pinned, c->status,
-                    c->inc_cnt, c->inc_ptr, c->inc, c->rowlen, c->rowptr, c->colidx, c->jcol, c->lane_row,
+                    c->inc_cnt, c->inc_ptr, c->inc, c->mesh_ptr, c->mesh_inc, c->rowlen, c->rowptr, c->colidx, c->jcol, c->lane_row,
                     c->row_lane, c->slot_cnt, c->jval, c->diag, c->dinv, c->binv, c->zb, c->x, c->r, c->q, c->tmp, c->bbuf,
                     c->p, c->partials, c->partials_u, c->res2, c->counter, c->st, c->scan_tmp, c->jval_hi, c->slice_row0, c->slice_psize, c->slice_vbase, c->sitem_win, c->cverts, c->cw, c->cn, c->jdel, c->cg_pd, c->cg_s, c->e32, c->r32, c->q32,
                     c->row_slice, c->sitem, c->vitem, c->inst_sitem0, c->inst_vitem0, c->restart, c->maxit_d,
@@ -212,6 +212,7 @@ pc_status pc_create(const pc_mesh *mesh, const pc_params *params, pc_ctx **out) 
         ctx->ell = sum / (3.0 * nt);
     }
     if ((st = topo_build(ctx, mesh, s))) return fail(st);
+    if ((st = mesh_incidences(ctx, s))) return fail(st);
     const int nh = ctx->nh;
     if (nt >= MAX_ELEMS || nh >= MAX_ELEMS) {
         ctx->err = "more than 2^28 triangles or hinges";
@@ -223,7 +224,6 @@ pc_status pc_create(const pc_mesh *mesh, const pc_params *params, pc_ctx **out) 
         return fail(PC_ERR_ARG);
     }
     ctx->ninc = 3 * (int64_t)nt + 4 * (int64_t)nh;
-    ctx->ninc_cap = ctx->ninc;
     // block capacity: diagonal + both directions of every triangle edge (6
     // per triangle, duplicates included) + both wing pairs of every hinge
     ctx->cap = (int64_t)nv + 6 * (int64_t)nt + 2 * (int64_t)nh;
@@ -233,7 +233,6 @@ pc_status pc_create(const pc_mesh *mesh, const pc_params *params, pc_ctx **out) 
         return fail(PC_ERR_ARG);
     }
     const size_t nsl = (size_t)ctx->nslices;
-    ALLOC(ctx->inc, sizeof(int) * (size_t)ctx->ninc);
     ALLOC(ctx->rowlen, sizeof(int) * (size_t)nv);
     ALLOC(ctx->rowptr, sizeof(int) * (size_t)(nv + 1));
     ALLOC(ctx->colidx, sizeof(int) * (size_t)ctx->cap);
@@ -795,7 +794,7 @@ pc_status cloth_set_contacts(pc_ctx *h, int32_t ncontacts, const int32_t *verts,
     }
     // capacities: 4 incidences and at most 12 more blocks per contact
     const int64_t ninc = 3 * (int64_t)ctx->nt + 4 * (int64_t)ctx->nh + 4 * nc;
-    if (ninc > ctx->ninc_cap) {
+    if (nc > 0 && ninc > ctx->ninc_cap) {
         dev_free(ctx, ctx->inc);
         ctx->inc = nullptr;
         ctx->ninc_cap = 0;

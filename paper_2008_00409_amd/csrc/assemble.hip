@@ -2,9 +2,10 @@
 // Sec. 3.2.2 for the dynamic block pattern and value filling).
 //
 // Per step, from the element list (triangles and hinges):
-//   1. count the element corners incident to each vertex, scan, and fill the
-//      per-vertex incidence buckets (integer atomics only: the contents of a
-//      bucket are fixed, their order is not);
+//   1. the element corners incident to each vertex: the mesh's own, which
+//      never change, are laid out when the context is created; an assembly
+//      with contacts counts, scans and adds theirs (integer atomics only: the
+//      contents of a bucket are fixed, their order is not);
 //   2. 16 lanes per row sort its incidences (type, element, corner), derive
 //      the row's distinct block columns (sort + unique of the element
 //      neighbours), its length and the elements that meet each column; a scan
@@ -34,6 +35,7 @@ __global__ void k_fill_int(int *p, int v, int64_t n) {
 // Exclusive scan, 1024 elements per block (256 threads x 4).
 constexpr int SCAN_TILE = 1024;
 
+// Sums of the tiles; a single tile also gives the total.
 __global__ void k_scan_tiles(const int *in, int *out, int *tile_sums, int n) {
     __shared__ int sh[256];
     const int t = threadIdx.x;
@@ -58,7 +60,10 @@ __global__ void k_scan_tiles(const int *in, int *out, int *tile_sums, int n) {
         if (base + k < n) out[base + k] = run;
         run += v[k];
     }
-    if (t == 255) tile_sums[blockIdx.x] = sh[255];
+    if (t == 255) {
+        tile_sums[blockIdx.x] = sh[255];
+        if (gridDim.x == 1) out[n] = sh[255];
+    }
 }
 
 __global__ void k_scan_sums(int *tile_sums, int ntiles, int *total_out) {
@@ -85,15 +90,32 @@ __global__ void k_scan_sums(int *tile_sums, int ntiles, int *total_out) {
     if (t == 0) *total_out = carry;
 }
 
-__global__ void k_scan_add(int *out, const int *tile_sums, int n) {
-    const int i = blockIdx.x * SCAN_TILE + threadIdx.x;
-    const int add = tile_sums[blockIdx.x];
+// Adds the sum of the tiles before each block's; the last block writes the
+// total.  scanned: tile_sums holds their exclusive scan (and out[n] is there).
+__global__ void __launch_bounds__(256) k_scan_add(int *out, const int *tile_sums, int n, bool scanned) {
+    __shared__ int sh[4];
+    const int b = blockIdx.x, t = threadIdx.x;
+    int add = 0;
+    if (scanned) {
+        add = tile_sums[b];
+    } else {
+        for (int k = t; k < b; k += 256) add += tile_sums[k];
+        add = wave_sum_int(add);
+        if (lane_id() == 0) sh[t / WAVE] = add;
+        __syncthreads();
+        add = sh[0] + sh[1] + sh[2] + sh[3];
+        if (b == (int)gridDim.x - 1 && t == 0) out[n] = add + tile_sums[b];
+    }
+    const int i = b * SCAN_TILE + t;
     for (int k = 0; k < 4; ++k) {
         int j = i + k * 256;
         if (j < n) out[j] += add;
     }
 }
 
+// One launch for up to 1,024 values; two, in which every block sums the tiles
+// before it itself, up to 4 M (a third launch cost 4.6 us, reading at most
+// 4,096 sums per block less than 1); three beyond.
 pc_status scan_excl(Ctx *ctx, const int *in, int *out, int n, hipStream_t s) {
     const int ntiles = (n + SCAN_TILE - 1) / SCAN_TILE;
     if ((size_t)ntiles > ctx->scan_tmp_elems) {
@@ -103,9 +125,10 @@ pc_status scan_excl(Ctx *ctx, const int *in, int *out, int n, hipStream_t s) {
         if (st) return st;
         ctx->scan_tmp_elems = ntiles;
     }
+    const bool scanned = ntiles > 4096 || ntiles == 0;
     if (n > 0) hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), dim3(256), 0, s, in, out, ctx->scan_tmp, n);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, ctx->scan_tmp, ntiles, out + n);
-    if (n > 0) hipLaunchKernelGGL(k_scan_add, dim3(ntiles), dim3(256), 0, s, out, ctx->scan_tmp, n);
+    if (scanned) hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, ctx->scan_tmp, ntiles, out + n);
+    if (ntiles > 1) hipLaunchKernelGGL(k_scan_add, dim3(ntiles), dim3(256), 0, s, out, ctx->scan_tmp, n, scanned);
     PC_HIP(hipGetLastError());
     return PC_OK;
 }
@@ -297,46 +320,116 @@ pc_status topo_build(Ctx *ctx, const pc_mesh *mesh, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------- incidences
-// Bucket every corner of every element (3 per triangle, 4 per hinge, 4 per
-// contact) at its vertex; codes as in pc_common.h.
-__global__ void k_inc_count(int nt, int nh, int nc, const int *tri, const int *hinge, const int *cverts,
-                            int *cnt) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t ntc = 3 * (int64_t)nt, nhc = 4 * (int64_t)nh;
-    if (idx < ntc) {
-        atomicAdd(&cnt[tri[idx]], 1);
-    } else if (idx < ntc + nhc) {
-        atomicAdd(&cnt[hinge[idx - ntc]], 1);
-    } else if (idx < ntc + nhc + 4 * (int64_t)nc) {
-        atomicAdd(&cnt[cverts[idx - ntc - nhc]], 1);
-    }
-}
-
-__global__ void k_inc_fill(int nt, int nh, int nc, const int *tri, const int *hinge, const int *cverts, int *cnt,
-                           const int *ptr, int *inc) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t ntc = 3 * (int64_t)nt, nhc = 4 * (int64_t)nh;
-    int v;
-    unsigned code;
+// Every corner of every element (3 per triangle, 4 per hinge, 4 per contact)
+// is bucketed at its vertex; codes as in pc_common.h.  The mesh's buckets are
+// built once, sorted; contacts come after triangles and hinges in the order
+// of the codes, so an assembly with contacts copies the mesh's buckets and
+// appends the contacts'.  Rebuilding all of them per assembly took 0.5 ms at
+// 1.65M triangles (15M corners), bound by the atomics and their scattered
+// stores.
+__device__ __forceinline__ void mesh_corner(int64_t idx, int nt, int nh, const int *tri, const int *hinge, int &v,
+                                            unsigned &code) {
+    const int64_t ntc = 3 * (int64_t)nt;
     if (idx < ntc) {
         const int k = (int)(idx / nt), t = (int)(idx % nt);
         v = tri[idx];
         code = inc_code(INC_TRI, (unsigned)t, (unsigned)k);
-    } else if (idx < ntc + nhc) {
+    } else {
         const int64_t j = idx - ntc;
         const int k = (int)(j / nh), h = (int)(j % nh);
         v = hinge[j];
         code = inc_code(INC_HINGE, (unsigned)h, (unsigned)k);
-    } else if (idx < ntc + nhc + 4 * (int64_t)nc) {
-        const int64_t j = idx - ntc - nhc;   // contacts are vertex-major: (contact, corner)
-        const int e = (int)(j >> 2), k = (int)(j & 3);
-        v = cverts[j];
-        code = inc_code(INC_CONTACT, (unsigned)e, (unsigned)k);
-    } else {
-        return;
     }
+}
+
+__global__ void k_mesh_inc_count(int nt, int nh, const int *tri, const int *hinge, int *cnt) {
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= 3 * (int64_t)nt + 4 * (int64_t)nh) return;
+    int v;
+    unsigned code;
+    mesh_corner(idx, nt, nh, tri, hinge, v, code);
+    atomicAdd(&cnt[v], 1);
+}
+
+__global__ void k_mesh_inc_fill(int nt, int nh, const int *tri, const int *hinge, int *cnt, const int *ptr, int *inc) {
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= 3 * (int64_t)nt + 4 * (int64_t)nh) return;
+    int v;
+    unsigned code;
+    mesh_corner(idx, nt, nh, tri, hinge, v, code);
     const int slot = atomicSub(&cnt[v], 1) - 1;
     inc[ptr[v] + slot] = (int)code;
+}
+
+// Each bucket ascending (rank sort, 16 lanes a bucket) and the largest size.
+__global__ void __launch_bounds__(256) k_mesh_inc_sort(int nv, const int *ptr, const int *in, int *out, int *longest) {
+    const int i = blockIdx.x * 16 + threadIdx.x / 16, t = threadIdx.x % 16;
+    if (i >= nv) return;
+    const int p0 = ptr[i], n = ptr[i + 1] - p0;
+    for (int m = t; m < n; m += 16) {
+        const unsigned key = (unsigned)in[p0 + m];
+        int r = 0;
+        for (int q = 0; q < n; ++q) r += (unsigned)in[p0 + q] < key;
+        out[p0 + r] = (int)key;
+    }
+    if (t == 0 && n > *longest) atomicMax(longest, n);   // most buckets are as long as the longest: a load, no atomic
+}
+
+pc_status mesh_incidences(Ctx *ctx, hipStream_t s) {
+    const int nv = ctx->nv, nt = ctx->nt, nh = ctx->nh, TB = 256;
+    const int64_t ni = 3 * (int64_t)nt + 4 * (int64_t)nh;
+    pc_status st;
+    int *list = nullptr, *longest = nullptr;
+    if ((st = dev_alloc(ctx, (void **)&ctx->mesh_ptr, sizeof(int) * (size_t)(nv + 1)))) return st;
+    if ((st = dev_alloc(ctx, (void **)&ctx->mesh_inc, sizeof(int) * (size_t)ni))) return st;
+    if ((st = dev_alloc(ctx, (void **)&list, sizeof(int) * (size_t)ni))) return st;
+    if ((st = dev_alloc(ctx, (void **)&longest, sizeof(int)))) {
+        dev_free(ctx, list);
+        return st;
+    }
+    const dim3 grid((unsigned)((ni + TB - 1) / TB));
+    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, longest, 0, (int64_t)1);
+    hipLaunchKernelGGL(k_mesh_inc_count, grid, dim3(TB), 0, s, nt, nh, ctx->tri, ctx->hinge, ctx->inc_cnt);
+    st = scan_excl(ctx, ctx->inc_cnt, ctx->mesh_ptr, nv, s);
+    hipLaunchKernelGGL(k_mesh_inc_fill, grid, dim3(TB), 0, s, nt, nh, ctx->tri, ctx->hinge, ctx->inc_cnt,
+                       ctx->mesh_ptr, list);
+    hipLaunchKernelGGL(k_mesh_inc_sort, dim3((nv + 15) / 16), dim3(256), 0, s, nv, ctx->mesh_ptr, list, ctx->mesh_inc,
+                       longest);
+    const hipError_t e1 = hipMemcpyAsync(&ctx->mesh_longest, longest, sizeof(int), hipMemcpyDeviceToHost, s);
+    const hipError_t e2 = hipStreamSynchronize(s);
+    dev_free(ctx, list);
+    dev_free(ctx, longest);
+    if (st) return st;
+    PC_HIP(e1);
+    PC_HIP(e2);
+    return PC_OK;
+}
+
+// Contacts are vertex-major: (contact, corner).
+__global__ void k_contact_inc_count(int nc, const int *cverts, int *cnt) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < 4 * (int64_t)nc) atomicAdd(&cnt[cverts[j]], 1);
+}
+
+// The mesh's buckets moved apart for the contacts' (ptr: the scan of their
+// counts on entry, the buckets' starts on exit), 16 lanes a bucket.
+__global__ void __launch_bounds__(256) k_contact_inc_copy(int nv, const int *mesh_ptr, const int *mesh_inc, int *ptr,
+                                                          int *inc) {
+    const int i = blockIdx.x * 16 + threadIdx.x / 16, t = threadIdx.x % 16;
+    if (i > nv) return;
+    const int p0 = mesh_ptr[i], to = p0 + ptr[i];
+    const int n = i < nv ? mesh_ptr[i + 1] - p0 : 0;
+    for (int m = t; m < n; m += 16) inc[to + m] = mesh_inc[p0 + m];
+    if (t == 0) ptr[i] = to;   // every lane of the bucket has read it: they are one wavefront's
+}
+
+__global__ void k_contact_inc_fill(int nc, const int *cverts, int *cnt, const int *mesh_ptr, const int *ptr, int *inc) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= 4 * (int64_t)nc) return;
+    const int v = cverts[j];
+    const int slot = atomicSub(&cnt[v], 1) - 1;
+    inc[ptr[v] + (mesh_ptr[v + 1] - mesh_ptr[v]) + slot] =
+        (int)inc_code(INC_CONTACT, (unsigned)(j >> 2), (unsigned)(j & 3));
 }
 
 // Validation of a contact set: indices in range, four distinct vertices,
@@ -429,7 +522,11 @@ __device__ __forceinline__ void tri_block(const double F[3][2], const double Sp[
 
 __global__ void __launch_bounds__(EVAL_THREADS) k_tri_eval(int nt, const int *tri, const double *Bm, const double *A0,
                                                            const double *x, const double *v, DevParams P,
-                                                           double *rec) {
+                                                           double *rec, int *status, int *wide_count) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {   // the row-limit bits and wide rows describe this assembly only
+        *status &= ~(ST_INC_OVERFLOW | ST_COL_OVERFLOW);
+        *wide_count = 0;
+    }
     __shared__ double lds[WAVE * 31];
     const int e0 = blockIdx.x * EVAL_THREADS, ne = min(WAVE, nt - e0), e = e0 + min((int)threadIdx.x, ne - 1);
     TriShape sh;
@@ -549,7 +646,7 @@ __global__ void __launch_bounds__(256) k_contact_eval(int nc, const int *cverts,
 struct AsmArgs {
     int nv, nt, nh;
     const int *tri, *hinge, *inc_ptr;
-    int *inc;                    // per-row incidence codes; the pattern pass sorts each row in place
+    int *inc;                    // per-row incidence codes (sorted; with contacts the pattern pass sorts each row in place)
     int nc;                      // contacts: vertices (nc x 4), weights (nc x 4), normals (nc x 3)
     const int *cverts;
     const double *cw, *cn;
@@ -733,7 +830,8 @@ __device__ __forceinline__ int row_pattern_g(RowGroupLDS<NI> &L, const AsmArgs &
         }
     __syncthreads();
     if (fits)
-        for (int m = t; m < n; m += G) A.inc[p0 + m] = (int)L.code[m];
+        for (int m = t; m < n; m += G)
+            if (A.nc > 0) A.inc[p0 + m] = (int)L.code[m];
     const int len = row_columns_g<G, NI>(L, A, i, n, fits, t);
     // does the row keep its diagonal block: free, with a pinned column
     int anyp = 0;
@@ -820,17 +918,22 @@ __global__ void __launch_bounds__(64) k_row_pattern(AsmArgs A) {
     }
     const bool act = i < A.nv && n <= RG_NI;
     if (!act) n = 0;
-    // incidence codes ascending (distinct: rank sort), written back in place
-    for (int m = t; m < n; m += RG) L.sorted[m] = A.inc[p0 + m];
+    // incidence codes ascending; with contacts (distinct: rank sort), written back in place
+    const bool sort = A.nc > 0;
+    if (sort)
+        for (int m = t; m < n; m += RG) L.sorted[m] = A.inc[p0 + m];
     if (t == 0) L.ncand = 0;
     __syncthreads();
     for (int m = t; m < n; m += RG) {
-        const unsigned key = (unsigned)L.sorted[m];
-        int r = 0;
+        const unsigned key = sort ? (unsigned)L.sorted[m] : (unsigned)A.inc[p0 + m];
+        int r = m;
+        if (sort) {
+            r = 0;
 #pragma unroll 4
-        for (int q = 0; q < n; ++q) r += (unsigned)L.sorted[q] < key;
+            for (int q = 0; q < n; ++q) r += (unsigned)L.sorted[q] < key;
+            A.inc[p0 + r] = (int)key;
+        }
         L.code[r] = key;
-        A.inc[p0 + r] = (int)key;
         const int4 ev = element_vertices(A, key);
         L.ev[r] = ev;
         push_candidates(cand, &L.ncand, key, ev);
@@ -1673,10 +1776,6 @@ __global__ void __launch_bounds__(64) k_f16_store(int nslices, const int *slice_
 
 static size_t dtype_size(pc_dtype d) { return d == PC_F64 ? 8 : (d == PC_F32 ? 4 : 2); }
 
-__global__ void k_clear_bits(int *status, int mask) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) status[0] &= ~mask;
-}
-
 pc_status check_contacts(Ctx *ctx, int nc, int *bad, hipStream_t s) {
     hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, (int *)ctx->counter, 0, (int64_t)1);
     hipLaunchKernelGGL(k_check_contacts, dim3((nc + 255) / 256), dim3(256), 0, s, nc, ctx->nv, ctx->cverts, ctx->cw,
@@ -1760,7 +1859,7 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
     // 1. elements, each evaluated once
     int slot = ctx->prof.begin(PK_ELEMENTS, s);
     hipLaunchKernelGGL(k_tri_eval, dim3((nt + EVAL_THREADS - 1) / EVAL_THREADS), dim3(EVAL_THREADS), 0, s, nt, ctx->tri, ctx->Bm, ctx->A0, x, v,
-                       ctx->prm, ctx->trec);
+                       ctx->prm, ctx->trec, ctx->status, (int *)ctx->counter + 1);
     if (nh > 0)
         hipLaunchKernelGGL(k_hinge_eval, dim3((nh + EVAL_THREADS - 1) / EVAL_THREADS), dim3(EVAL_THREADS), 0, s, nh, ctx->hinge, ctx->hcoef,
                            ctx->htbar, x, v, ctx->prm, ctx->hrec);
@@ -1768,19 +1867,20 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
         hipLaunchKernelGGL(k_contact_eval, dim3((nc + TB - 1) / TB), dim3(TB), 0, s, nc, ctx->cverts, ctx->cw,
                            ctx->cn, ctx->ceta, ctx->ckc, x, v, ctx->prm, ctx->crec);
     ctx->prof.end(slot, s);
-    // 2. incidence buckets (the row-limit bits describe this assembly only)
-    hipLaunchKernelGGL(k_clear_bits, dim3(1), dim3(64), 0, s, ctx->status, ST_INC_OVERFLOW | ST_COL_OVERFLOW);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, (int *)ctx->counter + 1, 0, (int64_t)1);
-    const int64_t ni = 3 * (int64_t)nt + 4 * (int64_t)nh + 4 * (int64_t)nc;
-    hipLaunchKernelGGL(k_inc_count, dim3((ni + TB - 1) / TB), dim3(TB), 0, s, nt, nh, nc, ctx->tri, ctx->hinge,
-                       ctx->cverts, ctx->inc_cnt);
-    if ((st = scan_excl(ctx, ctx->inc_cnt, ctx->inc_ptr, nv, s))) return st;
-    hipLaunchKernelGGL(k_inc_fill, dim3((ni + TB - 1) / TB), dim3(TB), 0, s, nt, nh, nc, ctx->tri, ctx->hinge,
-                       ctx->cverts, ctx->inc_cnt, ctx->inc_ptr, ctx->inc);
+    // 2. incidence buckets
+    if (nc > 0) {
+        const unsigned nb = (unsigned)((4 * (int64_t)nc + TB - 1) / TB);
+        hipLaunchKernelGGL(k_contact_inc_count, dim3(nb), dim3(TB), 0, s, nc, ctx->cverts, ctx->inc_cnt);
+        if ((st = scan_excl(ctx, ctx->inc_cnt, ctx->inc_ptr, nv, s))) return st;
+        hipLaunchKernelGGL(k_contact_inc_copy, dim3((nv + 16) / 16), dim3(256), 0, s, nv, ctx->mesh_ptr, ctx->mesh_inc,
+                           ctx->inc_ptr, ctx->inc);
+        hipLaunchKernelGGL(k_contact_inc_fill, dim3(nb), dim3(TB), 0, s, nc, ctx->cverts, ctx->inc_cnt, ctx->mesh_ptr,
+                           ctx->inc_ptr, ctx->inc);
+    }
     // 3. row patterns: sorted incidences, row lengths, pointers
     AsmArgs a;
     a.nv = nv; a.nt = nt; a.nh = nh;
-    a.tri = ctx->tri; a.hinge = ctx->hinge; a.inc_ptr = ctx->inc_ptr; a.inc = ctx->inc;
+    a.tri = ctx->tri; a.hinge = ctx->hinge; a.inc_ptr = nc > 0 ? ctx->inc_ptr : ctx->mesh_ptr; a.inc = nc > 0 ? ctx->inc : ctx->mesh_inc;
     a.nc = nc; a.cverts = ctx->cverts; a.cw = ctx->cw; a.cn = ctx->cn;
     a.Bm = ctx->Bm; a.A0 = ctx->A0; a.mass = ctx->mass;
     a.trec = ctx->trec; a.hrec = ctx->hrec; a.crec = ctx->crec;
@@ -1802,9 +1902,10 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
     // four rows per workgroup; a multiple of 8 workgroups for the XCD mapping
     const int ng = (((nv + RG_ROWS - 1) / RG_ROWS + 7) / 8) * 8;
     const int nwide = 256;   // workgroups of the wide-row passes (grid-stride over the list)
+    const bool wide = nc > 0 || ctx->mesh_longest > RG_NI;   // else no row has more incidences than the row groups take
     slot = ctx->prof.begin(PK_ROW_PAT, s);
     hipLaunchKernelGGL(k_row_pattern, dim3(ng), dim3(64), 0, s, a);
-    hipLaunchKernelGGL(k_row_pattern_wide, dim3(nwide), dim3(64), 0, s, a);
+    if (wide) hipLaunchKernelGGL(k_row_pattern_wide, dim3(nwide), dim3(64), 0, s, a);
     ctx->prof.end(slot, s);
     if ((st = scan_excl(ctx, ctx->rowlen, ctx->rowptr, nv, s))) return st;
     // 4. solver layout
@@ -1816,19 +1917,19 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
     switch (dtype) {
         case PC_F64:
             hipLaunchKernelGGL(k_row_values<double>, dim3(ng), dim3(64), 0, s, a);
-            hipLaunchKernelGGL(k_row_values_wide<double>, dim3(nwide), dim3(64), 0, s, a);
+            if (wide) hipLaunchKernelGGL(k_row_values_wide<double>, dim3(nwide), dim3(64), 0, s, a);
             break;
         case PC_F32:
             hipLaunchKernelGGL(k_row_values<float>, dim3(ng), dim3(64), 0, s, a);
-            hipLaunchKernelGGL(k_row_values_wide<float>, dim3(nwide), dim3(64), 0, s, a);
+            if (wide) hipLaunchKernelGGL(k_row_values_wide<float>, dim3(nwide), dim3(64), 0, s, a);
             break;
         case PC_BF16:
             hipLaunchKernelGGL(k_row_values<bf16_t>, dim3(ng), dim3(64), 0, s, a);
-            hipLaunchKernelGGL(k_row_values_wide<bf16_t>, dim3(nwide), dim3(64), 0, s, a);
+            if (wide) hipLaunchKernelGGL(k_row_values_wide<bf16_t>, dim3(nwide), dim3(64), 0, s, a);
             break;
         case PC_F16:
             hipLaunchKernelGGL(k_row_values<double>, dim3(ng), dim3(64), 0, s, a);
-            hipLaunchKernelGGL(k_row_values_wide<double>, dim3(nwide), dim3(64), 0, s, a);
+            if (wide) hipLaunchKernelGGL(k_row_values_wide<double>, dim3(nwide), dim3(64), 0, s, a);
             hipLaunchKernelGGL(k_f16_scale, dim3(ctx->ninst), dim3(1024), 0, s, ctx->inst_slice0, ctx->f16_part,
                                ctx->f16_scale);
             hipLaunchKernelGGL(k_f16_store, dim3(ctx->nslices), dim3(64), 0, s, ctx->nslices, ctx->slice_vbase,
