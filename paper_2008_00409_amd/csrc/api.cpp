@@ -119,6 +119,8 @@ static void free_all(Ctx *c) {
     if (c->win_info_h) (void)hipHostFree(c->win_info_h);
     if (c->st_host) (void)hipHostFree(c->st_host);
     if (c->restart_h) (void)hipHostFree(c->restart_h);
+    if (c->res2_h) (void)hipHostFree(c->res2_h);
+    if (c->maxit_h) (void)hipHostFree(c->maxit_h);
     if (c->status_host) (void)hipHostFree(c->status_host);
     bell_free(c, c->bell);
 }
@@ -658,21 +660,7 @@ pc_status pc_check(pc_ctx *h, void *stream) {
     Ctx *ctx = &h->c;
     int bits = 0;
     pc_status st = read_status(ctx, (hipStream_t)stream, &bits);
-    if (st) return st;
-    if (bits & (ST_INC_OVERFLOW | ST_COL_OVERFLOW | ST_BUCKET_OVERFLOW)) {
-        ctx->err = "a vertex exceeds the per-row limits (512 incident element corners, 64 block columns; at pc_create: 64 directed edges from a lower-numbered vertex)";
-        return PC_ERR_CAPACITY;
-    }
-    if (bits & ST_NONFINITE) {
-        ctx->err = "non-finite right-hand side";
-        PC_HIP(hipMemsetAsync(ctx->status, 0, sizeof(int), (hipStream_t)stream));
-        return PC_ERR_NONFINITE;
-    }
-    if (bits) {
-        ctx->err = "device check bits " + std::to_string(bits);
-        return PC_ERR_MESH;
-    }
-    return PC_OK;
+    return st ? st : pc::status_result(ctx, bits, (hipStream_t)stream);
 }
 
 static bool opts_ok(Ctx *ctx, const pc_solve_opts *o) {
@@ -690,9 +678,8 @@ pc_status cloth_pcg_solve(pc_ctx *h, const double *b, double *dv, const pc_solve
     Ctx *ctx = &h->c;
     if (!b || !dv) { ctx->err = "cloth_pcg_solve: b and dv must be device pointers"; return PC_ERR_ARG; }
     if (!opts_ok(ctx, opts)) return PC_ERR_ARG;
-    pc_status st = pc_check(h, stream);
-    if (st) return st;
-    return pcg_run(ctx, b, dv, opts, info, (hipStream_t)stream);
+    bool refused;
+    return pcg_run(ctx, b, dv, opts, info, &refused, (hipStream_t)stream);
 }
 
 pc_status cloth_spmv(pc_ctx *h, const double *x, double *y, int32_t solver_blocks, void *stream) {
@@ -854,11 +841,11 @@ pc_status cloth_step(pc_ctx *h, double *x, double *v, int32_t nsteps, pc_dtype d
         pc_status st = assemble_run(ctx, x, v, dtype, ctx->bbuf, nullptr, s);
         if (st) return st;
         pc_solve_info info{};
-        if ((st = pc_check(h, stream))) return st;
+        bool refused;
         pc_solve_opts ok = o;
         if (!ctx->have_prev_dv && ok.warm == 1) ok.warm = 0;  // the learned start accepts dv_prev = 0
-        st = pcg_run(ctx, ctx->bbuf, ctx->tmp, &ok, &info, s);
-        if (infos) infos[k] = info;
+        st = pcg_run(ctx, ctx->bbuf, ctx->tmp, &ok, &info, &refused, s);
+        if (infos && !refused) infos[k] = info;
         if (st) return st;
         if ((st = update_run(ctx, ctx->tmp, x, v, s))) return st;
         ctx->have_prev_dv = true;

@@ -1802,6 +1802,7 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
     }
     ctx->dtype = dtype;
     ctx->win_valid = false;
+    if (ctx->nc > 0 || !ctx->win_mesh) ctx->win_known = false;   // else the pattern is the mesh's, as before
     ctx->last_x = x;
     ctx->last_v = v;
     if (dtype != PC_F64 && ctx->hi_blocks < ctx->vcap) {

@@ -253,6 +253,8 @@ struct Ctx {
     int *inst_sitem0 = nullptr, *inst_vitem0 = nullptr;
     uint8_t *restart = nullptr;       // per-instance flags (device)
     uint8_t *restart_h = nullptr;     // pinned host staging
+    double *res2_h = nullptr;         // pinned: ||t||^2, ||b||^2 per instance
+    int *maxit_h = nullptr;           // pinned: iteration budgets of a solve
     int *maxit_d = nullptr;           // per-instance iteration budget
     int sched_version = 0;
     std::vector<pc_solve_info> inst_info;
@@ -282,7 +284,7 @@ struct Ctx {
     double *partials = nullptr;   // per-block partial sums (4 doubles per block): SpMV, starts, checks
     double *partials_u = nullptr; // per-block partial sums of the CG update (2 doubles per block)
     int cg_par = 0;               // parity of the next CG iteration launched
-    double *res2 = nullptr;       // 2 doubles per instance: true-residual check
+    double *res2 = nullptr;       // 3 doubles per instance: r.z, ||r||^2, ||b||^2 of the true residual
     unsigned *counter = nullptr;
     PcgState *st = nullptr;       // device, one per instance
     PcgState *st_host = nullptr;  // pinned host, one per instance
@@ -310,7 +312,9 @@ struct Ctx {
     // column windows of the SpMV work items (p staged in LDS)
     int2 *sitem_win = nullptr;
     int win_items = 0;            // items sitem_win can hold
-    bool win_valid = false;
+    bool win_valid = false;       // the windows' use is settled for this assembly
+    bool win_known = false;       // the windows of the current pattern are known,
+    bool win_mesh = false;        // which is that of the mesh without contacts
     bool use_win = true;          // PC_OPT_LDS_WINDOW
     int win_cap = 0;              // LDS window rows of the SpMV launches (0: global gathers)
     // window summary of an assembly: {largest window within PC_WIN_MAX, items
@@ -339,8 +343,10 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
                        double *diag_out, hipStream_t s);
 pc_status export_blocks(Ctx *ctx, double *vals, double *D, bool solver, hipStream_t s);
 pc_status spmv_run(Ctx *ctx, const double *xin, double *y, bool solver, hipStream_t s);
+// refused: the assembly's status word is not clean (the result reports it, dv
+// and info are untouched).
 pc_status pcg_run(Ctx *ctx, const double *b, double *dv, const pc_solve_opts *o, pc_solve_info *info,
-                  hipStream_t s);
+                  bool *refused, hipStream_t s);
 pc_status update_run(Ctx *ctx, const double *dv, double *x, double *v, hipStream_t s);
 pc_status scan_excl(Ctx *ctx, const int *in, int *out, int n, hipStream_t s);
 // Device memory of the library: through the context's allocator
@@ -349,6 +355,7 @@ pc_status scan_excl(Ctx *ctx, const int *in, int *out, int n, hipStream_t s);
 pc_status dev_alloc(Ctx *ctx, void **p, size_t bytes);
 void dev_free(Ctx *ctx, void *p);
 pc_status read_status(Ctx *ctx, hipStream_t s, int *bits);
+pc_status status_result(Ctx *ctx, int bits, hipStream_t s);   // what status word `bits` means to a caller
 pc_status build_schedule(Ctx *ctx);
 pc_status check_contacts(Ctx *ctx, int nc, int *bad, hipStream_t s);
 pc_status bell_assemble(Ctx *ctx, const double *x, const double *v, pc_dtype dtype, double *b, hipStream_t s);

@@ -90,11 +90,39 @@ __device__ __forceinline__ void instance_sum(const double *partials, int nitems,
 }
 
 // ---------------------------------------------------------------- kernels
-// Reset the state of every instance (restart == nullptr) or of the flagged ones.
-__global__ void k_state_init(int ninst, PcgState *st, const uint8_t *restart, double tol, double rho,
-                             const int *maxit) {
+// Values of a sweep start: rz, ||r_0||^2, ||b||^2 -> state (threshold, early
+// exit when the start already meets the tolerance).
+__device__ __forceinline__ void state_start(PcgState &T, int par, const double tot[3]) {
+    T.rzp[par] = tot[0];
+    T.rz0 = tot[0];
+    T.rzd = tot[0];
+    T.rr = tot[1];
+    T.bb = tot[2];
+    T.rr0 = tot[1];
+    T.live[0] = T.live[1] = 0;
+    T.thresh = fmax(T.tol2 * tot[2], T.rho2 * tot[1]);
+    if (!isfinite(tot[1]) || !isfinite(tot[2])) {
+        T.flags |= 2;
+        T.done = 1;
+    } else if (tot[1] <= T.tol2 * tot[2] || tot[2] == 0.0) {
+        T.done = 1;
+    }
+}
+
+// Reset the state of every instance (flags == nullptr) or of the flagged ones.
+// sums: the start's values (the check that ended the previous sweep has
+// already formed its residual and direction), else k_fin_start brings them.
+// `flags` and maxit may lie in pinned host memory; the flags are kept in
+// `restart` for the kernels that follow.
+__global__ void k_state_init(int ninst, PcgState *st, const uint8_t *flags, uint8_t *restart, double tol, double rho,
+                             const int *maxit, int par, const double *sums) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ninst || (restart && !restart[i])) return;
+    if (i >= ninst) return;
+    if (flags) {
+        const uint8_t f = flags[i];
+        restart[i] = f;
+        if (!f) return;
+    }
     PcgState &S = st[i];
     S.rzp[0] = S.rzp[1] = S.alpha = S.rr = S.bb = 0.0;
     S.tol2 = tol * tol;
@@ -109,6 +137,10 @@ __global__ void k_state_init(int ninst, PcgState *st, const uint8_t *restart, do
     S.maxit = maxit[i];
     S.done = 0;
     S.flags = 0;
+    if (sums) {
+        const double tot[3] = {sums[3 * i], sums[3 * i + 1], sums[3 * i + 2]};
+        state_start(S, par, tot);
+    }
 }
 
 // Column window of every SpMV work item: the smallest and largest block
@@ -568,34 +600,25 @@ __global__ void __launch_bounds__(256) k_fin_start(Sched S, int use_sitems, int 
         instance_sum<3>(partials, S.n_sitems, S.inst_sitem0[inst], S.inst_sitem0[inst + 1], tot);
     else
         instance_sum<3>(partials, S.n_vitems, S.inst_vitem0[inst], S.inst_vitem0[inst + 1], tot);
-    if (threadIdx.x == 0) {
-        PcgState &T = st[inst];
-        T.rzp[par] = tot[0];
-        T.rz0 = tot[0];
-        T.rzd = tot[0];
-        T.rr = tot[1];
-        T.bb = tot[2];
-        T.rr0 = tot[1];
-        T.live[0] = T.live[1] = 0;
-        T.thresh = fmax(T.tol2 * tot[2], T.rho2 * tot[1]);
-        if (!isfinite(tot[1]) || !isfinite(tot[2])) {
-            T.flags |= 2;
-            T.done = 1;
-        } else if (tot[1] <= T.tol2 * tot[2] || tot[2] == 0.0) {
-            T.done = 1;
-        }
-    }
+    if (threadIdx.x == 0) state_start(st[inst], par, tot);
 }
 
-// Residual check: ||t||^2, ||b||^2 of every instance -> out2[2 inst + {0,1}].
-__global__ void __launch_bounds__(256) k_fin_check(Sched S, const double *partials, double *out2) {
+// End of a sweep, for the host (pinned memory, read after the stream has been
+// waited for): ||t||^2 and ||b||^2 of every instance, its state and the
+// assembly's status word; and the sums a next sweep starts from.
+__global__ void __launch_bounds__(256) k_fin_check(Sched S, const double *partials, double *sums, double *res2_h,
+                                                   const PcgState *st, PcgState *st_h, const int *status,
+                                                   int *status_h) {
     const int inst = blockIdx.x;
     if (inst >= S.ninst) return;
     double tot[3];
     instance_sum<3>(partials, S.n_sitems, S.inst_sitem0[inst], S.inst_sitem0[inst + 1], tot);
+    if (threadIdx.x < 3) sums[3 * inst + threadIdx.x] = threadIdx.x == 0 ? tot[0] : (threadIdx.x == 1 ? tot[1] : tot[2]);
     if (threadIdx.x == 0) {
-        out2[2 * inst] = tot[1];
-        out2[2 * inst + 1] = tot[2];
+        res2_h[2 * inst] = tot[1];
+        res2_h[2 * inst + 1] = tot[2];
+        st_h[inst] = st[inst];
+        if (inst == 0) *status_h = *status;
     }
 }
 
@@ -616,18 +639,21 @@ __global__ void __launch_bounds__(1024) k_spmv_apply(SpmvArgs M, Sched S, const 
     }
 }
 
-// End of a refinement sweep with FP32 inner vectors: x += e, e = 0.
-__global__ void k_fold(int64_t n, double *x, float *e) {
+// End of a refinement sweep with FP32 inner vectors: x += e, e = 0.  The
+// iterate is the solution so far (dv, unless null or the assembly failed).
+__global__ void k_fold(int64_t n, double *x, float *e, double *dv, const int *status) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < n) {
-        x[k] += (double)e[k];
+        const double v = x[k] + (double)e[k];
+        x[k] = v;
         e[k] = 0.0f;
+        if (dv && *status == 0) dv[k] = v;
     }
 }
 
-__global__ void k_copy_d(int64_t n, const double *src, double *dst) {
+__global__ void k_copy_d(int64_t n, const double *src, double *dst, const int *status) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = src[i];
+    if (i < n && (!status || *status == 0)) dst[i] = src[i];
 }
 
 // Zero the rows of the flagged instances (b = 0 result).
@@ -761,19 +787,25 @@ pc_status build_schedule(Ctx *ctx) {
     if ((st = realloc((void **)&ctx->partials_u, sizeof(double) * 2 * nitems))) return st;
     if (ninst != ctx->ninst || !ctx->st) {
         if ((st = realloc((void **)&ctx->st, sizeof(PcgState) * ninst))) return st;
-        if ((st = realloc((void **)&ctx->res2, sizeof(double) * 2 * ninst))) return st;
+        if ((st = realloc((void **)&ctx->res2, sizeof(double) * 3 * ninst))) return st;
         if ((st = realloc((void **)&ctx->restart, (size_t)ninst))) return st;
         if ((st = realloc((void **)&ctx->maxit_d, sizeof(int) * ninst))) return st;
         if (ctx->st_host) (void)hipHostFree(ctx->st_host);
         if (ctx->restart_h) (void)hipHostFree(ctx->restart_h);
         if (ctx->win_info_h) (void)hipHostFree(ctx->win_info_h);
+        if (ctx->res2_h) (void)hipHostFree(ctx->res2_h);
+        if (ctx->maxit_h) (void)hipHostFree(ctx->maxit_h);
         ctx->st_host = nullptr;
         ctx->restart_h = nullptr;
         ctx->win_info_h = nullptr;
+        ctx->res2_h = nullptr;
+        ctx->maxit_h = nullptr;
         if ((st = realloc((void **)&ctx->win_info, sizeof(int) * (2 + (size_t)ninst)))) return st;
         PC_HIP(hipHostMalloc((void **)&ctx->win_info_h, sizeof(int) * (2 + (size_t)ninst), hipHostMallocDefault));
         PC_HIP(hipHostMalloc((void **)&ctx->st_host, sizeof(PcgState) * ninst, hipHostMallocDefault));
         PC_HIP(hipHostMalloc((void **)&ctx->restart_h, (size_t)ninst, hipHostMallocDefault));
+        PC_HIP(hipHostMalloc((void **)&ctx->res2_h, sizeof(double) * 2 * (size_t)ninst, hipHostMallocDefault));
+        PC_HIP(hipHostMalloc((void **)&ctx->maxit_h, sizeof(int) * (size_t)ninst, hipHostMallocDefault));
     }
     if (!ctx->row_slice && (st = dev_alloc(ctx, (void **)&ctx->row_slice, sizeof(int) * (size_t)ctx->nv))) return st;
     PC_HIP(hipMemcpy(ctx->slice_row0, slice_row0.data(), sizeof(int) * slice_row0.size(), hipMemcpyHostToDevice));
@@ -789,7 +821,7 @@ pc_status build_schedule(Ctx *ctx) {
     ctx->n_vitems = (int)vitems.size();
     ctx->inst_info.assign(ninst, pc_solve_info{});
     ctx->sched_version += 1;
-    ctx->win_valid = false;
+    ctx->win_valid = ctx->win_known = false;
     ctx->assembled = false;  // the solver layout depends on the slices
     return resident_plan(ctx);
 }
@@ -809,29 +841,36 @@ static Grids grids(Ctx *ctx) {
 
 // Column windows of the SpMV items (after an assembly or a schedule change)
 // and the LDS window capacity: the largest window up to PC_WIN_MAX rows;
-// items with wider windows gather from global memory.  Synchronises.
+// items with wider windows gather from global memory.  They depend on the
+// pattern alone, which without contacts is the mesh's: the kernels run (and
+// the host waits) after the first such assembly, a schedule change, and every
+// assembly with contacts.
 #ifndef PC_WIN_MAX
 #define PC_WIN_MAX 4096
 #endif
 static pc_status ensure_windows(Ctx *ctx, hipStream_t s) {
     if (ctx->win_valid) return PC_OK;
-    if (ctx->win_items < ctx->n_sitems) {
-        if (ctx->sitem_win) dev_free(ctx, ctx->sitem_win);
-        ctx->sitem_win = nullptr;
-        ctx->win_items = 0;
-        pc_status st = dev_alloc(ctx, (void **)&ctx->sitem_win, sizeof(int2) * (size_t)ctx->n_sitems);
-        if (st) return st;
-        ctx->win_items = ctx->n_sitems;
+    if (!ctx->win_known) {
+        if (ctx->win_items < ctx->n_sitems) {
+            if (ctx->sitem_win) dev_free(ctx, ctx->sitem_win);
+            ctx->sitem_win = nullptr;
+            ctx->win_items = 0;
+            pc_status st = dev_alloc(ctx, (void **)&ctx->sitem_win, sizeof(int2) * (size_t)ctx->n_sitems);
+            if (st) return st;
+            ctx->win_items = ctx->n_sitems;
+        }
+        const Sched S = sched_args(ctx);
+        const int ni = 2 + ctx->ninst;
+        hipLaunchKernelGGL(k_clear_ints, dim3((ni + 255) / 256), dim3(256), 0, s, ctx->win_info, ni);
+        hipLaunchKernelGGL(k_item_windows, dim3(ctx->n_sitems), dim3(256), 0, s, S, ctx->slice_row0, ctx->rowptr,
+                           ctx->colidx, ctx->sitem_win, PC_WIN_MAX, ctx->win_info);
+        if (ctx->res.valid) resident_windows(ctx, ctx->win_info + 2, s);
+        PC_HIP(hipGetLastError());
+        PC_HIP(hipMemcpyAsync(ctx->win_info_h, ctx->win_info, sizeof(int) * ni, hipMemcpyDeviceToHost, s));
+        PC_HIP(hipStreamSynchronize(s));
+        ctx->win_known = true;
+        ctx->win_mesh = ctx->nc == 0;
     }
-    const Sched S = sched_args(ctx);
-    const int ni = 2 + ctx->ninst;
-    hipLaunchKernelGGL(k_clear_ints, dim3((ni + 255) / 256), dim3(256), 0, s, ctx->win_info, ni);
-    hipLaunchKernelGGL(k_item_windows, dim3(ctx->n_sitems), dim3(256), 0, s, S, ctx->slice_row0, ctx->rowptr,
-                       ctx->colidx, ctx->sitem_win, PC_WIN_MAX, ctx->win_info);
-    if (ctx->res.valid) resident_windows(ctx, ctx->win_info + 2, s);
-    PC_HIP(hipGetLastError());
-    PC_HIP(hipMemcpyAsync(ctx->win_info_h, ctx->win_info, sizeof(int) * ni, hipMemcpyDeviceToHost, s));
-    PC_HIP(hipStreamSynchronize(s));
     ctx->win_cap = ctx->use_win ? ctx->win_info_h[0] : 0;
     ctx->narrow = ctx->win_info_h[1] == 0;
     ResPlan &P = ctx->res;
@@ -933,10 +972,12 @@ static void launch_iters(Ctx *ctx, const SpmvArgs &M, const Sched &S, const Grid
 
 // Residuals always use the FP64 blocks.  mode 0 starts a sweep from x for
 // the flagged instances (restart == nullptr: all), mode 2 does the same but
-// keeps the search direction (residual replacement), mode 1 writes
-// ||b - A x||^2 and ||b||^2 of every instance to out2.
+// keeps the search direction (residual replacement); mode 1 forms the sums of
+// k_fin_check, and with `start` (FP32 inner vectors) the residual and the
+// direction of a next sweep as mode 0 does, for every instance: all are at
+// the end of a sweep.
 static void launch_residual(Ctx *ctx, const SpmvArgs &M, const Sched &S, const Grids &g, const uint8_t *restart,
-                            const double *b, const double *x, int mode, double *out2, hipStream_t s) {
+                            const double *b, const double *x, int mode, bool start, hipStream_t s) {
     using TB = double;
     if (mode == 0) {
         if (ctx->inner32)
@@ -964,9 +1005,14 @@ static void launch_residual(Ctx *ctx, const SpmvArgs &M, const Sched &S, const G
         hipLaunchKernelGGL(k_fin_start, dim3(ctx->ninst), dim3(256), 0, s, S, 1, ctx->cg_par, restart, ctx->partials,
                            ctx->st);
     } else {
-        hipLaunchKernelGGL((k_residual<TB, 1, double>), dim3(g.sblocks), dim3(g.sthreads), 0, s, M, S, restart, b, x,
-                           ctx->r, ctx->p, pre_args(ctx), ctx->partials, (double *)nullptr);
-        hipLaunchKernelGGL(k_fin_check, dim3(ctx->ninst), dim3(256), 0, s, S, ctx->partials, out2);
+        if (start)
+            hipLaunchKernelGGL((k_residual<TB, 0, float>), dim3(g.sblocks), dim3(g.sthreads), 0, s, M, S, restart, b,
+                               x, ctx->r32, ctx->p, pre_args(ctx), ctx->partials, ctx->e32);
+        else
+            hipLaunchKernelGGL((k_residual<TB, 1, double>), dim3(g.sblocks), dim3(g.sthreads), 0, s, M, S, restart, b,
+                               x, ctx->r, ctx->p, pre_args(ctx), ctx->partials, (double *)nullptr);
+        hipLaunchKernelGGL(k_fin_check, dim3(ctx->ninst), dim3(256), 0, s, S, ctx->partials, ctx->res2, ctx->res2_h,
+                           ctx->st, ctx->st_host, ctx->status, ctx->status_host);
     }
 }
 
@@ -982,11 +1028,15 @@ static void launch_start_zero(Ctx *ctx, const Sched &S, const Grids &g, const ui
                        ctx->st);
 }
 
-// With FP32 inner vectors the sweep's correction is added to x at its end.
-static void launch_fold(Ctx *ctx, hipStream_t s) {
-    if (!ctx->inner32) return;
+// End of a sweep: with FP32 inner vectors its correction is added to x; the
+// iterate goes to dv (when not null).
+static void launch_fold(Ctx *ctx, double *dv, hipStream_t s) {
     const int64_t n3 = 3 * (int64_t)ctx->nv;
-    hipLaunchKernelGGL(k_fold, dim3((n3 + 255) / 256), dim3(256), 0, s, n3, ctx->x, ctx->e32);
+    const dim3 grid((unsigned)((n3 + 255) / 256));
+    if (ctx->inner32)
+        hipLaunchKernelGGL(k_fold, grid, dim3(256), 0, s, n3, ctx->x, ctx->e32, dv, ctx->status);
+    else if (dv)
+        hipLaunchKernelGGL(k_copy_d, grid, dim3(256), 0, s, n3, ctx->x, dv, ctx->status);
 }
 
 // FP32 inner vectors apply to BF16 and FP16 blocks with the textbook
@@ -1094,6 +1144,23 @@ pc_status read_status(Ctx *ctx, hipStream_t s, int *bits) {
     return PC_OK;
 }
 
+pc_status status_result(Ctx *ctx, int bits, hipStream_t s) {
+    if (bits & (ST_INC_OVERFLOW | ST_COL_OVERFLOW | ST_BUCKET_OVERFLOW)) {
+        ctx->err = "a vertex exceeds the per-row limits (512 incident element corners, 64 block columns; at pc_create: 64 directed edges from a lower-numbered vertex)";
+        return PC_ERR_CAPACITY;
+    }
+    if (bits & ST_NONFINITE) {
+        ctx->err = "non-finite right-hand side";
+        PC_HIP(hipMemsetAsync(ctx->status, 0, sizeof(int), s));
+        return PC_ERR_NONFINITE;
+    }
+    if (bits) {
+        ctx->err = "device check bits " + std::to_string(bits);
+        return PC_ERR_MESH;
+    }
+    return PC_OK;
+}
+
 static pc_status read_states(Ctx *ctx, hipStream_t s) {
     PC_HIP(hipMemcpyAsync(ctx->st_host, ctx->st, sizeof(PcgState) * ctx->ninst, hipMemcpyDeviceToHost, s));
     PC_HIP(hipStreamSynchronize(s));
@@ -1112,10 +1179,13 @@ static pc_status upload_flags(Ctx *ctx, const std::vector<uint8_t> &f, hipStream
 // true residual misses the tolerance restart from x (iterative refinement),
 // up to max_sweeps sweeps.  Per-instance results go to ctx->inst_info; info
 // receives the aggregate (total iterations of the slowest instance, largest
-// residuals).
+// residuals).  The host waits once per sweep where every instance's
+// iterations run resident, else also per chunk of iterations; *bits gets the
+// assembly's status word with the first wait (non-zero: the caller reports
+// it; dv has not been written).
 template <typename TB>
 static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve_opts *o, pc_solve_info *info,
-                           hipStream_t s) {
+                           int *bits, hipStream_t s) {
     const SpmvArgs M = spmv_args(ctx, false);
     const SpmvArgs Mhi = spmv_args(ctx, true);
     const Sched S = sched_args(ctx);
@@ -1143,7 +1213,8 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
 
     std::vector<int> iters(ninst, 0), sweeps(ninst, 0), fallback(ninst, 0), wused(ninst, 0);
     std::vector<uint8_t> active(ninst, 1);
-    std::vector<double> res2(2 * ninst, 0.0);
+    double *const res2 = ctx->res2_h;
+    for (int i = 0; i < 2 * ninst; ++i) res2[i] = 0.0;
     // Refinement sweeps on the low-precision copy (inner reduction rho > 0)
     // have an iteration budget: half of maxit for the first, three times the
     // instance's longest earlier sweep (at least 256) for the others.  For
@@ -1153,7 +1224,13 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
     // below then moves the instance to the FP64 blocks.
     const bool sweep_budget = rho > 0.0 && ctx->hi_valid;
     std::vector<int> longest(ninst, 0);
-    std::vector<int> maxit_h(ninst, sweep_budget ? std::max(1, maxit / 2) : maxit);
+    int *const maxit_h = ctx->maxit_h;   // pinned, read by k_state_init
+    for (int i = 0; i < ninst; ++i) maxit_h[i] = sweep_budget ? std::max(1, maxit / 2) : maxit;
+    // dv takes every sweep's iterate unless it overlaps b
+    const bool apart = dv + n3 <= b || b + n3 <= dv;
+    // the sweep's final residual also starts the next one (a solve with low-
+    // precision blocks mostly needs several)
+    const bool chained = lowp && ctx->inner32 && !keep;
     pc_status st;
 
     ctx->cg_par = 0;
@@ -1168,20 +1245,20 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
         if ((st = mlp_start(ctx, ctx->mlp, ctx->last_x, ctx->last_v, b, dv, ctx->x, ctx->q, &used, s))) return st;
         warm_kind = used;
     } else if (warm) {
-        hipLaunchKernelGGL(k_copy_d, dim3((n3 + 255) / 256), dim3(256), 0, s, n3, dv, ctx->x);
+        hipLaunchKernelGGL(k_copy_d, dim3((n3 + 255) / 256), dim3(256), 0, s, n3, dv, ctx->x,
+                           (const int *)nullptr);
         warm_kind = 1;
     }
     for (int i = 0; i < ninst; ++i) wused[i] = warm_kind;
 
     // first start of every instance
-    PC_HIP(hipMemcpyAsync(ctx->maxit_d, maxit_h.data(), sizeof(int) * ninst, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_state_init, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, ctx->st,
-                       (const uint8_t *)nullptr, tol, rho, ctx->maxit_d);
+                       (const uint8_t *)nullptr, ctx->restart, tol, rho, maxit_h, 0, (const double *)nullptr);
     if (warm_kind) {
         // the start is used as given: its residual norm is no guide to the
         // CG iterations it saves (a start accurate in the slowly converging
         // smooth modes can have a residual above ||b||)
-        launch_residual(ctx, Mhi, S, g, nullptr, b, ctx->x, 0, nullptr, s);
+        launch_residual(ctx, Mhi, S, g, nullptr, b, ctx->x, 0, false, s);
     } else {
         launch_start_zero(ctx, S, g, nullptr, b, s);
     }
@@ -1191,7 +1268,6 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
     int guard = 0;
     long long nchunk = 0;
     for (;;) {
-        if ((st = read_states(ctx, s))) return st;
         // iterate until every instance is done
         const int variant = inner_hi ? 1 : 0;
         const bool resident = use_resident(ctx) && !lost;
@@ -1205,7 +1281,14 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
                 if (st) return st;
             }
         }
-        for (;;) {
+        const bool whole = resident && ctx->res.all && ctx->prof.every == 0;   // one launch to the end of the sweep
+        if (whole) {
+            st = inner_hi ? resident_launch<double>(ctx, Mhi, 1 << 30, s) : resident_launch<TB>(ctx, M, 1 << 30, s);
+            if (st) return st;
+        } else if ((st = read_states(ctx, s))) {
+            return st;
+        }
+        while (!whole) {
             bool all_done = true;
             int most = 0;
             for (int i = 0; i < ninst; ++i) {
@@ -1247,17 +1330,17 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
             if ((st = read_states(ctx, s))) return st;
             ctx->prof.harvest();
         }
+        // true residual of every instance
+        launch_fold(ctx, apart ? dv : nullptr, s);
+        launch_residual(ctx, Mhi, S, g, nullptr, b, ctx->x, 1, chained, s);
+        PC_HIP(hipGetLastError());
+        PC_HIP(hipStreamSynchronize(s));
+        if ((*bits = *ctx->status_host)) return PC_OK;
         for (int i = 0; i < ninst; ++i)
             if (active[i]) {
                 iters[i] += ctx->st_host[i].iters;
                 longest[i] = std::max(longest[i], ctx->st_host[i].iters);
             }
-        launch_fold(ctx, s);
-        // true residual of every instance
-        launch_residual(ctx, Mhi, S, g, nullptr, b, ctx->x, 1, ctx->res2, s);
-        PC_HIP(hipGetLastError());
-        PC_HIP(hipMemcpyAsync(res2.data(), ctx->res2, sizeof(double) * 2 * ninst, hipMemcpyDeviceToHost, s));
-        PC_HIP(hipStreamSynchronize(s));
         std::vector<uint8_t> again(ninst, 0);
         bool any = false, any_breakdown = false, any_lost = false;
         for (int i = 0; i < ninst; ++i) {
@@ -1302,13 +1385,14 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
                 if (sweep_budget && !inner_hi) maxit_h[i] = std::min(maxit_h[i], std::max(256, 3 * longest[i]));
             }
         }
-        PC_HIP(hipMemcpyAsync(ctx->maxit_d, maxit_h.data(), sizeof(int) * ninst, hipMemcpyHostToDevice, s));
-        if ((st = upload_flags(ctx, again, s))) return st;
-        hipLaunchKernelGGL(k_state_init, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, ctx->st, ctx->restart, tol,
-                           rho, ctx->maxit_d);
+        for (int i = 0; i < ninst; ++i) ctx->restart_h[i] = again[i];
+        hipLaunchKernelGGL(k_state_init, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, ctx->st, ctx->restart_h,
+                           ctx->restart, tol, rho, maxit_h, ctx->cg_par, chained ? ctx->res2 : (const double *)nullptr);
         // a breakdown, the switch to the FP64 blocks or a lost launch restarts
         // from P^-1 r
-        launch_residual(ctx, Mhi, S, g, ctx->restart, b, ctx->x, (keep && !any_breakdown && !any_lost) ? 2 : 0, nullptr, s);
+        if (!chained)
+            launch_residual(ctx, Mhi, S, g, ctx->restart, b, ctx->x, (keep && !any_breakdown && !any_lost) ? 2 : 0, false,
+                            s);
         PC_HIP(hipGetLastError());
     }
     // b = 0: the solution is 0 whatever the start
@@ -1324,9 +1408,11 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
         if ((st = upload_flags(ctx, zero, s))) return st;
         hipLaunchKernelGGL(k_zero_rows, dim3(g.vblocks), dim3(VT), 0, s, S, ctx->restart, ctx->x);
     }
-    hipLaunchKernelGGL(k_copy_d, dim3((n3 + 255) / 256), dim3(256), 0, s, n3, ctx->x, dv);
-    PC_HIP(hipGetLastError());
-    PC_HIP(hipStreamSynchronize(s));
+    if (anyzero || !apart) {
+        hipLaunchKernelGGL(k_copy_d, dim3((n3 + 255) / 256), dim3(256), 0, s, n3, ctx->x, dv, (const int *)nullptr);
+        PC_HIP(hipGetLastError());
+        PC_HIP(hipStreamSynchronize(s));
+    }
     pc_status ret = PC_OK;
     pc_solve_info agg{};
     double bb_all = 0.0, tt_all = 0.0;
@@ -1380,7 +1466,7 @@ static pc_status time_iters(Ctx *ctx, const double *b, int iters, float *ms, hip
     std::vector<int> big(ninst, 1 << 30);
     PC_HIP(hipMemcpyAsync(ctx->maxit_d, big.data(), sizeof(int) * ninst, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_state_init, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, ctx->st,
-                       (const uint8_t *)nullptr, 0.0, 0.0, ctx->maxit_d);
+                       (const uint8_t *)nullptr, ctx->restart, 0.0, 0.0, ctx->maxit_d, 0, (const double *)nullptr);
     pc_status wst = ensure_windows(ctx, s);
     if (wst) return wst;
     ctx->cg_par = 0;
@@ -1486,27 +1572,46 @@ pc_status autotune_run(Ctx *ctx, const double *b, int iters, int64_t *chosen, fl
 }
 
 pc_status pcg_run(Ctx *ctx, const double *b, double *dv, const pc_solve_opts *o, pc_solve_info *info,
-                  hipStream_t s) {
+                  bool *refused, hipStream_t s) {
+    *refused = false;
+    int bits = 0;
+    pc_status st = PC_OK;
     if (!ctx->assembled) {
+        if ((st = read_status(ctx, s, &bits))) return st;
+        if (bits) {
+            *refused = true;
+            return status_result(ctx, bits, s);
+        }
         ctx->err = "cloth_pcg_solve: nothing assembled";
         return PC_ERR_ARG;
     }
     ctx->precond = o ? o->precond : 0;
     ctx->method = o ? o->method : 0;
     if (ctx->method == 1 && !ctx->cg_pd) {
-        pc_status st = dev_alloc(ctx, (void **)&ctx->cg_pd, sizeof(double) * 3 * (size_t)ctx->nv);
-        if (st) return st;
+        if ((st = dev_alloc(ctx, (void **)&ctx->cg_pd, sizeof(double) * 3 * (size_t)ctx->nv))) return st;
         if ((st = dev_alloc(ctx, (void **)&ctx->cg_s, sizeof(double) * 3 * (size_t)ctx->nv))) return st;
     }
     pc_status ist = set_inner_vectors(ctx);
     if (ist) return ist;
-    switch (ctx->dtype) {
-        case PC_F64: return pcg_typed<double>(ctx, b, dv, o, info, s);
-        case PC_F32: return pcg_typed<float>(ctx, b, dv, o, info, s);
-        case PC_BF16: return pcg_typed<bf16_t>(ctx, b, dv, o, info, s);
-        case PC_F16: return pcg_typed<f16_t>(ctx, b, dv, o, info, s);
+    st = PC_ERR_ARG;
+    if (o && o->warm == 2) {   // the learned start waits for its own results
+        if ((st = read_status(ctx, s, &bits))) return st;
+        if (bits) {
+            *refused = true;
+            return status_result(ctx, bits, s);
+        }
     }
-    return PC_ERR_ARG;
+    switch (ctx->dtype) {
+        case PC_F64: st = pcg_typed<double>(ctx, b, dv, o, info, &bits, s); break;
+        case PC_F32: st = pcg_typed<float>(ctx, b, dv, o, info, &bits, s); break;
+        case PC_BF16: st = pcg_typed<bf16_t>(ctx, b, dv, o, info, &bits, s); break;
+        case PC_F16: st = pcg_typed<f16_t>(ctx, b, dv, o, info, &bits, s); break;
+    }
+    if (bits) {
+        *refused = true;
+        return status_result(ctx, bits, s);
+    }
+    return st;
 }
 
 pc_status update_run(Ctx *ctx, const double *dv, double *x, double *v, hipStream_t s) {
