@@ -119,16 +119,26 @@ struct ResInst {
     int pq_off, rz_off;    // first slots
 };
 
+// Block-column window of a resident workgroup: near rows [lo, lo + n), then
+// bn rows from blo below and an rows from alo above them.
+struct ResWin {
+    int lo, n, blo, bn, alo, an;
+};
+
 // Teams of all instances (built with the schedule) and, per assembly, their
 // block-column windows.
 struct ResPlan {
     bool valid = false, coop = false;
     int ns = 1, threads = 1024, nwg = 0;
     int slot_n = 0, slot_rep = 0, slot_rz = 0;
+    std::vector<std::pair<int, int>> rounds;   // (first workgroup, workgroups) of each launch
     ResInst *inst = nullptr;
     int4 *wg = nullptr;
-    int2 *win = nullptr;
+    ResWin *win = nullptr;
     unsigned long long *slots = nullptr;
+    int16_t *place = nullptr;                  // with contacts: columns as rows of the windows
+    size_t place_bytes = 0;
+    bool placed = false;
     size_t inst_bytes = 0, wg_bytes = 0, win_bytes = 0, slot_bytes = 0;
     const int *inst_win = nullptr;             // per instance: largest window (in Ctx::win_info)
     int win_rows = 0;                          // LDS rows of the launches (0: no instance fits)

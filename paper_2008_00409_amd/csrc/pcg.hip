@@ -864,7 +864,10 @@ static pc_status ensure_windows(Ctx *ctx, hipStream_t s) {
         hipLaunchKernelGGL(k_clear_ints, dim3((ni + 255) / 256), dim3(256), 0, s, ctx->win_info, ni);
         hipLaunchKernelGGL(k_item_windows, dim3(ctx->n_sitems), dim3(256), 0, s, S, ctx->slice_row0, ctx->rowptr,
                            ctx->colidx, ctx->sitem_win, PC_WIN_MAX, ctx->win_info);
-        if (ctx->res.valid) resident_windows(ctx, ctx->win_info + 2, s);
+        if (ctx->res.valid) {
+            pc_status st = resident_windows(ctx, ctx->win_info + 2, s);
+            if (st) return st;
+        }
         PC_HIP(hipGetLastError());
         PC_HIP(hipMemcpyAsync(ctx->win_info_h, ctx->win_info, sizeof(int) * ni, hipMemcpyDeviceToHost, s));
         PC_HIP(hipStreamSynchronize(s));

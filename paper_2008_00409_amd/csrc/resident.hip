@@ -87,7 +87,7 @@ struct ResArgs {
     // solver layout (pc_spmv.h)
     const int *slice_vbase, *lane_row, *row_lane;
     const uint8_t *slot_cnt;
-    const int16_t *jdel;
+    const int16_t *jdel;   // block columns as offsets from the slice's first row, or (FAR) as rows of the window
     const void *jval;
     const double *mass;
     const double *vscale_inv;   // FP16 blocks: 1 / S of slice s at [2 s]
@@ -95,10 +95,11 @@ struct ResArgs {
     // teams
     ResInst const *inst;
     const int4 *wg;        // instance, first pair, pairs, rank in the team
-    const int2 *win;       // block-column window of each workgroup
+    const ResWin *win;     // block-column window of each workgroup
     const int *inst_win;   // largest window of each instance's workgroups
     int win_rows;          // LDS rows of the window
     int win_cap;           // instances with a wider window are left to the three-launch iteration
+    int wg0;               // first workgroup of the launch
     PcgState *st;
     float *p;
     void *x, *r;           // iterate and residual (TV)
@@ -297,8 +298,10 @@ __device__ __forceinline__ double chain_sum(const double *v) {
 
 // NS: 64-row slices per wavefront.  NS = 1 (SPLIT): the two slices of a pair
 // are on two wavefronts (w and w + pairs); NS = 2: one pair per wavefront.
-// KIND: 0 Jacobi, 1 block Jacobi.
-template <typename TB, typename TV, int NS, int NT, int KIND>
+// KIND: 0 Jacobi, 1 block Jacobi.  FAR: windows with far rows and placed
+// columns (with contacts; a kernel of its own because the loop over the far
+// rows cost the others 3% where it was skipped).
+template <typename TB, typename TV, int NS, int NT, int KIND, bool FAR>
 __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
     extern __shared__ float4 pwin[];
     constexpr bool SPLIT = NS == 1;
@@ -315,7 +318,7 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
     __shared__ double P1[16], P2[2][4];    // wavefront sums
     __shared__ double2 pass[SPLIT ? NPL : 1][WAVE];
     __shared__ int bad;
-    const int4 G = A.wg[blockIdx.x];
+    const int4 G = A.wg[A.wg0 + (int)blockIdx.x];
     const ResInst I = A.inst[G.x];
     if (A.inst_win[G.x] > A.win_cap) return;
     PcgState &T = A.st[G.x];
@@ -328,16 +331,17 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
     const int t0 = threadIdx.x, nt = blockDim.x;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)), nw = nt / WAVE;
     const int np = G.z;
-    const int2 W = A.win[blockIdx.x];
-    const int lo = W.x, wn = W.y - W.x + 1;
+    const ResWin W = A.win[A.wg0 + (int)blockIdx.x];
+    const int lo = W.lo, wn = W.n, hi = lo + wn, nfar = FAR ? W.bn + W.an : 0;   // near rows [lo, hi), then the far ones
+    auto far_row = [&](int f) { return f < W.bn ? W.blo + f : W.alo + f - W.bn; };
     if (t0 == 0) bad = 0;
-    for (int k = t0; k < wn; k += nt) pwin[k] = ld3(A.p, lo + k);
+    for (int k = t0; k < wn + nfar; k += nt) pwin[k] = ld3(A.p, !FAR || k < wn ? lo + k : far_row(k - wn));
     // rows of this workgroup: [a0, a1) and [b0, b1); the other rows of its
     // window are its halo
     const int it0 = G.y / 16, w0 = G.y % 16, rend = I.row0 + I.nrows;
     const int a0 = min(rend, I.row0 + 2048 * it0 + 64 * w0), a1 = min(rend, a0 + 64 * np);
     const int b0 = min(rend, I.row0 + 2048 * it0 + 1024 + 64 * w0), b1 = min(rend, b0 + 64 * np);
-    const int h0 = max(0, a0 - lo), h1 = max(0, min(b0, W.y + 1) - a1), h2 = max(0, W.y + 1 - max(a1, b1));
+    const int h0 = max(0, a0 - lo), h1 = max(0, min(b0, hi) - a1), h2 = max(0, hi - max(a1, b1));
     const int hb = max(a1, b1), nh = h0 + h1 + h2;
 
     // the wavefront's slices j: local pair, half; first row r0 (rend: none);
@@ -378,7 +382,7 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
             keep[j][k].clear();
             keep[j][k].set_col((unsigned)max(srel[j], 0));
             if (slots[j].n > 0)
-                load_slot<TB>(keep[j][k], A, slots[j], k, lane, r0[j] - lo, (unsigned)max(srel[j], 0));
+                load_slot<TB>(keep[j][k], A, slots[j], k, lane, FAR ? 0 : r0[j] - lo, (unsigned)max(srel[j], 0));
             __builtin_amdgcn_sched_barrier(0);
         }
         const bool in = row < rend;
@@ -441,7 +445,7 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
             const double m = A.mass[lo + self];
             if (n > K && !ahead) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) load_slot<TB>(cur[u], A, slots[j], K + u, lane, r0[j] - lo, (unsigned)self);
+                for (int u = 0; u < U; ++u) load_slot<TB>(cur[u], A, slots[j], K + u, lane, FAR ? 0 : r0[j] - lo, (unsigned)self);
             }
             // kept blocks, GR at a time; the next ones' rows of the window
             // are read while these are applied
@@ -477,7 +481,7 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
                 S.n = over ? slots[jn].n : S.n;
                 const int sf = over ? max(srel[jn], 0) : self, rr = over ? r0[jn] : r0[j], kn = over ? K : k + U;
 #pragma unroll
-                for (int u = 0; u < U; ++u) load_slot<TB>(nxt[u], A, S, kn + u, lane, rr - lo, (unsigned)sf);
+                for (int u = 0; u < U; ++u) load_slot<TB>(nxt[u], A, S, kn + u, lane, FAR ? 0 : rr - lo, (unsigned)sf);
 #pragma unroll
                 for (int u = 0; u < U; ++u) ps4[u] = block_p(cur[u], pwin);
 #pragma unroll
@@ -749,37 +753,41 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
             T.rr = tr;
             if (new_dir) T.rzd = tz;
         }
-        auto direct = [&](int row, double z0, double z1, double z2) {
-            const float4 po = pwin[row - lo];
-            pwin[row - lo] = make_float4((float)__builtin_fma(beta, (double)po.x, z0),
+        auto direct = [&](int at, double z0, double z1, double z2) {
+            const float4 po = pwin[at];
+            pwin[at] = make_float4((float)__builtin_fma(beta, (double)po.x, z0),
                                          (float)__builtin_fma(beta, (double)po.y, z1),
                                          (float)__builtin_fma(beta, (double)po.z, z2), 0.0f);
         };
+        // n rows of the halo, four rows' loads in flight per thread
+        auto halo = [&](int n, auto row_of, auto place_of) {
+            for (int hh = t; hh < n; hh += 4 * nt) {
+                TE e[4][3];
+                int row[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    row[u] = row_of(min(hh + u * nt, n - 1));
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) e[u][c] = agent_load_f(E + (size_t)c * A.nv + row[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (hh + u * nt >= n) break;
+                    double z[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        z[c] = (double)e[u][c];
+                        if constexpr (KIND == 0) z[c] *= (double)A.pre[3 * row[u] + c];
+                    }
+                    direct(place_of(hh + u * nt, row[u]), z[0], z[1], z[2]);
+                }
+            }
+        };
         if (new_dir) {
             if (!finished) {
-                // four rows' loads in flight per thread
-                for (int hh = t; hh < nh; hh += 4 * nt) {
-                    TE e[4][3];
-                    int row[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int h = min(hh + u * nt, nh - 1);
-                        row[u] = h < h0 ? lo + h : (h < h0 + h1 ? a1 + h - h0 : hb + h - h0 - h1);
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) e[u][c] = agent_load_f(E + (size_t)c * A.nv + row[u]);
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        if (hh + u * nt >= nh) break;
-                        double z[3];
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            z[c] = (double)e[u][c];
-                            if constexpr (KIND == 0) z[c] *= (double)A.pre[3 * row[u] + c];
-                        }
-                        direct(row[u], z[0], z[1], z[2]);
-                    }
-                }
+                halo(nh, [&](int h) { return h < h0 ? lo + h : (h < h0 + h1 ? a1 + h - h0 : hb + h - h0 - h1); },
+                     [&](int, int row) { return row - lo; });
+                if constexpr (FAR) halo(nfar, far_row, [&](int f, int) { return wn + f; });
             }
 #pragma unroll
             for (int j = 0; j < NS; ++j) {
@@ -790,9 +798,9 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
 #pragma unroll
                     for (int c = 0; c < 3; ++c)
                         z[c] = (double)(RLDS ? LR[(c * NS + j) * NT + t] : rv_[RLDS ? 0 : j][c]) * (double)pre[j][c];
-                    direct(row, z[0], z[1], z[2]);
+                    direct(row - lo, z[0], z[1], z[2]);
                 } else {
-                    direct(row, (double)zf[j][0], (double)zf[j][1], (double)zf[j][2]);
+                    direct(row - lo, (double)zf[j][0], (double)zf[j][1], (double)zf[j][2]);
                 }
             }
         }
@@ -822,39 +830,76 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
     }
 }
 
-// Block-column window of every resident workgroup and the largest one of each
-// instance (block-CSR columns are ascending, so the ends of each row suffice).
+// Block-column window of every resident workgroup: the near columns (within
+// `reach` rows of its own), the smallest and largest of those below and of
+// those above them (contacts couple sheets whose rows lie far apart); and the
+// most rows of a window of each instance.
+constexpr int RES_REACH = 4096;
 __global__ void __launch_bounds__(256) k_res_windows(const ResInst *inst, const int4 *wg, const int *rowptr,
-                                                     const int *colidx, int2 *win, int *inst_win) {
-    __shared__ int sh[2][4];
+                                                     const int *colidx, int reach, ResWin *win, int *inst_win) {
+    __shared__ int sh[6][4];
     const int4 G = wg[blockIdx.x];
     const ResInst I = inst[G.x];
-    const int rend = I.row0 + I.nrows;
-    int lo = 0x7fffffff, hi = -1;
-    for (int k = threadIdx.x; k < 128 * G.z; k += blockDim.x) {
-        const int pg = G.y + k / 128, half = (k / 64) & 1;
-        const int i = I.row0 + 2048 * (pg / 16) + 1024 * half + 64 * (pg % 16) + k % 64;
-        if (i >= rend) continue;
-        lo = min(lo, colidx[rowptr[i]]);
-        hi = max(hi, colidx[rowptr[i + 1] - 1]);
+    const int rend = I.row0 + I.nrows, it0 = G.y / 16, w0 = G.y % 16;
+    const int a0 = min(rend, I.row0 + 2048 * it0 + 64 * w0), a1 = min(rend, a0 + 64 * G.z);
+    const int b0 = min(rend, I.row0 + 2048 * it0 + 1024 + 64 * w0), b1 = min(rend, b0 + 64 * G.z);
+    const int nlo = a0 - reach, nhi = max(a1, b1) + reach;
+    int v[6] = {0x7fffffff, -1, 0x7fffffff, -1, 0x7fffffff, -1};   // near, below, above: smallest, largest
+    for (int run = 0; run < 2; ++run) {
+        const int e0 = run ? rowptr[b0] : rowptr[a0], e1 = run ? rowptr[b1] : rowptr[a1];
+        for (int k = e0 + (int)threadIdx.x; k < e1; k += blockDim.x) {
+            const int c = colidx[k], q = c < nlo ? 2 : (c >= nhi ? 4 : 0);
+#pragma unroll
+            for (int x = 0; x < 6; x += 2)
+                if (q == x) {
+                    v[x] = min(v[x], c);
+                    v[x + 1] = max(v[x + 1], c);
+                }
+        }
     }
-    for (int m = 32; m >= 1; m >>= 1) {
-        lo = min(lo, __shfl_xor(lo, m, WAVE));
-        hi = max(hi, __shfl_xor(hi, m, WAVE));
-    }
-    const int w = threadIdx.x / WAVE;
-    if (lane_id() == 0) {
-        sh[0][w] = lo;
-        sh[1][w] = hi;
+#pragma unroll
+    for (int x = 0; x < 6; ++x) {
+        for (int m = 32; m >= 1; m >>= 1) {
+            const int o = __shfl_xor(v[x], m, WAVE);
+            v[x] = x & 1 ? max(v[x], o) : min(v[x], o);
+        }
+        if (lane_id() == 0) sh[x][threadIdx.x / WAVE] = v[x];
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int k = 1; k < (int)blockDim.x / WAVE; ++k) {
-            lo = min(lo, sh[0][k]);
-            hi = max(hi, sh[1][k]);
+        for (int x = 0; x < 6; ++x)
+            for (int k = 1; k < (int)blockDim.x / WAVE; ++k) v[x] = x & 1 ? max(v[x], sh[x][k]) : min(v[x], sh[x][k]);
+        ResWin W;
+        W.lo = v[0]; W.n = v[1] - v[0] + 1;
+        W.blo = v[3] < 0 ? 0 : v[2]; W.bn = v[3] < 0 ? 0 : v[3] - v[2] + 1;
+        W.alo = v[5] < 0 ? 0 : v[4]; W.an = v[5] < 0 ? 0 : v[5] - v[4] + 1;
+        win[blockIdx.x] = W;
+        atomicMax(&inst_win[G.x], W.n + W.bn + W.an);
+    }
+}
+
+// Every stored block's column as a row of its workgroup's window (where the
+// window has the rows that fit; a wider one is not used).  One workgroup per
+// resident workgroup, a wavefront per slice.
+__global__ void __launch_bounds__(512) k_res_place(const ResInst *inst, const int4 *wg, const ResWin *win,
+                                                   const int *slice_vbase, const uint8_t *slot_cnt, const int *jcol,
+                                                   int16_t *place) {
+    const int4 G = wg[blockIdx.x];
+    const ResInst I = inst[G.x];
+    const ResWin W = win[blockIdx.x];
+    const int lane = lane_id();
+    for (int q = threadIdx.x / WAVE; q < 2 * G.z; q += blockDim.x / WAVE) {
+        const int pg = G.y + q / 2, sl = 32 * (pg / 16) + 16 * (q & 1) + pg % 16;
+        if (sl >= I.nsl) continue;
+        const int s = I.slice0 + sl, cnt = (int)slot_cnt[s * WAVE + lane];
+        const int off = slice_vbase[s] + wave_excl_scan(slot_width(cnt));
+        const int n = __popcll(__ballot(cnt > 0));
+        for (int k = 0; k < n; ++k) {
+            const int at = __builtin_amdgcn_readlane(off, k) + lane;
+            if (lane >= __builtin_amdgcn_readlane(cnt, k)) continue;
+            const int c = jcol[at];
+            place[at] = (int16_t)(c < W.lo ? W.n + c - W.blo : (c < W.lo + W.n ? c - W.lo : W.n + W.bn + c - W.alo));
         }
-        win[blockIdx.x] = make_int2(lo, hi);
-        atomicMax(&inst_win[G.x], hi - lo + 1);
     }
 }
 
@@ -867,14 +912,17 @@ __global__ void k_res_clear(u64 *slots, size_t n) {
 // Teams.  With P = 1, 2 or 4 pairs per workgroup (one slice per wavefront,
 // 2 P wavefronts) or 8 (two slices per wavefront of 8), the smallest P whose
 // teams fit the compute units at once is taken: one workgroup per unit, on as
-// many units as there is work for.  Beyond (more than 1,024 rows a unit) the
-// three-launch iteration runs: whole items per workgroup kept 4 of 12 blocks a
-// row in registers and streamed the rest with 8 wavefronts in flight, 41.0 us
-// against 43.3 us at 420k rows but 62 -> 73 us for a batch in two rounds, and
-// half of the chip idle just past 262k rows.
+// many units as there is work for.  Where 8 do not fit, the instances go in
+// several rounds, each to the end of the sweep.  An instance of more than
+// 1,024 rows a unit does not fit any round: the three-launch iteration runs.
+// (Whole items per workgroup, 2,048 rows, kept 4 of 12 blocks a row in
+// registers and streamed the rest with 8 wavefronts in flight: 41.0 us against
+// 43.3 us at 420k rows, but half of the chip idle just past 262k rows, and a
+// batch in two such rounds 73 us against 62 us.)
 pc_status resident_plan(Ctx *ctx) {
     ResPlan &P = ctx->res;
     P.valid = false;
+    P.rounds.clear();
     const int ninst = (int)ctx->inst_row0_h.size() - 1;
     int dev = 0, ncu = 0;
     PC_HIP(hipGetDevice(&dev));
@@ -895,7 +943,7 @@ pc_status resident_plan(Ctx *ctx) {
     }
     auto pairs_of = [](const ResInst &I) { return 16 * (I.nitems - 1) + std::min(16, I.nsl - 32 * (I.nitems - 1)); };
     auto team_of = [&](const ResInst &I, int per) { return (pairs_of(I) + per - 1) / per; };
-    int per = 0;
+    int per = 8;
     for (int cand : {1, 2, 4, 8}) {
         int64_t sum = 0;
         for (const ResInst &I : inst) sum += team_of(I, cand);
@@ -904,15 +952,19 @@ pc_status resident_plan(Ctx *ctx) {
             break;
         }
     }
-    if (per == 0) return PC_OK;
     P.ns = per <= 4 ? 1 : 2;
     P.threads = per <= 4 ? 2 * per * WAVE : 512;
     std::vector<int4> wg;
-    int npq = 0, nrz = 0;
+    int npq = 0, nrz = 0, first = 0;
     for (int i = 0; i < ninst; ++i) {
         ResInst &I = inst[i];
         I.k = per;
         I.team = team_of(I, per);
+        if (I.team > ncu) return PC_OK;
+        if ((int)wg.size() - first + I.team > ncu) {
+            P.rounds.push_back({first, (int)wg.size() - first});
+            first = (int)wg.size();
+        }
         const int pairs = pairs_of(I);
         for (int g = 0; g < I.team; ++g) wg.push_back(int4{i, g * per, std::min(per, pairs - g * per), g});
         I.pq_off = npq;
@@ -920,6 +972,7 @@ pc_status resident_plan(Ctx *ctx) {
         npq += per <= 4 ? 32 * I.nitems : (4 * I.nitems + 15) / 16 * 16;   // whole cache lines
         nrz += 32 * I.nitems;
     }
+    P.rounds.push_back({first, (int)wg.size() - first});
     P.slot_rz = npq;
     P.slot_n = npq + nrz;
     P.slot_rep = 2 * P.slot_n + 32;
@@ -937,7 +990,7 @@ pc_status resident_plan(Ctx *ctx) {
     };
     if ((st = grow((void **)&P.inst, P.inst_bytes, sizeof(ResInst) * ninst))) return st;
     if ((st = grow((void **)&P.wg, P.wg_bytes, sizeof(int4) * wg.size()))) return st;
-    if ((st = grow((void **)&P.win, P.win_bytes, sizeof(int2) * wg.size()))) return st;
+    if ((st = grow((void **)&P.win, P.win_bytes, sizeof(ResWin) * wg.size()))) return st;
     if ((st = grow((void **)&P.slots, P.slot_bytes, sizeof(u64) * (size_t)REPLICAS * P.slot_rep))) return st;
     PC_HIP(hipMemcpy(P.inst, inst.data(), sizeof(ResInst) * ninst, hipMemcpyHostToDevice));
     PC_HIP(hipMemcpy(P.wg, wg.data(), sizeof(int4) * wg.size(), hipMemcpyHostToDevice));
@@ -952,37 +1005,62 @@ void resident_free(Ctx *ctx) {
     dev_free(ctx, P.wg);
     dev_free(ctx, P.win);
     dev_free(ctx, P.slots);
+    dev_free(ctx, P.place);
     P = ResPlan{};
 }
 
-void resident_windows(Ctx *ctx, int *inst_win, hipStream_t s) {
-    const ResPlan &P = ctx->res;
-    hipLaunchKernelGGL(k_res_windows, dim3(P.nwg), dim3(256), 0, s, P.inst, P.wg, ctx->rowptr, ctx->colidx, P.win,
-                       inst_win);
+// Without contacts one near range is the whole window and the 16-bit offsets
+// serve; with contacts the columns are placed per assembly (16 bits a block).
+pc_status resident_windows(Ctx *ctx, int *inst_win, hipStream_t s) {
+    ResPlan &P = ctx->res;
+    P.placed = ctx->nc > 0;
+    hipLaunchKernelGGL(k_res_windows, dim3(P.nwg), dim3(256), 0, s, P.inst, P.wg, ctx->rowptr, ctx->colidx,
+                       P.placed ? RES_REACH : 1 << 30, P.win, inst_win);
+    if (P.placed) {
+        const size_t bytes = sizeof(int16_t) * (size_t)ctx->vcap;
+        if (bytes > P.place_bytes) {
+            dev_free(ctx, P.place);
+            P.place = nullptr;
+            P.place_bytes = 0;
+            pc_status st = dev_alloc(ctx, (void **)&P.place, bytes);
+            if (st) return st;
+            P.place_bytes = bytes;
+        }
+        hipLaunchKernelGGL(k_res_place, dim3(P.nwg), dim3(512), 0, s, P.inst, P.wg, P.win, ctx->slice_vbase,
+                           ctx->slot_cnt, ctx->jcol, P.place);
+    }
+    return PC_OK;
 }
 
-template <typename TB, typename TV, int NS, int NT, int KIND>
+template <typename TB, typename TV, int NS, int NT, int KIND, bool FAR>
 static pc_status launch_kind(Ctx *ctx, ResArgs &A, hipStream_t s) {
     const ResPlan &P = ctx->res;
     const size_t lds = sizeof(float4) * (size_t)P.win_rows + sizeof(TV) * (size_t)(3 * NS * NT * res_vectors(NS)) +
                        sizeof(double) * RAW;
-    const void *fn = (const void *)k_pcg_resident<TB, TV, NS, NT, KIND>;
+    const void *fn = (const void *)k_pcg_resident<TB, TV, NS, NT, KIND, FAR>;
     PC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const size_t nslots = (size_t)REPLICAS * P.slot_rep;
     hipLaunchKernelGGL(k_res_clear, dim3((nslots + 255) / 256), dim3(256), 0, s, A.slots, nslots);
-    if (P.coop) {
-        void *args[] = {&A};
-        PC_HIP(hipLaunchCooperativeKernel(fn, dim3(P.nwg), dim3(P.threads), args, (unsigned)lds, s));
-    } else {
-        hipLaunchKernelGGL((k_pcg_resident<TB, TV, NS, NT, KIND>), dim3(P.nwg), dim3(P.threads), lds, s, A);
+    for (const auto &round : P.rounds) {
+        A.wg0 = round.first;
+        if (P.coop) {
+            void *args[] = {&A};
+            PC_HIP(hipLaunchCooperativeKernel(fn, dim3(round.second), dim3(P.threads), args, (unsigned)lds, s));
+        } else {
+            hipLaunchKernelGGL((k_pcg_resident<TB, TV, NS, NT, KIND, FAR>), dim3(round.second), dim3(P.threads), lds, s, A);
+        }
+        PC_HIP(hipGetLastError());
     }
-    PC_HIP(hipGetLastError());
     return PC_OK;
 }
 
 template <typename TB, typename TV, int NS, int NT>
 static pc_status launch_ns(Ctx *ctx, ResArgs &A, hipStream_t s) {
-    return ctx->precond == 0 ? launch_kind<TB, TV, NS, NT, 0>(ctx, A, s) : launch_kind<TB, TV, NS, NT, 1>(ctx, A, s);
+    if (ctx->res.placed)
+        return ctx->precond == 0 ? launch_kind<TB, TV, NS, NT, 0, true>(ctx, A, s)
+                                 : launch_kind<TB, TV, NS, NT, 1, true>(ctx, A, s);
+    return ctx->precond == 0 ? launch_kind<TB, TV, NS, NT, 0, false>(ctx, A, s)
+                             : launch_kind<TB, TV, NS, NT, 1, false>(ctx, A, s);
 }
 
 int resident_win_max(const Ctx *ctx) {
@@ -1010,7 +1088,7 @@ pc_status resident_launch(Ctx *ctx, const SpmvArgs &M, int max_iters, hipStream_
     A.lane_row = M.lane_row;
     A.row_lane = ctx->row_lane;
     A.slot_cnt = M.slot_cnt;
-    A.jdel = ctx->jdel;   // offsets within a window of at most 9,728 rows always fit 16 bits
+    A.jdel = P.placed ? P.place : ctx->jdel;   // within a window of at most 9,728 rows both fit 16 bits
     A.jval = M.jval;
     A.mass = M.mass;
     A.vscale_inv = ctx->f16_scale ? ctx->f16_scale + 1 : nullptr;

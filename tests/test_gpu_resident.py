@@ -28,13 +28,15 @@ def B():
     return binding
 
 
-def both(torch, B, c, dtype, precond, maxit, instances=None, spoil=None):
+def both(torch, B, c, dtype, precond, maxit, instances=None, spoil=None, contacts=None):
     """(dv, info) with the resident launches and with three launches."""
     ctx = B.Context.from_cloth(c)
     out = []
     try:
         if instances is not None:
             ctx.set_instances(instances)
+        if contacts is not None:
+            ctx.cloth_set_contacts(*contacts)
         v = to_dev(torch, random_velocity(c, 0.05, seed=2))
         for window in (1, 0):
             ctx.set_option(B.PC_OPT_LDS_WINDOW, window)
@@ -83,3 +85,44 @@ def test_resident_reports_a_right_hand_side_that_is_not_finite(torch, B, value):
     (_, i1), (_, i0) = both(torch, B, c, "f16", "block", maxit=40, spoil=(3 * 700, value))
     assert i1["status"] == i0["status"] != 0
     assert i1["iters"] == i0["iters"] and i1["sweeps"] == i0["sweeps"]
+
+
+@pytest.mark.parametrize("nx,ny", [(5, 4), (23, 19), (90, 70), (150, 130)])
+@pytest.mark.parametrize("sheets", [2, 3])
+def test_resident_with_contacts_between_sheets(torch, B, sheets, nx, ny):
+    """Contacts between neighbouring sheets put columns far below and above a
+    workgroup's own rows (up to 2 x 19,500 away): random vertex-face pairs."""
+    parts = [sheet(nx, ny, seed=51 + k, bumps=False, delaunay=False) for k in range(sheets)]
+    n = nx * ny
+    cat = lambda k: np.concatenate([getattr(q, k) for q in parts])
+    tris = np.concatenate([q.tris + n * k for k, q in enumerate(parts)]).astype(np.int32)
+    x0 = cat("x0")
+    for k in range(sheets):
+        x0[n * k:n * (k + 1), 2] += 1.5e-3 * k
+    c = mg.Cloth("stack", cat("rest"), tris, cat("mass"), cat("pinned"), x0, cat("v0"), 0.01, 1e-6, 1,
+                 [(0, sheets * n)], [(0, len(tris))])
+    rng = np.random.default_rng(7)
+    up = rng.permutation(n)[:max(3, n // 2)]
+    low = parts[0].tris[rng.integers(0, len(parts[0].tris), len(up))]
+    near = np.array([parts[0].tris[np.argmin(np.abs(parts[0].tris - u).sum(axis=1))] for u in up[:64]])
+    low[:len(near)] = near
+    verts = np.concatenate([np.column_stack([n * (k + 1) + up, n * k + low]) for k in range(sheets - 1)]).astype(np.int32)
+    weights = np.tile([1.0, -0.5, -0.3, -0.2], (len(verts), 1))
+    normals = np.tile([0.0, 0.0, 1.0], (len(verts), 1))
+    for dtype, precond in (("f16", "block"), ("f32", "jacobi"), ("f64", "block")):
+        check_same(both(torch, B, c, dtype, precond, maxit=23, contacts=(verts, weights, normals, 2e-3, 1000.0)))
+
+
+@pytest.mark.parametrize("count,nx,ny", [(17, 128, 128), (40, 80, 90), (300, 20, 20), (257, 2, 2)])
+def test_resident_rounds(torch, B, count, nx, ny):
+    """More instances than the chip takes at once: several launches (the last
+    shape is one workgroup an instance)."""
+    parts = [sheet(nx, ny, seed=61 + k % 3, bumps=False, delaunay=False) for k in range(count)]
+    n = nx * ny
+    cat = lambda k: np.concatenate([getattr(q, k) for q in parts])
+    tris = np.concatenate([q.tris + n * k for k, q in enumerate(parts)]).astype(np.int32)
+    c = mg.Cloth("rounds", cat("rest"), tris, cat("mass"), cat("pinned"), cat("x0"), cat("v0"), 0.01, 1e-6, 1,
+                 [(0, count * n)], [(0, len(tris))])
+    begins = list(range(0, count * n + 1, n))
+    for dtype, precond in (("bf16", "block"), ("f32", "block"), ("f64", "jacobi")):
+        check_same(both(torch, B, c, dtype, precond, maxit=60, instances=begins))
