@@ -47,6 +47,17 @@ __device__ __forceinline__ short f2bf(float f) {
     u += 0x7fffu + ((u >> 16) & 1u);
     return (short)(u >> 16);
 }
+// Four values at a time in gfx950's packed conversion (two instructions): the
+// same bits as f2bf for every float (all 2^32 compared, NaN included).
+__device__ __forceinline__ bf16x4 f2bf4(float a, float b, float c, float d) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const f32x2 lo = {a, b}, hi = {c, d};
+    const u32x2 r = {__builtin_bit_cast(unsigned, __builtin_convertvector(lo, b16x2)),
+                     __builtin_bit_cast(unsigned, __builtin_convertvector(hi, b16x2))};
+    return __builtin_bit_cast(bf16x4, r);
+}
 __device__ __forceinline__ float bf2f(short s) { return __uint_as_float(((unsigned)(unsigned short)s) << 16); }
 
 // Offsets of the padded parameter layout (floats).
@@ -103,32 +114,57 @@ __global__ void __launch_bounds__(64) k_mfma_probe(float *out) {
 // ---------------------------------------------------------------- features
 // The 27 features of vertex i (see the oracle's definition), rounded to
 // BF16, in a row of 32 (features 27..31 = 0).  Rows nv..nv_pad-1 are zero.
-__global__ void k_ws_features(int nv, int nv_pad, const int *rowptr, const int *colidx, const double *x,
+// Bound by the latency of the neighbours' values behind their columns: three
+// neighbours (39 values) are in flight at a time, added in column order: 60 ->
+// 37 us at 159k vertices (two 40-42, four 38, seven 43 us; one by one with
+// whole-row stores 47 us).
+constexpr int FT_THREADS = 128, FT_BATCH = 3;
+__global__ void __launch_bounds__(FT_THREADS) k_ws_features(int nv, int nv_pad, const int *rowptr, const int *colidx, const double *x,
                               const double *v, const double *b, const double *diag, const double *mass,
                               const uint8_t *pinned, const double *dvp, double ell, double h, short *X) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nv_pad) return;
     float f[32];
+#pragma unroll
     for (int q = 0; q < 32; ++q) f[q] = 0.0f;
     if (i < nv) {
         const double sv = ell / h;
         const double mi = mass[i];
         double sdv[3] = {0, 0, 0}, sbm[3] = {0, 0, 0}, svv[3] = {0, 0, 0}, sx[3] = {0, 0, 0};
         int cnt = 0;
-        for (int p = rowptr[i]; p < rowptr[i + 1]; ++p) {
-            const int j = colidx[p];
-            if (j == i) continue;
-            ++cnt;
-            const double mj = mass[j];
-            for (int a = 0; a < 3; ++a) {
-                sdv[a] += dvp[3 * j + a];
-                sbm[a] += b[3 * j + a] / mj;
-                svv[a] += v[3 * j + a];
-                sx[a] += x[3 * j + a];
+        const int p1 = rowptr[i + 1];
+        for (int p = rowptr[i]; p < p1; p += FT_BATCH) {
+            int j[FT_BATCH];
+            double n[FT_BATCH][13];
+#pragma unroll
+            for (int u = 0; u < FT_BATCH; ++u) j[u] = colidx[min(p + u, p1 - 1)];
+#pragma unroll
+            for (int u = 0; u < FT_BATCH; ++u) {
+                n[u][12] = mass[j[u]];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    n[u][a] = dvp[3 * j[u] + a];
+                    n[u][3 + a] = b[3 * j[u] + a];
+                    n[u][6 + a] = v[3 * j[u] + a];
+                    n[u][9 + a] = x[3 * j[u] + a];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < FT_BATCH; ++u) {
+                if (p + u >= p1 || j[u] == i) continue;
+                ++cnt;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    sdv[a] += n[u][a];
+                    sbm[a] += n[u][3 + a] / n[u][12];
+                    svv[a] += n[u][6 + a];
+                    sx[a] += n[u][9 + a];
+                }
             }
         }
         const double inv = 1.0 / (double)(cnt > 0 ? cnt : 1);
         double dsum = 0.0;
+#pragma unroll
         for (int a = 0; a < 3; ++a) {
             const double bi = b[3 * i + a], bmi = bi / mi;
             f[0 + a] = (float)(v[3 * i + a] / sv);
@@ -145,26 +181,42 @@ __global__ void k_ws_features(int nv, int nv_pad, const int *rowptr, const int *
         f[25] = (float)log10(dsum / 3.0 / mi);
         f[26] = (float)(cnt / 12.0);
     }
-    for (int q = 0; q < 32; ++q) X[(int64_t)i * 32 + q] = f2bf(f[q]);
+    uint4 *out = (uint4 *)(X + (int64_t)i * 32);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        unsigned u[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            u[k] = (unsigned short)f2bf(f[8 * q + 2 * k]) | (unsigned)(unsigned short)f2bf(f[8 * q + 2 * k + 1]) << 16;
+        out[q] = make_uint4(u[0], u[1], u[2], u[3]);
+    }
 }
 
 // ---------------------------------------------------------------- forward
-// A-operand tile of W^T (rows: output features m0.., K: input features k0..)
-// from the row-major [in][out] BF16 weights.
-__device__ __forceinline__ bf16x4 load_wt(const short *W, int out, int m0, int k0) {
-    const int l = threadIdx.x & 63;
-    bf16x4 a;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = W[(k0 + 4 * (l / 16) + i) * out + m0 + l % 16];
-    return a;
+// The BF16 weights are kept as the lanes take them, twice: as the A operand of
+// W (bwd) and, MLP_PADDED values further on, of W^T (fwd).  Tile (m, k) of a
+// layer: lane l's four values are row 16 m + l % 16, columns 16 k + 4 (l / 16)
+// .., so a wavefront reads a tile as 512 consecutive bytes (from row-major
+// weights: 176 two-byte loads per wavefront for W^T).
+__device__ __forceinline__ int weight_at(int row, int col, int cols) {
+    const int l = row % 16 + 16 * (col % 16 / 4);
+    return ((row / 16 * (cols / 16) + col / 16) * 64 + l) * 4 + col % 4;
 }
-// A-operand tile of W (rows: input features m0.., K: output features k0..).
-__device__ __forceinline__ bf16x4 load_w(const short *W, int out, int m0, int k0) {
-    const int l = threadIdx.x & 63;
-    bf16x4 a;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = W[(m0 + l % 16) * out + k0 + 4 * (l / 16) + i];
-    return a;
+__device__ __forceinline__ void store_weight(short *wb, int i, float w) {
+    int off, in, out;
+    if (i < OFF_B1) { off = OFF_W1; in = 32; out = 64; }
+    else if (i >= OFF_W2 && i < OFF_B2) { off = OFF_W2; in = 64; out = 64; }
+    else if (i >= OFF_W3 && i < OFF_B3) { off = OFF_W3; in = 64; out = 64; }
+    else if (i >= OFF_W4 && i < OFF_B4) { off = OFF_W4; in = 64; out = 16; }
+    else return;   // biases are read in FP32
+    const int r = (i - off) / out, c = (i - off) % out;
+    const short b = f2bf(w);
+    wb[off + weight_at(r, c, out)] = b;
+    wb[MLP_PADDED + off + weight_at(c, r, in)] = b;
+}
+// tile (m, k) of a layer whose rows have `cols` values
+__device__ __forceinline__ bf16x4 load_w(const short *W, int cols, int m, int k) {
+    return *reinterpret_cast<const bf16x4 *>(W + ((m * (cols / 16) + k) * 64 + (threadIdx.x & 63)) * 4);
 }
 // B-operand / accumulator-layout tile of a vertex-major [v][width] BF16 array.
 __device__ __forceinline__ bf16x4 load_act(const short *H, int width, int v0, int f0) {
@@ -174,19 +226,28 @@ __device__ __forceinline__ bf16x4 load_act(const short *H, int width, int v0, in
     r[0] = p[0]; r[1] = p[1]; r[2] = p[2]; r[3] = p[3];
     return r;
 }
-__device__ __forceinline__ void store_act(short *H, int width, int v0, int f0, bf16x4 r) {
-    const int l = threadIdx.x & 63;
-    short *p = H + (int64_t)(v0 + l % 16) * width + f0 + 4 * (l / 16);
-    p[0] = r[0]; p[1] = r[1]; p[2] = r[2]; p[3] = r[3];
+// The hidden activations and gradients are stored as the lanes hold them:
+// tile t of 16 vertices, block m of 16 features, lane, its four values (vertex
+// l % 16, features 4 (l / 16) ..), so a wavefront reads or writes 512
+// consecutive bytes.
+__device__ __forceinline__ int64_t act_at(int t, int m) {
+    return (int64_t)t * 1024 + m * 256 + 4 * (threadIdx.x & 63);
+}
+__device__ __forceinline__ bf16x4 load_tile(const short *H, int t, int m) {
+    return *reinterpret_cast<const bf16x4 *>(H + act_at(t, m));
+}
+__device__ __forceinline__ void store_tile(short *H, int t, int m, bf16x4 r) {
+    *reinterpret_cast<bf16x4 *>(H + act_at(t, m)) = r;
 }
 
 // Bias + ReLU + BF16 of an accumulator tile whose rows are features f0..f0+15.
 __device__ __forceinline__ bf16x4 act_relu(f32x4 c, const float *bias, int f0) {
     const int l = threadIdx.x & 63;
-    bf16x4 r;
+    const float *p = bias + f0 + 4 * (l / 16);
+    float r[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = f2bf(fmaxf(c[i] + bias[f0 + 4 * (l / 16) + i], 0.0f));
-    return r;
+    for (int i = 0; i < 4; ++i) r[i] = fmaxf(c[i] + p[i], 0.0f);
+    return f2bf4(r[0], r[1], r[2], r[3]);
 }
 
 struct FwdArgs {
@@ -201,29 +262,45 @@ struct FwdArgs {
     double *dv0;          // start: dv_prev + s_v y (free), 0 (pinned); dvp == nullptr: s_v y
 };
 
+// Both passes hold the weights in 144-148 registers, so three wavefronts fit a
+// SIMD: 768 blocks of four are all resident, and none waits for a second turn
+// (us with 512 / 768 / 1,024 blocks: fwd 24.9 / 23.8 / 29.9 and bwd 25.3 / 26.4
+// / 27.8 at 159k vertices, fwd 9.5 / 10.6 / 11.8 at 62k).
+constexpr int MLP_BLOCKS = 768;
+
 // One wavefront per 16-vertex tile, grid-stride over tiles; weights stay in
-// registers for all tiles of the wavefront.
+// registers for all tiles of the wavefront.  Bound by the vector instructions
+// between the layers (bias, ReLU, rounding) and their chain: 38 -> 24 us at
+// 159k vertices (71 MB) and 18 -> 10.6 at 62k, nearly all of it from the packed
+// rounding.  The next tile's input is loaded a tile ahead.
 __global__ void __launch_bounds__(256) k_mlp_fwd(FwdArgs F) {
     const int l = threadIdx.x & 63;
     const int wave = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
     const int nwaves = gridDim.x * (blockDim.x / 64);
-    const short *W1 = F.Wb + OFF_W1, *W2 = F.Wb + OFF_W2, *W3 = F.Wb + OFF_W3, *W4 = F.Wb + OFF_W4;
+    const short *Wt = F.Wb + MLP_PADDED, *W1 = Wt + OFF_W1, *W2 = Wt + OFF_W2, *W3 = Wt + OFF_W3, *W4 = Wt + OFF_W4;
     bf16x4 A1[4][2], A2[4][4], A3[4][4], A4[4];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) A1[m][k] = load_wt(W1, 64, 16 * m, 16 * k);
+        for (int k = 0; k < 2; ++k) A1[m][k] = load_w(W1, 32, m, k);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            A2[m][k] = load_wt(W2, 64, 16 * m, 16 * k);
-            A3[m][k] = load_wt(W3, 64, 16 * m, 16 * k);
+            A2[m][k] = load_w(W2, 64, m, k);
+            A3[m][k] = load_w(W3, 64, m, k);
         }
-        A4[m] = load_wt(W4, 16, 0, 16 * m);
+        A4[m] = load_w(W4, 64, 0, m);
     }
     const float *b1 = F.Wf + OFF_B1, *b2 = F.Wf + OFF_B2, *b3 = F.Wf + OFF_B3, *b4 = F.Wf + OFF_B4;
+    bf16x4 N0{}, N1{};   // the next tile's input, loaded a tile ahead
+    if (wave < F.ntiles) {
+        N0 = load_act(F.X, 32, 16 * wave, 0);
+        N1 = load_act(F.X, 32, 16 * wave, 16);
+    }
     for (int t = wave; t < F.ntiles; t += nwaves) {
-        const int v0 = 16 * t;
-        bf16x4 X0 = load_act(F.X, 32, v0, 0), X1 = load_act(F.X, 32, v0, 16);
+        const int v0 = 16 * t, vn = 16 * min(t + nwaves, F.ntiles - 1);
+        const bf16x4 X0 = N0, X1 = N1;
+        N0 = load_act(F.X, 32, vn, 0);
+        N1 = load_act(F.X, 32, vn, 16);
         bf16x4 H1[4], H2[4], H3[4];
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
@@ -251,19 +328,20 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(FwdArgs F) {
         if (F.H1) {
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                store_act(F.H1, 64, v0, 16 * m, H1[m]);
-                store_act(F.H2, 64, v0, 16 * m, H2[m]);
-                store_act(F.H3, 64, v0, 16 * m, H3[m]);
+                store_tile(F.H1, t, m, H1[m]);
+                store_tile(F.H2, t, m, H2[m]);
+                store_tile(F.H3, t, m, H3[m]);
             }
         }
         // lanes 0..15 hold output rows 0..3 of vertex v0 + l
         const int vtx = v0 + l;
         if (l < 16 && vtx < F.nv) {
+            const bool pin = F.pinned[vtx] != 0;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const double ya = (double)(y[a] + b4[a]);
                 const double base = F.dvp ? F.dvp[3 * vtx + a] : 0.0;
-                F.dv0[3 * vtx + a] = F.pinned[vtx] ? 0.0 : base + F.sv * ya;
+                const double ya = (double)(y[a] + b4[a]);
+                F.dv0[3 * vtx + a] = pin ? 0.0 : base + F.sv * ya;
             }
         }
     }
@@ -284,6 +362,11 @@ __global__ void k_ws_out_grad(int nv, int nv_pad, const double *Ad, const double
     for (int q = 0; q < 16; ++q) G4[(int64_t)i * 16 + q] = f2bf(q < 3 ? g[q] : 0.0f);
 }
 
+// c where the activation h (at least 0, never NaN) is positive
+__device__ __forceinline__ bf16x4 relu_grad(f32x4 c, bf16x4 h) {
+    return f2bf4(h[0] > 0 ? c[0] : 0.0f, h[1] > 0 ? c[1] : 0.0f, h[2] > 0 ? c[2] : 0.0f, h[3] > 0 ? c[3] : 0.0f);
+}
+
 struct BwdArgs {
     int ntiles;
     const short *Wb;
@@ -292,61 +375,69 @@ struct BwdArgs {
 };
 
 // G3 = (W4 G4) . [H3 > 0], G2 = (W3 G3) . [H2 > 0], G1 = (W2 G2) . [H1 > 0],
-// each rounded to BF16 and stored for the weight gradients.
+// each rounded to BF16 and stored for the weight gradients.  Bound by its 122
+// MB at 159k vertices: 52 -> 30 us with the next tile's operands loaded a tile
+// ahead in 512-byte pieces (row by row before), 26 (4.7 TB/s) with the packed
+// rounding.
 __global__ void __launch_bounds__(256) k_mlp_bwd(BwdArgs B) {
-    const int l = threadIdx.x & 63;
     const int wave = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
     const int nwaves = gridDim.x * (blockDim.x / 64);
     const short *W2 = B.Wb + OFF_W2, *W3 = B.Wb + OFF_W3, *W4 = B.Wb + OFF_W4;
     bf16x4 A4[4], A3[4][4], A2[4][4];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-        A4[m] = load_w(W4, 16, 16 * m, 0);
+        A4[m] = load_w(W4, 16, m, 0);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            A3[m][k] = load_w(W3, 64, 16 * m, 16 * k);
-            A2[m][k] = load_w(W2, 64, 16 * m, 16 * k);
+            A3[m][k] = load_w(W3, 64, m, k);
+            A2[m][k] = load_w(W2, 64, m, k);
         }
     }
-    (void)l;
+    bf16x4 ng{}, nh[3][4];   // the next tile's operands, loaded a tile ahead
+    auto fetch = [&](int t) {
+        ng = load_act(B.G4, 16, 16 * t, 0);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            nh[0][m] = load_tile(B.H3, t, m);
+            nh[1][m] = load_tile(B.H2, t, m);
+            nh[2][m] = load_tile(B.H1, t, m);
+        }
+    };
+    if (wave < B.ntiles) fetch(wave);
     for (int t = wave; t < B.ntiles; t += nwaves) {
-        const int v0 = 16 * t;
-        const bf16x4 g4 = load_act(B.G4, 16, v0, 0);
+        const bf16x4 g4 = ng;
+        bf16x4 hs[3][4];
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) hs[q][m] = nh[q][m];
+        fetch(min(t + nwaves, B.ntiles - 1));
         bf16x4 G3[4], G2[4], G1[4];
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             f32x4 c = {0.f, 0.f, 0.f, 0.f};
             c = mfma16(A4[m], g4, c);
-            const bf16x4 h = load_act(B.H3, 64, v0, 16 * m);
-            bf16x4 r;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] = f2bf(bf2f(h[i]) > 0.0f ? c[i] : 0.0f);
+            const bf16x4 r = relu_grad(c, hs[0][m]);
             G3[m] = r;
-            store_act(B.G3, 64, v0, 16 * m, r);
+            store_tile(B.G3, t, m, r);
         }
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             f32x4 c = {0.f, 0.f, 0.f, 0.f};
             c = mfma32(A3[m][0], A3[m][1], G3[0], G3[1], c);
             c = mfma32(A3[m][2], A3[m][3], G3[2], G3[3], c);
-            const bf16x4 h = load_act(B.H2, 64, v0, 16 * m);
-            bf16x4 r;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] = f2bf(bf2f(h[i]) > 0.0f ? c[i] : 0.0f);
+            const bf16x4 r = relu_grad(c, hs[1][m]);
             G2[m] = r;
-            store_act(B.G2, 64, v0, 16 * m, r);
+            store_tile(B.G2, t, m, r);
         }
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             f32x4 c = {0.f, 0.f, 0.f, 0.f};
             c = mfma32(A2[m][0], A2[m][1], G2[0], G2[1], c);
             c = mfma32(A2[m][2], A2[m][3], G2[2], G2[3], c);
-            const bf16x4 h = load_act(B.H1, 64, v0, 16 * m);
-            bf16x4 r;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] = f2bf(bf2f(h[i]) > 0.0f ? c[i] : 0.0f);
+            const bf16x4 r = relu_grad(c, hs[2][m]);
             G1[m] = r;
-            store_act(B.G1, 64, v0, 16 * m, r);
+            store_tile(B.G1, t, m, r);
         }
     }
 }
@@ -366,23 +457,23 @@ __constant__ GradTile c_tiles[MLP_GRAD_TILES];
 // grid is three blocks per CU.  Partial tiles
 // go to part[block][tile][16 x 16] (row-major).
 //
-// A lane's K values are 8 vertices of one feature, 128 bytes apart in the
-// vertex-major activations, so each 32-vertex chunk of all eight arrays
-// (X, H1..H3, G1..G4: 27 KiB) is first copied to LDS with 16-byte loads, in
-// the same vertex-major order.  Every array gets rows of WG_P = 68 values
-// (64 + 4 padding, whatever its width): the 2-byte operand reads of the four
-// lane groups (rows 4 apart) then fall on distinct banks, and a read's offset
-// from its tile's base is a constant.  Vertices past the block's range are
-// staged as zeros.
+// A lane's K values are 8 vertices of one feature: each 32-vertex chunk of all
+// eight arrays (X, H1..H3, G1..G4: 27 KiB) is copied to LDS with 16-byte loads
+// and turned feature-major on the way (a unit of the tiles of H and G holds
+// four features of two neighbouring vertices: four dwords), so that an operand
+// is two 8-byte reads instead of eight 2-byte ones, which bound the kernel (41
+// us at 159k vertices, 33 now).  Rows of WG_P = 36 values (32 + 4 padding): a
+// unit's dword writes of a wavefront fall on distinct banks.  Vertices past
+// the block's range are staged as zeros.
 // Arrays k = 0..7: X (32 features), H1, H2, H3, G1, G2, G3 (64), G4 (16).
-constexpr int WG_V = 32, WG_P = 68;
+constexpr int WG_V = 32, WG_P = 36;
 __host__ __device__ constexpr int wg_width(int k) { return k == 0 ? 32 : (k == 7 ? 16 : 64); }
-__host__ __device__ constexpr int wg_off(int k) { return k * WG_V * WG_P; }
+__host__ __device__ constexpr int wg_off(int k) { return k == 0 ? 0 : (32 + 64 * (k - 1)) * WG_P; }
 // first 16-byte unit of array k in a chunk
 __host__ __device__ constexpr int wg_units(int k) {
     return k == 0 ? 0 : (k <= 7 ? WG_V * 32 / 8 + (k - 1) * WG_V * 64 / 8 : WG_V * (32 + 6 * 64 + 16) / 8);
 }
-constexpr int WG_LDS = wg_off(8);       // 17,408 values
+constexpr int WG_LDS = wg_off(7) + 16 * WG_P;   // 15,552 values
 constexpr int WG_UNITS = wg_units(8);   // 1,728 16-byte units per chunk
 static_assert(wg_units(7) + WG_V * wg_width(7) / 8 == WG_UNITS, "unit count");
 static_assert(WG_P % 4 == 0, "LDS rows must stay 8-byte aligned");
@@ -409,8 +500,20 @@ __global__ void __launch_bounds__(256, 3) k_mlp_wgrad(int ntiles, const short *X
     const bool hi = threadIdx.x >= 128;
     const int uidx = hi ? (int)threadIdx.x - 128 : (int)threadIdx.x + 128;   // unit within its array (k >= 1)
     uint4 pre[UPT];
+    // Array j's unit of this thread: vertex of the chunk (the first of two in
+    // the tiles of H and G) and feature of its first value.
+    auto unit_of = [&](int k, int &v, int &f) {
+        const int u = k == 0 ? (int)threadIdx.x : uidx, W = wg_width(k);
+        if (W == 64) {
+            const int tile = u / 128, m = u / 32 % 4, l2 = 2 * (u % 32);   // lanes l2, l2 + 1 of the tile's block m
+            v = 16 * tile + l2 % 16;
+            f = 16 * m + 4 * (l2 / 16);
+        } else {
+            v = 8 * u / W;
+            f = 8 * u % W;
+        }
+    };
     auto load_chunk = [&](int t) {
-        const int v0 = 16 * t;
         const int nvalid = min(WG_V, 16 * (t1 - t));
 #pragma unroll
         for (int j = 0; j < UPT; ++j) {
@@ -419,8 +522,8 @@ __global__ void __launch_bounds__(256, 3) k_mlp_wgrad(int ntiles, const short *X
             const int e = 8 * (k == 0 ? (int)threadIdx.x : uidx);
             const short *p = hi ? src[j + 1] : src[j];
             pre[j] = make_uint4(0u, 0u, 0u, 0u);
-            if ((j < 6 || threadIdx.x < 192) && e / W < nvalid)
-                pre[j] = *reinterpret_cast<const uint4 *>(p + (int64_t)v0 * W + e);
+            if ((j < 6 || threadIdx.x < 192) && e < nvalid * W)
+                pre[j] = *reinterpret_cast<const uint4 *>(p + (int64_t)16 * t * W + e);
         }
     };
     auto store_chunk = [&]() {
@@ -428,11 +531,21 @@ __global__ void __launch_bounds__(256, 3) k_mlp_wgrad(int ntiles, const short *X
         for (int j = 0; j < UPT; ++j) {
             if (j == 6 && threadIdx.x >= 192) continue;
             const int k = hi ? j + 1 : j;
-            const int W = wg_width(k);
-            const int e = 8 * (k == 0 ? (int)threadIdx.x : uidx);
-            uint2 *dst = reinterpret_cast<uint2 *>(L + wg_off(k) + (e / W) * WG_P + e % W);
-            dst[0] = make_uint2(pre[j].x, pre[j].y);
-            dst[1] = make_uint2(pre[j].z, pre[j].w);
+            int v, f;
+            unit_of(k, v, f);
+            short *dst = L + wg_off(k) + f * WG_P + v;
+            const unsigned q[4] = {pre[j].x, pre[j].y, pre[j].z, pre[j].w};
+            if (wg_width(k) == 64) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {   // feature f + i of vertices v, v + 1
+                    const unsigned a = q[i / 2], b = q[2 + i / 2];
+                    *reinterpret_cast<unsigned *>(dst + i * WG_P) =
+                        i % 2 ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | b << 16;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) dst[i * WG_P] = (short)(q[i / 2] >> (16 * (i % 2)));
+            }
         }
     };
     if (t0 < t1) load_chunk(t0);
@@ -446,17 +559,16 @@ __global__ void __launch_bounds__(256, 3) k_mlp_wgrad(int ntiles, const short *X
             if (tile >= MLP_GRAD_TILES) continue;       // uniform per wavefront
             const GradTile T = c_tiles[tile];
             const int kin = T.layer, kout = 4 + T.layer;
-            const short *Lin = L + wg_off(kin) + 4 * (l / 16) * WG_P + 16 * T.mb + l % 16;
-            const short *Lout = L + wg_off(kout) + 4 * (l / 16) * WG_P + 16 * T.nb + l % 16;
+            const short *Lin = L + wg_off(kin) + (16 * T.mb + l % 16) * WG_P + 4 * (l / 16);
+            const short *Lout = L + wg_off(kout) + (16 * T.nb + l % 16) * WG_P + 4 * (l / 16);
             bf16x4 a[2], bb[2];
+            const short one = (l % 16) == 0 ? 0x3F80 : 0;
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    // vertex 16 h + 4 (l / 16) + i of the chunk
-                    a[h][i] = T.bias ? (short)((l % 16) == 0 ? 0x3F80 : 0) : Lin[(16 * h + i) * WG_P];
-                    bb[h][i] = Lout[(16 * h + i) * WG_P];
-                }
+            for (int h = 0; h < 2; ++h) {
+                // vertices 16 h + 4 (l / 16) .. + 3 of the chunk
+                a[h] = T.bias ? bf16x4{one, one, one, one} : *reinterpret_cast<const bf16x4 *>(Lin + 16 * h);
+                bb[h] = *reinterpret_cast<const bf16x4 *>(Lout + 16 * h);
+            }
             acc[q] = mfma32(a[0], a[1], bb[0], bb[1], acc[q]);
         }
         __syncthreads();
@@ -481,6 +593,7 @@ __global__ void __launch_bounds__(256) k_mlp_grad_reduce(int nblocks, const floa
     const int tile = blockIdx.x, quarter = blockIdx.y;
     const int j = threadIdx.x % 16, g = threadIdx.x / 16;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
     for (int b = g; b < nblocks; b += 16) {
         const float4 p =
             *reinterpret_cast<const float4 *>(part + ((int64_t)b * MLP_GRAD_TILES + tile) * 256 + 64 * quarter + 4 * j);
@@ -519,12 +632,12 @@ __global__ void k_adam(int n, float *w, float *m, float *v, const float *g, shor
     v[i] = vi;
     const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
     w[i] = wi;
-    wb[i] = f2bf(wi);
+    store_weight(wb, i, wi);
 }
 
 __global__ void k_to_bf16(int n, const float *w, short *wb) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) wb[i] = f2bf(w[i]);
+    if (i < n) store_weight(wb, i, w[i]);
 }
 
 // ---------------------------------------------------------------- reductions
@@ -609,7 +722,7 @@ pc_status mlp_init(Ctx *ctx, MlpState *M) {
     pc_status st;
     void **bufs[] = {(void **)&M->w, (void **)&M->m, (void **)&M->v, (void **)&M->g, (void **)&M->wb};
     const size_t sizes[] = {sizeof(float) * MLP_PADDED, sizeof(float) * MLP_PADDED, sizeof(float) * MLP_PADDED,
-                            sizeof(float) * MLP_PADDED, sizeof(short) * MLP_PADDED};
+                            sizeof(float) * MLP_PADDED, 2 * sizeof(short) * MLP_PADDED};
     for (int k = 0; k < 5; ++k)
         if ((st = dev_alloc(ctx, bufs[k], sizes[k]))) return st;
     if ((st = dev_alloc(ctx, (void **)&M->X, sizeof(short) * 32 * nvp))) return st;
@@ -619,7 +732,7 @@ pc_status mlp_init(Ctx *ctx, MlpState *M) {
     PC_HIP(hipMemset(M->m, 0, sizeof(float) * MLP_PADDED));
     PC_HIP(hipMemset(M->v, 0, sizeof(float) * MLP_PADDED));
     PC_HIP(hipMemset(M->g, 0, sizeof(float) * MLP_PADDED));
-    PC_HIP(hipMemset(M->wb, 0, sizeof(short) * MLP_PADDED));
+    PC_HIP(hipMemset(M->wb, 0, 2 * sizeof(short) * MLP_PADDED));
     M->ready = true;
     return PC_OK;
 }
@@ -704,7 +817,7 @@ pc_status mlp_features(Ctx *ctx, MlpState *M, const double *x, const double *v, 
         ctx->err = "warm start: nothing assembled";
         return PC_ERR_ARG;
     }
-    hipLaunchKernelGGL(k_ws_features, dim3((M->nv_pad + 255) / 256), dim3(256), 0, s, ctx->nv, M->nv_pad,
+    hipLaunchKernelGGL(k_ws_features, dim3((M->nv_pad + FT_THREADS - 1) / FT_THREADS), dim3(FT_THREADS), 0, s, ctx->nv, M->nv_pad,
                        ctx->rowptr, ctx->colidx, x, v, b, ctx->diag, ctx->mass, ctx->pinned, dvp, ctx->ell,
                        ctx->prm.h, M->X);
     PC_HIP(hipGetLastError());
@@ -727,7 +840,7 @@ pc_status mlp_forward(Ctx *ctx, MlpState *M, const double *dvp, double *dv0, boo
     F.pinned = ctx->pinned;
     F.sv = ctx->ell / ctx->prm.h;
     F.dv0 = dv0;
-    const int blocks = std::min(1024, (F.ntiles + 3) / 4);
+    const int blocks = std::min(MLP_BLOCKS, (F.ntiles + 3) / 4);
     hipLaunchKernelGGL(k_mlp_fwd, dim3(blocks > 0 ? blocks : 1), dim3(256), 0, s, F);
     PC_HIP(hipGetLastError());
     return PC_OK;
@@ -766,7 +879,7 @@ pc_status mlp_gradient(Ctx *ctx, MlpState *M, const double *x, const double *v, 
     Bw.Wb = M->wb;
     Bw.H1 = M->H1; Bw.H2 = M->H2; Bw.H3 = M->H3; Bw.G4 = M->G4;
     Bw.G1 = M->G1; Bw.G2 = M->G2; Bw.G3 = M->G3;
-    const int blocks = std::min(1024, (Bw.ntiles + 3) / 4);
+    const int blocks = std::min(MLP_BLOCKS, (Bw.ntiles + 3) / 4);
     hipLaunchKernelGGL(k_mlp_bwd, dim3(blocks > 0 ? blocks : 1), dim3(256), 0, s, Bw);
     hipLaunchKernelGGL(k_mlp_wgrad, dim3(MLP_WGRAD_BLOCKS), dim3(256), 0, s, M->nv_pad / 16, M->X, M->H1, M->H2,
                        M->H3, M->G1, M->G2, M->G3, M->G4, M->part);
@@ -888,7 +1001,7 @@ pc_status mlp_predict_noalloc(Ctx *ctx, const double *x, const double *v, const 
         return PC_ERR_ARG;
     }
     short *X = (short *)ctx->ws_scratch;
-    hipLaunchKernelGGL(k_ws_features, dim3((nv_pad + 255) / 256), dim3(256), 0, s, ctx->nv, nv_pad, ctx->rowptr,
+    hipLaunchKernelGGL(k_ws_features, dim3((nv_pad + FT_THREADS - 1) / FT_THREADS), dim3(FT_THREADS), 0, s, ctx->nv, nv_pad, ctx->rowptr,
                        ctx->colidx, x, v, b, ctx->diag, ctx->mass, ctx->pinned, dvp, ctx->ell, ctx->prm.h, X);
     PC_HIP(hipGetLastError());
     FwdArgs F;
@@ -902,7 +1015,7 @@ pc_status mlp_predict_noalloc(Ctx *ctx, const double *x, const double *v, const 
     F.pinned = ctx->pinned;
     F.sv = ctx->ell / ctx->prm.h;
     F.dv0 = dv0;
-    const int blocks = std::min(1024, (F.ntiles + 3) / 4);
+    const int blocks = std::min(MLP_BLOCKS, (F.ntiles + 3) / 4);
     hipLaunchKernelGGL(k_mlp_fwd, dim3(blocks > 0 ? blocks : 1), dim3(256), 0, s, F);
     PC_HIP(hipGetLastError());
     return PC_OK;

@@ -15,7 +15,7 @@ struct MlpState {
     int step = 0;
     double last_scale = 0.0;
     float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;  // padded FP32 parameters, Adam moments, gradient
-    short *wb = nullptr;                                             // BF16 copy of w
+    short *wb = nullptr;                                             // BF16 copies of the weights as operands of W and of W^T
     short *X = nullptr;                                              // features [nv_pad][32]
     short *H1 = nullptr, *H2 = nullptr, *H3 = nullptr;               // activations [nv_pad][64]
     short *G1 = nullptr, *G2 = nullptr, *G3 = nullptr;               // gradients [nv_pad][64]
