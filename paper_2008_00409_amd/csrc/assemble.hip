@@ -1336,19 +1336,24 @@ __device__ __forceinline__ void row_values_g(RowGroupLDS<NI> &L, const AsmArgs &
 // slices' largest magnitudes are taken here, from the registers.
 //
 // What bounds it is the latency of its three rounds of dependent loads (the
-// row's state, its lists, the records) at 11 wavefronts a compute unit, and
-// behind it the memory traffic (2 GB).  Reading the records pair by pair from
+// row's state, its lists, the records) at 12 wavefronts a compute unit, and
+// behind it the memory traffic (2 GB) and the vector instructions (1,120 a
+// wavefront, 45% of its time).  Reading the records pair by pair from
 // planes took 420 accesses to the L1 a row (1.35 ms for 828k rows; also 64 or
 // 16 rows side by side per load, with 2 to 4 pairs in flight, 1.55 to 1.65
 // ms); so the parts of the records that the group needs come once, 16 bytes a
 // lane, straight into LDS, all in flight together, and the pairs are read
 // from there: 1.02 ms, which replaces the 0.13 ms of a pass over the blocks
-// for their magnitudes too.  Workgroups that stay and fetch the next group's
+// for their magnitudes too.  The lanes of the incidences list the chunks'
+// sources: with each chunk's row, incidence and part found from its number
+// there were 1,680 vector instructions a wavefront; and every value that the
+// slots need is requested before the one wait for the records: 0.85 ms.
+// Workgroups that stay and fetch the next group's
 // lists ahead measured 1.5 to 1.85 ms: their waits include the stores.
 constexpr int REC_CHUNKS = 704;   // 16-byte chunks of records a group keeps in LDS; the incidences beyond are read directly
 constexpr int TRI_CHUNKS = 12;    // of a triangle: the two blocks and the force of the row's corner
 struct RowPairsLDS {
-    unsigned code[RG_NI + 1];
+    unsigned loc[RG_NI + 1];   // where each incidence's records lie (rec_loc)
     unsigned pair[3 * RG_NI / 4 + 1];
     int cols[MAX_COLS + 1];
     uint8_t start[MAX_COLS + 4];
@@ -1358,27 +1363,25 @@ struct RowRecordsLDS {
     RowPairsLDS row[RG_ROWS];
 };
 
-// Where a row's incidence records lie: triangles from chunk c0, hinges from
-// chunk h0 (hc chunks each); nt triangles.
-struct RowChunks {
-    int c0, h0, nt, hc;
-    __device__ __forceinline__ int at(int m) const { return m < nt ? c0 + TRI_CHUNKS * m : h0 + hc * (m - nt); }
-    __device__ __forceinline__ bool in_lds(int m, unsigned type) const {
-        return type != INC_CONTACT && at(m) + (m < nt ? TRI_CHUNKS : hc) <= REC_CHUNKS;
-    }
-};
+// An incidence's place: its first chunk, the row's corner, and whether it is a
+// triangle and in LDS.
+constexpr unsigned LOC_TRI = 1u << 12, LOC_LDS = 1u << 13;
+__device__ __forceinline__ unsigned rec_loc(int at, unsigned code, bool in) {
+    return in ? (unsigned)at | (unsigned)inc_corner(code) << 10 | (inc_type(code) == INC_TRI ? LOC_TRI : 0u) | LOC_LDS : 0u;
+}
+static_assert(REC_CHUNKS <= 1024, "first chunks take 10 bits");
 
 // add_stiffness and add_force from LDS where the record is there.
-__device__ __forceinline__ void add_stiffness_lds(const RowRecordsLDS &L, const AsmArgs &A, const RowChunks &C,
-                                                  unsigned code, int m, int l, double acc[9]) {
-    const int k = inc_corner(code);
-    const unsigned type = inc_type(code);
-    if (!C.in_lds(m, type)) {
-        add_stiffness(A, code, l, acc);
+// w = the incidence's place, inc = its code
+__device__ __forceinline__ void add_stiffness_lds(const RowRecordsLDS &L, const AsmArgs &A, unsigned w, const int *inc,
+                                                  int l, double acc[9]) {
+    if (!(w & LOC_LDS)) {
+        add_stiffness(A, (unsigned)*inc, l, acc);
         return;
     }
-    const double *R = (const double *)(L.rec + C.at(m));
-    if (type == INC_TRI) {
+    const int k = w >> 10 & 3;
+    const double *R = (const double *)(L.rec + (w & 1023));
+    if (w & LOC_TRI) {
         R += l == (k == 2 ? 1 : 2) ? 10 : 0;   // the corner's second block
         double K[9];
 #pragma unroll
@@ -1401,20 +1404,18 @@ __device__ __forceinline__ void add_stiffness_lds(const RowRecordsLDS &L, const 
     }
 }
 
-__device__ __forceinline__ void add_force_lds(const RowRecordsLDS &L, const AsmArgs &A, const RowChunks &C,
-                                              unsigned code, int m, double f[3]) {
-    const int k = inc_corner(code);
-    const unsigned type = inc_type(code);
-    if (!C.in_lds(m, type)) {
-        add_force(A, code, f);
+__device__ __forceinline__ void add_force_lds(const RowRecordsLDS &L, const AsmArgs &A, unsigned w, const int *inc,
+                                              double f[3]) {
+    if (!(w & LOC_LDS)) {
+        add_force(A, (unsigned)*inc, f);
         return;
     }
-    const double *R = (const double *)(L.rec + C.at(m));
-    if (type == INC_TRI) {
+    const double *R = (const double *)(L.rec + (w & 1023));
+    if (w & LOC_TRI) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) f[a] += R[20 + a];
     } else {
-        const double phi = R[12], *G = A.prm.s_look != 0.0 ? R + 14 : R + 3 * k;
+        const double phi = R[12], *G = A.prm.s_look != 0.0 ? R + 14 : R + 3 * (w >> 10 & 3);
 #pragma unroll
         for (int a = 0; a < 3; ++a) f[a] = __builtin_fma(phi, G[a], f[a]);
     }
@@ -1430,8 +1431,10 @@ __global__ void __launch_bounds__(64, 3) k_row_values(AsmArgs A) {
     // the row's state and what its outputs need
     int st = -1, p0 = 0, n = 0, len = 0, np = 0, rp = 0, pos = 0, si = 0;
     bool rowpin = false, keep = false;
+    double mass = 0.0;
     d3 vi = mk(0.0, 0.0, 0.0);
     if (i < A.nv) {
+        mass = A.mass[i];
         st = (int)A.row_state[i];
         p0 = A.inc_ptr[i];
         n = A.inc_ptr[i + 1] - p0;
@@ -1448,13 +1451,14 @@ __global__ void __launch_bounds__(64, 3) k_row_values(AsmArgs A) {
     if (st != ROW_GROUP) n = len = np = 0;
     // its lists
     const unsigned *pairs = (const unsigned *)A.pairs_tmp + p0;
+    const int *const inc = A.inc + p0;
     const int l0 = 3 * p0 + i;   // the row's part of cols_tmp and starts_tmp
     unsigned code[2] = {0u, 0u}, pair[2] = {0u, 0u};
     int cols[4] = {0, 0, 0, 0}, first[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int m = t + RG * k;
-        if (m < n) code[k] = (unsigned)A.inc[p0 + m];
+        if (m < n) code[k] = (unsigned)inc[m];
         if (4 * m < np) pair[k] = pairs[m];
     }
 #pragma unroll
@@ -1470,7 +1474,6 @@ __global__ void __launch_bounds__(64, 3) k_row_values(AsmArgs A) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int m = t + RG * k;
-        if (m < n) W.code[m] = code[k];
         if (4 * m < np) W.pair[m] = pair[k];
         const unsigned sh = RG * g;
         ntri += __popc((unsigned)(__ballot(m < n && inc_type(code[k]) == INC_TRI) >> sh) & 0xffffu);
@@ -1485,69 +1488,85 @@ __global__ void __launch_bounds__(64, 3) k_row_values(AsmArgs A) {
         }
     }
     if (t == 0) W.start[len] = (uint8_t)np;
-    // chunks of the group's records, row after row
+    // chunks of the group's records, row after row: a row's triangles from
+    // chunk c0, then its hinges
     const bool look = P.s_look != 0.0;
-    RowChunks C;
-    C.hc = look ? 9 : 7;
-    C.nt = ntri;
-    const int mine = TRI_CHUNKS * ntri + C.hc * nhin;
-    int end[RG_ROWS], tris[RG_ROWS], total = 0;
+    const int hc = look ? 9 : 7, hstride = look ? HREC_LOOK / 2 : HREC / 2;
+    const int mine = TRI_CHUNKS * ntri + hc * nhin;
+    int c0 = 0, total = 0;
 #pragma unroll
     for (int k = 0; k < RG_ROWS; ++k) {
-        if (k == g) C.c0 = total;
+        if (k == g) c0 = total;
         total += __builtin_amdgcn_readlane(mine, RG * k);
-        end[k] = total;
-        tris[k] = __builtin_amdgcn_readlane(ntri, RG * k);
     }
-    C.h0 = C.c0 + TRI_CHUNKS * ntri;
-    __syncthreads();
-    total = min(total, REC_CHUNKS);
-    for (int b = 0; b < total; b += WAVE) {
-        const int c = b + lane;
-        int row = 0, base = 0, rt = tris[0];
+    // each chunk's source (16-byte units; hinges' with bit 31), at the end of
+    // the space that the chunks will take: a load's chunks end before the
+    // sources of the ones after it
+    unsigned *const source = (unsigned *)(L.rec + REC_CHUNKS) - REC_CHUNKS;
+    int stop = 0;
 #pragma unroll
-        for (int k = 1; k < RG_ROWS; ++k)
-            if (c >= end[k - 1]) {
-                row = k;
-                base = end[k - 1];
-                rt = tris[k];
-            }
-        const int x = c - base, hx = x - TRI_CHUNKS * rt;
-        if (c < total) {
-            const char *src;
-            if (hx < 0) {
-                const int m = x / TRI_CHUNKS, part = x % TRI_CHUNKS;
-                const unsigned cd = L.row[row].code[m];
-                const int k = inc_corner(cd);
-                const int ch = part < 5 ? (k == 2 ? 5 : 0) + part
-                                        : (part < 10 ? (k == 0 ? 5 : 10) + part - 5 : 15 + 2 * k + part - 10);
-                src = (const char *)(A.trec + (int64_t)inc_elem(cd) * TREC) + 16 * ch;
-            } else {
-                const int h = look ? hx / 9 : hx / 7, part = hx - h * C.hc;
-                const unsigned cd = L.row[row].code[rt + h];
-                const int ch = part < 7 ? part : 2 * inc_corner(cd) + part;
-                src = (const char *)(A.hrec + (int64_t)inc_elem(cd) * (look ? HREC_LOOK : HREC)) + 16 * ch;
-            }
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                             (__attribute__((address_space(3))) void *)(L.rec + b), 16, 0, 0);
+    for (int k = 0; k < 2; ++k) {
+        const int m = t + RG * k;
+        if (m >= n) continue;
+        const unsigned type = inc_type(code[k]), kc = inc_corner(code[k]), e = inc_elem(code[k]);
+        const bool tri = type == INC_TRI;
+        const int at = tri ? c0 + TRI_CHUNKS * m : c0 + TRI_CHUNKS * ntri + hc * (m - ntri);
+        const int end = at + (tri ? TRI_CHUNKS : hc);
+        const bool in = type != INC_CONTACT && end <= REC_CHUNKS;
+        W.loc[m] = rec_loc(at, code[k], in);
+        if (!in) continue;
+        stop = end;
+        const unsigned r = tri ? (TREC / 2) * e : 0x80000000u | (unsigned)hstride * e;
+        const unsigned b0 = tri && kc == 2 ? r + 5 : r, b1 = tri && kc != 0 ? r + 10 : r + 5;
+        unsigned *const o = source + at;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) o[q] = b0 + q;
+        o[5] = b1;
+        o[6] = b1 + 1;
+        if (tri) {
+#pragma unroll
+            for (int q = 2; q < 5; ++q) o[5 + q] = b1 + q;
+            o[10] = r + 15 + 2 * kc;
+            o[11] = r + 16 + 2 * kc;
+        } else if (look) {
+            o[7] = r + 7 + 2 * kc;
+            o[8] = r + 8 + 2 * kc;
         }
     }
+    if (total > REC_CHUNKS) {   // the last incidence that fits ends them
+#pragma unroll
+        for (int d = 1; d < WAVE; d *= 2) stop = max(stop, __shfl_xor(stop, d, WAVE));
+        total = __builtin_amdgcn_readfirstlane(stop);
+    }
+    __syncthreads();
+    unsigned src[REC_CHUNKS / WAVE];
+#pragma unroll
+    for (int u = 0; u < REC_CHUNKS / WAVE; ++u) src[u] = source[WAVE * u + lane];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < REC_CHUNKS / WAVE; ++u)
+        if (WAVE * u + lane < total) {
+            const char *rec = (int)src[u] < 0 ? (const char *)A.hrec : (const char *)A.trec;
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)(rec + 16 * (uint64_t)(src[u] & 0x7fffffffu)),
+                (__attribute__((address_space(3))) void *)(L.rec + WAVE * u), 16, 0, 0);
+        }
     // what the lane's next slot needs besides the records, in flight with them
-    int col = i, wd = 0, off = 0;
-    bool colpin = false;
+    // (their values are used after the wait only: no conversion here)
+    int col = i, off = 0;
+    uint8_t cnt = 0, cpin = 0;
     d3 vc = vi;
     auto slot_loads = [&](int s, int c) {
         col = c;
         if (s >= len || c == i) return;
         // the diagonal, when left out, precedes the columns above it
         const int ss = si * WAVE + (keep || c < i ? s : s - 1);
-        wd = slot_width((int)A.slot_cnt[ss]);
+        cnt = A.slot_cnt[ss];
         off = A.slot_off[ss];
-        colpin = A.pinned[c] != 0;
+        cpin = A.pinned[c];
         vc = ld3(A.v, c);
     };
     slot_loads(t, cols[0]);
-    const double mass = i < A.nv ? A.mass[i] : 0.0;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     double red[9];   // K v (3), diagonal of sum_j K_ij (3), its symmetrised off-diagonal entries (3)
@@ -1562,13 +1581,20 @@ __global__ void __launch_bounds__(64, 3) k_row_values(AsmArgs A) {
             dslot = s;
             continue;
         }
+        const bool colpin = cpin != 0;
+        const int wd = slot_width((int)cnt);
         double acc[9];
 #pragma unroll
         for (int q = 0; q < 9; ++q) acc[q] = 0.0;
-        const int qe = W.start[s + 1];
-        for (int q = W.start[s]; q < qe; ++q) {
-            const int key = pr[q], m = key >> 2;
-            add_stiffness_lds(L, A, C, W.code[m], m, key & 3, acc);
+        const int q0 = W.start[s], qe = W.start[s + 1];
+        int key = pr[q0];
+        unsigned w = W.loc[key >> 2];
+        for (int q = q0; q < qe; ++q) {   // the next pair's place is read a pair ahead
+            const int kn = pr[min(q + 1, qe - 1)];
+            const unsigned wn = W.loc[kn >> 2];
+            add_stiffness_lds(L, A, w, inc + (key >> 2), key & 3, acc);
+            key = kn;
+            w = wn;
         }
         npin += colpin ? 1 : 0;
         const d3 dvv = vc - vi;
@@ -1593,7 +1619,7 @@ __global__ void __launch_bounds__(64, 3) k_row_values(AsmArgs A) {
         BlockIO<TB>::store((TB *)A.jval + 9 * seg, wd, pos, blk);
         if (A.jval_hi) BlockIO<double>::store(A.jval_hi + 9 * seg, wd, pos, blk);
     }
-    for (int m = t; m < n; m += RG) add_force_lds(L, A, C, W.code[m], m, f);
+    for (int m = t; m < n; m += RG) add_force_lds(L, A, W.loc[m], inc + m, f);
     // every lane of the row gets the totals
 #pragma unroll
     for (int q = 0; q < 9; ++q) red[q] = row_sum(red[q]);
@@ -1627,7 +1653,7 @@ __global__ void __launch_bounds__(64, 3) k_row_values(AsmArgs A) {
                 if (!A.pinned[W.cols[s]]) continue;
                 for (int q = W.start[s]; q < W.start[s + 1]; ++q) {
                     const int m = pr[q] >> 2;
-                    add_stiffness_lds(L, A, C, W.code[m], m, pr[q] & 3, own);
+                    add_stiffness_lds(L, A, W.loc[m], inc + m, pr[q] & 3, own);
                 }
             }
 #pragma unroll
