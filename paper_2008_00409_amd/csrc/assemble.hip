@@ -522,11 +522,16 @@ __device__ __forceinline__ void tri_block(const double F[3][2], const double Sp[
 
 __global__ void __launch_bounds__(EVAL_THREADS) k_tri_eval(int nt, const int *tri, const double *Bm, const double *A0,
                                                            const double *x, const double *v, DevParams P,
-                                                           double *rec, int *status, int *wide_count) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {   // the row-limit bits and wide rows describe this assembly only
+                                                           double *rec, int *status, int *wide_count,
+                                                           int nslices, unsigned long long *f16_max) {
+    // the row-limit bits, the wide rows (unless the pattern is the mesh's as
+    // laid out before) and the largest magnitudes describe this assembly only
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         *status &= ~(ST_INC_OVERFLOW | ST_COL_OVERFLOW);
-        *wide_count = 0;
+        if (wide_count) *wide_count = 0;
     }
+    if (f16_max)
+        for (int k = blockIdx.x * EVAL_THREADS + threadIdx.x; k < nslices; k += gridDim.x * EVAL_THREADS) f16_max[k] = 0ull;
     __shared__ double lds[WAVE * 31];
     const int e0 = blockIdx.x * EVAL_THREADS, ne = min(WAVE, nt - e0), e = e0 + min((int)threadIdx.x, ne - 1);
     TriShape sh;
@@ -1029,7 +1034,7 @@ __global__ void __launch_bounds__(64) k_row_pattern_wide(AsmArgs A) {
 // slice_psize, the padded block count of each slice).
 __global__ void __launch_bounds__(64) k_slice_layout(int nslices, const int *slice_row0, const int *rowlen,
                                                      int *lane_row, int *row_lane, uint8_t *slot_cnt,
-                                                     int *slot_off, int *slice_psize, unsigned long long *f16_max) {
+                                                     int *slot_off, int *slice_psize) {
     const int s = blockIdx.x;
     if (s >= nslices) return;
     const int t = threadIdx.x;
@@ -1051,7 +1056,6 @@ __global__ void __launch_bounds__(64) k_slice_layout(int nslices, const int *sli
     slot_off[s * WAVE + t] = wave_excl_scan(slot_width(c));
     const int padded = wave_sum_int(slot_width(c));
     if (t == 0) slice_psize[s] = padded;
-    if (t == 0 && f16_max) f16_max[s] = 0ull;
 }
 
 // A row that overflowed the per-row limits has length 1 (set by the pattern
@@ -1853,6 +1857,88 @@ pc_status check_contacts(Ctx *ctx, int nc, int *bad, hipStream_t s) {
     return PC_OK;
 }
 
+// Buffers of the pattern pass.
+static pc_status pattern_buffers(Ctx *ctx) {
+    const int nv = ctx->nv;
+    pc_status st;
+    if (!ctx->row_state) {
+        if ((st = dev_alloc(ctx, (void **)&ctx->rowlen_s, sizeof(int) * (size_t)nv))) return st;
+        if ((st = dev_alloc(ctx, (void **)&ctx->row_state, (size_t)nv))) return st;
+        if ((st = dev_alloc(ctx, (void **)&ctx->wide_rows, sizeof(int) * (size_t)nv))) return st;
+        if ((st = dev_alloc(ctx, (void **)&ctx->row_npairs, (size_t)nv))) return st;
+    }
+    // per-row columns and pair lists between the two passes: 3 per incidence (+1 column per row)
+    if (ctx->pair_incs < ctx->ninc) {
+        dev_free(ctx, ctx->cols_tmp);
+        dev_free(ctx, ctx->pairs_tmp);
+        dev_free(ctx, ctx->starts_tmp);
+        ctx->cols_tmp = nullptr;
+        ctx->pairs_tmp = ctx->starts_tmp = nullptr;
+        ctx->pair_incs = 0;
+        ctx->pattern_held = false;
+        if ((st = dev_alloc(ctx, (void **)&ctx->cols_tmp, sizeof(int) * (3 * (size_t)ctx->ninc + nv)))) return st;
+        if ((st = dev_alloc(ctx, (void **)&ctx->pairs_tmp, 4 * (size_t)ctx->ninc))) return st;
+        if ((st = dev_alloc(ctx, (void **)&ctx->starts_tmp, 3 * (size_t)ctx->ninc + nv))) return st;
+        ctx->pair_incs = ctx->ninc;
+    }
+    return PC_OK;
+}
+
+static AsmArgs pattern_args(Ctx *ctx) {
+    AsmArgs a = {};
+    const int nc = ctx->nc;
+    a.nv = ctx->nv; a.nt = ctx->nt; a.nh = ctx->nh;
+    a.tri = ctx->tri; a.hinge = ctx->hinge; a.inc_ptr = nc > 0 ? ctx->inc_ptr : ctx->mesh_ptr; a.inc = nc > 0 ? ctx->inc : ctx->mesh_inc;
+    a.nc = nc; a.cverts = ctx->cverts; a.cw = ctx->cw; a.cn = ctx->cn;
+    a.Bm = ctx->Bm; a.A0 = ctx->A0; a.mass = ctx->mass;
+    a.trec = ctx->trec; a.hrec = ctx->hrec; a.crec = ctx->crec;
+    a.pinned = ctx->pinned; a.prm = ctx->prm;
+    a.rowlen = ctx->rowlen; a.rowlen_s = ctx->rowlen_s; a.rowptr = ctx->rowptr; a.colidx = ctx->colidx; a.jcol = ctx->jcol; a.jdel = ctx->jdel;
+    a.row_lane = ctx->row_lane; a.lane_row = ctx->lane_row; a.slot_cnt = ctx->slot_cnt; a.slot_off = ctx->slot_off; a.jval = ctx->jval;
+    a.row_slice = ctx->row_slice; a.slice_row0 = ctx->slice_row0; a.slice_vbase = ctx->slice_vbase;
+    a.row_state = ctx->row_state; a.wide_rows = ctx->wide_rows; a.wide_count = (int *)ctx->counter + 1;
+    a.nslices = ctx->nslices;
+    a.cols_tmp = ctx->cols_tmp; a.pairs_tmp = ctx->pairs_tmp; a.starts_tmp = ctx->starts_tmp; a.row_npairs = ctx->row_npairs;
+    a.status = ctx->status;
+    return a;
+}
+
+// four rows per workgroup; a multiple of 8 workgroups for the XCD mapping
+static int row_groups(int nv) { return (((nv + RG_ROWS - 1) / RG_ROWS + 7) / 8) * 8; }
+constexpr int WIDE_BLOCKS = 256;   // workgroups of the wide-row passes (grid-stride over the list)
+// else no row has more incidences than the row groups take
+static bool wide_rows(const Ctx *ctx) { return ctx->nc > 0 || ctx->mesh_longest > RG_NI; }
+
+// Row patterns (sorted incidences, columns, pairs, row lengths and pointers) and
+// the solver layout.
+static pc_status pattern_pass(Ctx *ctx, const AsmArgs &a, hipStream_t s) {
+    pc_status st;
+    hipLaunchKernelGGL(k_row_pattern, dim3(row_groups(ctx->nv)), dim3(64), 0, s, a);
+    if (wide_rows(ctx)) hipLaunchKernelGGL(k_row_pattern_wide, dim3(WIDE_BLOCKS), dim3(64), 0, s, a);
+    if ((st = scan_excl(ctx, ctx->rowlen, ctx->rowptr, ctx->nv, s))) return st;
+    hipLaunchKernelGGL(k_slice_layout, dim3(ctx->nslices), dim3(64), 0, s, ctx->nslices, ctx->slice_row0, ctx->rowlen_s,
+                       ctx->lane_row, ctx->row_lane, ctx->slot_cnt, ctx->slot_off, ctx->slice_psize);
+    return scan_excl(ctx, ctx->slice_psize, ctx->slice_vbase, ctx->nslices, s);
+}
+
+// Lays out the pattern of the mesh without contacts for the assemblies to come
+// (1.65M triangles: 0.43 ms, which each of them spent).  Not held when a row
+// is past the limits: those bits are reported by every assembly.
+pc_status mesh_pattern(Ctx *ctx, bool create) {
+    pc_status st;
+    if ((st = pattern_buffers(ctx))) return st;
+    hipStream_t s = nullptr;
+    AsmArgs a = pattern_args(ctx);
+    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, a.wide_count, 0, (int64_t)1);
+    if ((st = pattern_pass(ctx, a, s))) return st;
+    PC_HIP(hipGetLastError());
+    PC_HIP(hipMemcpyAsync(ctx->status_host, ctx->status, sizeof(int), hipMemcpyDeviceToHost, s));
+    PC_HIP(hipStreamSynchronize(s));
+    if (create) ctx->mesh_fits = (*ctx->status_host & (ST_INC_OVERFLOW | ST_COL_OVERFLOW)) == 0;
+    ctx->pattern_held = ctx->mesh_fits;
+    return PC_OK;
+}
+
 pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtype, double *b,
                        double *diag_out, hipStream_t s) {
     const int nv = ctx->nv, nt = ctx->nt, nh = ctx->nh;
@@ -1903,30 +1989,26 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
         if ((st = dev_alloc(ctx, (void **)&ctx->f16_scale, sizeof(double) * 2 * (size_t)ctx->nslices))) return st;
         ctx->f16_cap = ctx->nslices;
     }
-    if (!ctx->row_state) {
-        if ((st = dev_alloc(ctx, (void **)&ctx->rowlen_s, sizeof(int) * (size_t)nv))) return st;
-        if ((st = dev_alloc(ctx, (void **)&ctx->row_state, (size_t)nv))) return st;
-        if ((st = dev_alloc(ctx, (void **)&ctx->wide_rows, sizeof(int) * (size_t)nv))) return st;
-        if ((st = dev_alloc(ctx, (void **)&ctx->row_npairs, (size_t)nv))) return st;
+    if ((st = pattern_buffers(ctx))) return st;
+    // The pattern without contacts is the mesh's: it is laid out when the mesh
+    // or its instances are set, and again here after an assembly with contacts
+    // or a change of the schedule.  A captured assembly always lays it out,
+    // since what ran before its replays is not known here; after the capture of
+    // one with contacts every assembly does.
+    bool capturing = false;
+    if (s) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        PC_HIP(hipStreamIsCapturing(s, &cs));
+        capturing = cs == hipStreamCaptureStatusActive;
     }
-    // per-row columns and pair lists between the two passes: 3 per incidence (+1 column per row)
-    if (ctx->pair_incs < ctx->ninc) {
-        dev_free(ctx, ctx->cols_tmp);
-        dev_free(ctx, ctx->pairs_tmp);
-        dev_free(ctx, ctx->starts_tmp);
-        ctx->cols_tmp = nullptr;
-        ctx->pairs_tmp = ctx->starts_tmp = nullptr;
-        ctx->pair_incs = 0;
-        if ((st = dev_alloc(ctx, (void **)&ctx->cols_tmp, sizeof(int) * (3 * (size_t)ctx->ninc + nv)))) return st;
-        if ((st = dev_alloc(ctx, (void **)&ctx->pairs_tmp, 4 * (size_t)ctx->ninc))) return st;
-        if ((st = dev_alloc(ctx, (void **)&ctx->starts_tmp, 3 * (size_t)ctx->ninc + nv))) return st;
-        ctx->pair_incs = ctx->ninc;
-    }
+    if (capturing && nc > 0) ctx->mesh_fits = false;
+    const bool held = nc == 0 && ctx->pattern_held && !capturing;
     const int slot_all = ctx->prof.begin(PK_ASM_ALL, s);
     // 1. elements, each evaluated once
     int slot = ctx->prof.begin(PK_ELEMENTS, s);
     hipLaunchKernelGGL(k_tri_eval, dim3((nt + EVAL_THREADS - 1) / EVAL_THREADS), dim3(EVAL_THREADS), 0, s, nt, ctx->tri, ctx->Bm, ctx->A0, x, v,
-                       ctx->prm, ctx->trec, ctx->status, (int *)ctx->counter + 1);
+                       ctx->prm, ctx->trec, ctx->status, held ? nullptr : (int *)ctx->counter + 1, ctx->nslices,
+                       dtype == PC_F16 ? (unsigned long long *)ctx->f16_part : nullptr);
     if (nh > 0)
         hipLaunchKernelGGL(k_hinge_eval, dim3((nh + EVAL_THREADS - 1) / EVAL_THREADS), dim3(EVAL_THREADS), 0, s, nh, ctx->hinge, ctx->hcoef,
                            ctx->htbar, x, v, ctx->prm, ctx->hrec);
@@ -1944,20 +2026,9 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
         hipLaunchKernelGGL(k_contact_inc_fill, dim3(nb), dim3(TB), 0, s, nc, ctx->cverts, ctx->inc_cnt, ctx->mesh_ptr,
                            ctx->inc_ptr, ctx->inc);
     }
-    // 3. row patterns: sorted incidences, row lengths, pointers
-    AsmArgs a;
-    a.nv = nv; a.nt = nt; a.nh = nh;
-    a.tri = ctx->tri; a.hinge = ctx->hinge; a.inc_ptr = nc > 0 ? ctx->inc_ptr : ctx->mesh_ptr; a.inc = nc > 0 ? ctx->inc : ctx->mesh_inc;
-    a.nc = nc; a.cverts = ctx->cverts; a.cw = ctx->cw; a.cn = ctx->cn;
-    a.Bm = ctx->Bm; a.A0 = ctx->A0; a.mass = ctx->mass;
-    a.trec = ctx->trec; a.hrec = ctx->hrec; a.crec = ctx->crec;
-    a.pinned = ctx->pinned; a.v = v; a.prm = ctx->prm;
-    a.rowlen = ctx->rowlen; a.rowlen_s = ctx->rowlen_s; a.rowptr = ctx->rowptr; a.colidx = ctx->colidx; a.jcol = ctx->jcol; a.jdel = ctx->jdel;
-    a.row_lane = ctx->row_lane; a.lane_row = ctx->lane_row; a.slot_cnt = ctx->slot_cnt; a.slot_off = ctx->slot_off; a.jval = ctx->jval;
-    a.row_slice = ctx->row_slice; a.slice_row0 = ctx->slice_row0; a.slice_vbase = ctx->slice_vbase;
-    a.row_state = ctx->row_state; a.wide_rows = ctx->wide_rows; a.wide_count = (int *)ctx->counter + 1;
-    a.nslices = ctx->nslices;
-    a.cols_tmp = ctx->cols_tmp; a.pairs_tmp = ctx->pairs_tmp; a.starts_tmp = ctx->starts_tmp; a.row_npairs = ctx->row_npairs;
+    // 3. row patterns and solver layout, with contacts or after them
+    AsmArgs a = pattern_args(ctx);
+    a.v = v;
     a.f16_max = dtype == PC_F16 ? (unsigned long long *)ctx->f16_part : nullptr;
     a.jval_hi = dtype != PC_F64 ? ctx->jval_hi : nullptr;
     if (dtype == PC_F16) {
@@ -1966,19 +2037,16 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
         a.jval_hi = nullptr;
     }
     a.b = b; a.diag = diag_out ? diag_out : ctx->diag; a.dinv = ctx->dinv; a.binv = ctx->binv; a.status = ctx->status;
-    // four rows per workgroup; a multiple of 8 workgroups for the XCD mapping
-    const int ng = (((nv + RG_ROWS - 1) / RG_ROWS + 7) / 8) * 8;
-    const int nwide = 256;   // workgroups of the wide-row passes (grid-stride over the list)
-    const bool wide = nc > 0 || ctx->mesh_longest > RG_NI;   // else no row has more incidences than the row groups take
+    const int ng = row_groups(nv);
+    const int nwide = WIDE_BLOCKS;
+    const bool wide = wide_rows(ctx);
     slot = ctx->prof.begin(PK_ROW_PAT, s);
-    hipLaunchKernelGGL(k_row_pattern, dim3(ng), dim3(64), 0, s, a);
-    if (wide) hipLaunchKernelGGL(k_row_pattern_wide, dim3(nwide), dim3(64), 0, s, a);
+    if (!held) {
+        ctx->pattern_held = false;
+        if ((st = pattern_pass(ctx, a, s))) return st;
+        ctx->pattern_held = nc == 0 && ctx->mesh_fits && !capturing;
+    }
     ctx->prof.end(slot, s);
-    if ((st = scan_excl(ctx, ctx->rowlen, ctx->rowptr, nv, s))) return st;
-    // 4. solver layout
-    hipLaunchKernelGGL(k_slice_layout, dim3(ctx->nslices), dim3(64), 0, s, ctx->nslices, ctx->slice_row0,
-                       ctx->rowlen_s, ctx->lane_row, ctx->row_lane, ctx->slot_cnt, ctx->slot_off, ctx->slice_psize, a.f16_max);
-    if ((st = scan_excl(ctx, ctx->slice_psize, ctx->slice_vbase, ctx->nslices, s))) return st;
     // 5. values
     slot = ctx->prof.begin(PK_ROW_ASM, s);
     switch (dtype) {

@@ -726,6 +726,7 @@ static PreArgs pre_args(Ctx *ctx) {
 // Slices (up to 64 rows, never across instances) and work items from the
 // instance row ranges and the current spb / rpb.
 pc_status build_schedule(Ctx *ctx) {
+    ctx->pattern_held = false;   // its solver layout depends on the slices
     const int ninst = (int)ctx->inst_row0_h.size() - 1;
     std::vector<int> slice_row0, row_slice(ctx->nv);
     std::vector<int4> sitems, vitems;
