@@ -1351,9 +1351,9 @@ __device__ __forceinline__ void row_values_g(RowGroupLDS<NI> &L, const AsmArgs &
 // for their magnitudes too.  The lanes of the incidences list the chunks'
 // sources: with each chunk's row, incidence and part found from its number
 // there were 1,680 vector instructions a wavefront; and every value that the
-// slots need is requested before the one wait for the records: 0.85 ms.
-// Workgroups that stay and fetch the next group's
-// lists ahead measured 1.5 to 1.85 ms: their waits include the stores.
+// slots need is requested before the one wait for the records: 0.85 ms, or
+// 0.90 where the lists were laid out with the mesh and are not fresh in the
+// caches.  Workgroups that stay and fetch the next group's lists ahead measured 1.5 to 1.85 ms: their waits include the stores.
 constexpr int REC_CHUNKS = 704;   // 16-byte chunks of records a group keeps in LDS; the incidences beyond are read directly
 constexpr int TRI_CHUNKS = 12;    // of a triangle: the two blocks and the force of the row's corner
 struct RowPairsLDS {

@@ -193,8 +193,15 @@ struct Sched {
     const int *inst_sitem0, *inst_vitem0;
 };
 
-__device__ __forceinline__ int item_of_block(int n) {
-    const int b = xcd_remap(blockIdx.x, gridDim.x);
+// back: each XCD takes its items from the last to the first.  The kernels of
+// the iterations alternate (SpMV and direction of one parity forward, update
+// back, and the reverse for the other), so that each begins with what the one
+// before it, or the last SpMV, left in the caches: 96 iterations at 828k rows
+// in FP16 7.05 -> 6.95 ms (the matrix and vectors just fit the 256 MB cache),
+// FP32 12.16 -> 11.48, FP64 19.07 -> 18.45 (435 and 800 MB).
+__device__ __forceinline__ int item_of_block(int n, bool back = false) {
+    const int per = (int)gridDim.x >> 3, k = (int)blockIdx.x >> 3;   // the grid is a multiple of 8
+    const int b = ((int)blockIdx.x & 7) * per + (back ? per - 1 - k : k);
     return b < n ? b : -1;
 }
 
@@ -252,9 +259,9 @@ __device__ __forceinline__ void block_times(const float b6[6], const double rk[3
 template <typename TB, bool NARROW, typename TQ>
 __global__ void __launch_bounds__(1024) k_pcg_spmv(SpmvArgs M, Sched S, const float *p, TQ *q,
                                                   const PcgState *st, double *partials, const int2 *win,
-                                                  int win_cap) {
+                                                  int win_cap, bool back) {
     extern __shared__ float4 pwin[];
-    const int it = item_of_block(S.n_sitems);
+    const int it = item_of_block(S.n_sitems, back);
     if (it < 0) return;
     const int4 I = S.sitem[it];
     if (st[I.x].done) return;

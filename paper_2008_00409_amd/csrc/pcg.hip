@@ -233,7 +233,7 @@ struct UpdRows {
 template <typename TV>
 __global__ void __launch_bounds__(VT) k_pcg_update(Sched S, int par, TV *r, const TV *q, PreArgs P, PcgState *st,
                                                     const double *part_s, double *part_u) {
-    const int it = item_of_block(S.n_vitems);
+    const int it = item_of_block(S.n_vitems, par == 0);
     if (it < 0) return;
     const int4 I = S.vitem[it];
     if (st[I.x].done) return;
@@ -327,7 +327,7 @@ struct DirRow {
 template <typename TV>
 __global__ void __launch_bounds__(VT) k_pcg_dir(Sched S, int par, TV *x, const TV *r, float *p, PreArgs P,
                                                  PcgState *st, const double *part_u) {
-    const int it = item_of_block(S.n_vitems);
+    const int it = item_of_block(S.n_vitems, par != 0);
     if (it < 0) return;
     const int4 I = S.vitem[it];
     const bool first = it == S.inst_vitem0[I.x] && threadIdx.x == 0;
@@ -894,15 +894,15 @@ static pc_status ensure_windows(Ctx *ctx, hipStream_t s) {
 
 // SpMV of p into q (stored as TQ) with partials of p.q.
 template <typename TB, typename TQ>
-static void launch_spmv(Ctx *ctx, const SpmvArgs &M, const Sched &S, const Grids &g, hipStream_t s, TQ *q) {
+static void launch_spmv(Ctx *ctx, const SpmvArgs &M, const Sched &S, const Grids &g, hipStream_t s, TQ *q, bool back) {
     if (ctx->narrow && M.jdel)
         hipLaunchKernelGGL((k_pcg_spmv<TB, true, TQ>), dim3(g.sblocks), dim3(g.sthreads),
                            sizeof(float4) * (size_t)ctx->win_cap, s, M, S, ctx->p, q, ctx->st, ctx->partials,
-                           ctx->sitem_win, ctx->win_cap);
+                           ctx->sitem_win, ctx->win_cap, back);
     else
         hipLaunchKernelGGL((k_pcg_spmv<TB, false, TQ>), dim3(g.sblocks), dim3(g.sthreads),
                            sizeof(float4) * (size_t)ctx->win_cap, s, M, S, ctx->p, q, ctx->st, ctx->partials,
-                           ctx->sitem_win, ctx->win_cap);
+                           ctx->sitem_win, ctx->win_cap, back);
 }
 
 // One CG iteration of parity par (the parity selects the rz slot, see
@@ -915,7 +915,7 @@ template <typename TB, typename TV>
 static void launch_iter_v(Ctx *ctx, const SpmvArgs &M, const Sched &S, const Grids &g, hipStream_t s, int par,
                           TV *x, TV *r, TV *q) {
     int slot = ctx->prof.begin(PK_SPMV, s);
-    launch_spmv<TB, TV>(ctx, M, S, g, s, q);
+    launch_spmv<TB, TV>(ctx, M, S, g, s, q, par != 0);
     ctx->prof.end(slot, s);
     slot = ctx->prof.begin(PK_UPDATE, s);
     hipLaunchKernelGGL(k_pcg_update<TV>, dim3(g.vblocks), dim3(VT), 0, s, S, par, r, (const TV *)q, pre_args(ctx),
@@ -940,7 +940,7 @@ static void launch_iter(Ctx *ctx, const SpmvArgs &M, const Sched &S, const Grids
 template <typename TB>
 static void launch_iter_cgcg(Ctx *ctx, const SpmvArgs &M, const Sched &S, const Grids &g, hipStream_t s) {
     int slot = ctx->prof.begin(PK_SPMV, s);
-    launch_spmv<TB, double>(ctx, M, S, g, s, ctx->q);
+    launch_spmv<TB, double>(ctx, M, S, g, s, ctx->q, false);
     ctx->prof.end(slot, s);
     hipLaunchKernelGGL(k_fin_cgcg, dim3(ctx->ninst), dim3(1024), 0, s, S, ctx->partials, ctx->partials_u, ctx->st);
     slot = ctx->prof.begin(PK_UPDATE, s);
