@@ -209,7 +209,7 @@ struct Ctx {
     uint8_t *pinned = nullptr;
     int *status = nullptr;    // device error bits
 
-    // per-step pattern
+    // pattern: the mesh's while pattern_held, else that of the last assembly
     int *inc_cnt = nullptr;   // nv (kept at zero between uses)
     int *inc_ptr = nullptr;   // nv + 1
     int *mesh_ptr = nullptr, *mesh_inc = nullptr;   // the mesh's incidences: nv + 1 starts, sorted codes
