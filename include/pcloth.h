@@ -193,8 +193,10 @@ pc_status pc_sizes(const pc_ctx *ctx, int64_t out[4]);
  * (coefficient, rest angle) pairs to host memory (either pointer may be NULL). */
 pc_status pc_get_hinges(pc_ctx *ctx, int32_t *hinges_host, double *coef_host);
 
-/* Assemble A and b at state (x, v) (paper Sec. 3.2.2 and Eq. 3): rebuild the
- * block pattern from the element list, sum the element blocks of each block
+/* Assemble A and b at state (x, v) (paper Sec. 3.2.2 and Eq. 3): derive the
+ * block pattern from the element list (with contacts; without, it is the
+ * mesh's, laid out by pc_create and pc_set_instances), sum the element blocks of
+ * each block
  * (deterministic order: triangles then hinges, by index), eliminate pinned
  * vertices, and form b and the Jacobi diagonal.  Block values are stored as
  * `dtype`; diag_out (optional, device nv*3 doubles) receives diag(A).
