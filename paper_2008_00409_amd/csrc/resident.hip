@@ -26,7 +26,7 @@
 // items t, t + 1024, ...; the update's thread adds row t and row t + 1024 of
 // its item, 16 wavefronts in order make a vector item.  The pair of 64-row
 // slices (w, w + 16) of a 32-slice item is therefore the smallest unit of
-// work; a workgroup owns 1, 2, 4 or 8 consecutive pairs of one item.
+// work; a workgroup owns 2, 4 or 8 consecutive pairs of one item.
 //
 // Memory shared between workgroups during the launch (the partial sums and
 // the halo rows' z) goes through relaxed agent-scope atomics, which bypass
@@ -909,10 +909,13 @@ __global__ void k_res_clear(u64 *slots, size_t n) {
 }
 
 // ---------------------------------------------------------------- host side
-// Teams.  With P = 1, 2 or 4 pairs per workgroup (one slice per wavefront,
-// 2 P wavefronts) or 8 (two slices per wavefront of 8), the smallest P whose
-// teams fit the compute units at once is taken: one workgroup per unit, on as
-// many units as there is work for.  Where 8 do not fit, the instances go in
+// Teams.  With P = 2 or 4 pairs per workgroup (one slice per wavefront, 2 P
+// wavefronts) or 8 (two slices per wavefront of 8), the smallest P whose teams
+// fit the compute units at once is taken: one workgroup per unit.  P = 1 meets
+// with twice the workgroups (us per iteration, P = 1 / 2, FP64 and FP32 blocks:
+// 1k rows 6.1 / 6.2 and 5.8 / 5.8, 3k 8.7 / 7.6 and 8.1 / 6.9, 7k 9.4 / 8.2 and
+// 8.7 / 7.5, 33k 11.7 / 9.6 and 11.1 / 9.0); with P = 4 fewer FP64 blocks stay in
+// registers (3k 10.6, 33k 12.7), while FP32 gains at most 1.9 us (62k 10.9 / 9.0).  Where 8 do not fit, the instances go in
 // several rounds, each to the end of the sweep.  An instance of more than
 // 1,024 rows a unit does not fit any round: the three-launch iteration runs.
 // (Whole items per workgroup, 2,048 rows, kept 4 of 12 blocks a row in
@@ -944,7 +947,7 @@ pc_status resident_plan(Ctx *ctx) {
     auto pairs_of = [](const ResInst &I) { return 16 * (I.nitems - 1) + std::min(16, I.nsl - 32 * (I.nitems - 1)); };
     auto team_of = [&](const ResInst &I, int per) { return (pairs_of(I) + per - 1) / per; };
     int per = 8;
-    for (int cand : {1, 2, 4, 8}) {
+    for (int cand : {2, 4, 8}) {
         int64_t sum = 0;
         for (const ResInst &I : inst) sum += team_of(I, cand);
         if (sum <= ncu) {
