@@ -2001,6 +2001,7 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
         PC_HIP(hipStreamIsCapturing(s, &cs));
         capturing = cs == hipStreamCaptureStatusActive;
     }
+    ctx->asm_captured = ctx->asm_captured || capturing;
     if (capturing && nc > 0) ctx->mesh_fits = false;
     const bool held = nc == 0 && ctx->pattern_held && !capturing;
     const int slot_all = ctx->prof.begin(PK_ASM_ALL, s);

@@ -216,6 +216,7 @@ struct Ctx {
     int mesh_longest = 0;     // largest number of them at a vertex
     bool mesh_fits = false;      // no row of the mesh is past the row limits, and no captured assembly has contacts
     bool pattern_held = false;   // the pattern arrays and the solver layout are those of the mesh without contacts
+    bool asm_captured = false;   // an assembly has been captured: its replays may change the pattern at any time
     int *inc = nullptr;       // ninc
     int *rowlen = nullptr;    // nv
     int *rowptr = nullptr;    // nv + 1

@@ -845,11 +845,14 @@ static Grids grids(Ctx *ctx) {
 // items with wider windows gather from global memory.  They depend on the
 // pattern alone, which without contacts is the mesh's: the kernels run (and
 // the host waits) after the first such assembly, a schedule change, and every
-// assembly with contacts.
+// assembly with contacts.  Replays of a captured assembly, which are not seen
+// here, can leave another pattern in the buffers than that of the last call:
+// once one has been captured, they run before every solve.
 #ifndef PC_WIN_MAX
 #define PC_WIN_MAX 4096
 #endif
 static pc_status ensure_windows(Ctx *ctx, hipStream_t s) {
+    if (ctx->asm_captured) ctx->win_valid = ctx->win_known = false;
     if (ctx->win_valid) return PC_OK;
     if (!ctx->win_known) {
         if (ctx->win_items < ctx->n_sitems) {
