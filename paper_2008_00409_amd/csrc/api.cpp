@@ -106,6 +106,15 @@ static bool params_ok(const pc_params *p, std::string &err) {
     return true;
 }
 
+// Why so many triangles and hinges are refused; nullptr where they are taken.
+static const char *too_many_elements(int64_t nt, int64_t nh) {
+    if (nt >= MAX_ELEMS || nh >= MAX_ELEMS) return "more than 2^28 triangles or hinges";
+    // 32-bit counts of element values (36 per triangle, up to 25 per hinge)
+    if (36 * nt >= ((int64_t)1 << 31) || 25 * nh >= ((int64_t)1 << 31))
+        return "more than 59,652,323 triangles or 85,899,345 hinges";
+    return nullptr;
+}
+
 static void free_all(Ctx *c) {
     void *ptrs[] = {c->tri, c->Bm, c->A0, c->hinge, c->hcoef, c->htbar, c->mass, c->pinned, c->status,
                     c->inc_cnt, c->inc_ptr, c->inc, c->mesh_ptr, c->mesh_inc, c->rowlen, c->rowptr, c->colidx, c->jcol, c->lane_row,
@@ -148,6 +157,8 @@ pc_status pc_create(const pc_mesh *mesh, const pc_params *params, pc_ctx **out) 
             g_create_err = "triangle index out of range";
             return PC_ERR_MESH;
         }
+    // before anything is built from the elements: their counts index with 32 bits
+    if (const char *e = too_many_elements(nt, 0)) { g_create_err = e; return PC_ERR_ARG; }
     pc_ctx *h = new (std::nothrow) pc_ctx();
     if (!h) { g_create_err = "host allocation failed"; return PC_ERR_OOM; }
     Ctx *ctx = &h->c;
@@ -214,17 +225,12 @@ pc_status pc_create(const pc_mesh *mesh, const pc_params *params, pc_ctx **out) 
         ctx->ell = sum / (3.0 * nt);
     }
     if ((st = topo_build(ctx, mesh, s))) return fail(st);
-    if ((st = mesh_incidences(ctx, s))) return fail(st);
     const int nh = ctx->nh;
-    if (nt >= MAX_ELEMS || nh >= MAX_ELEMS) {
-        ctx->err = "more than 2^28 triangles or hinges";
+    if (const char *e = too_many_elements(nt, nh)) {
+        ctx->err = e;
         return fail(PC_ERR_ARG);
     }
-    // 32-bit counts of element values (36 per triangle, up to 25 per hinge)
-    if ((int64_t)36 * nt >= ((int64_t)1 << 31) || (int64_t)25 * nh >= ((int64_t)1 << 31)) {
-        ctx->err = "more than 59,652,323 triangles or 85,899,345 hinges";
-        return fail(PC_ERR_ARG);
-    }
+    if ((st = mesh_incidences(ctx, s))) return fail(st);
     ctx->ninc = 3 * (int64_t)nt + 4 * (int64_t)nh;
     // block capacity: diagonal + both directions of every triangle edge (6
     // per triangle, duplicates included) + both wing pairs of every hinge
