@@ -319,6 +319,10 @@ pc_status topo_build(Ctx *ctx, const pc_mesh *mesh, hipStream_t s) {
     return PC_OK;
 }
 
+// Incidences that a row group and the wide-row pass take (see "row groups").
+constexpr int RG = 16, RG_ROWS = 4, RG_NI = 32;
+constexpr int WIDE_NI = 512;
+
 // ---------------------------------------------------------------- incidences
 // Every corner of every element (3 per triangle, 4 per hinge, 4 per contact)
 // is bucketed at its vertex; codes as in pc_common.h.  The mesh's buckets are
@@ -361,15 +365,20 @@ __global__ void k_mesh_inc_fill(int nt, int nh, const int *tri, const int *hinge
     inc[ptr[v] + slot] = (int)code;
 }
 
-// Each bucket ascending (rank sort, 16 lanes a bucket) and the largest size.
+// Each bucket ascending (rank sort, 16 lanes a bucket: n^2 / 16 steps) and the
+// largest size.  A bucket past the wide-row pass's capacity is copied as it is:
+// every assembly refuses its row unread.
 __global__ void __launch_bounds__(256) k_mesh_inc_sort(int nv, const int *ptr, const int *in, int *out, int *longest) {
     const int i = blockIdx.x * 16 + threadIdx.x / 16, t = threadIdx.x % 16;
     if (i >= nv) return;
     const int p0 = ptr[i], n = ptr[i + 1] - p0;
     for (int m = t; m < n; m += 16) {
         const unsigned key = (unsigned)in[p0 + m];
-        int r = 0;
-        for (int q = 0; q < n; ++q) r += (unsigned)in[p0 + q] < key;
+        int r = m;
+        if (n <= WIDE_NI) {
+            r = 0;
+            for (int q = 0; q < n; ++q) r += (unsigned)in[p0 + q] < key;
+        }
         out[p0 + r] = (int)key;
     }
     if (t == 0 && n > *longest) atomicMax(longest, n);   // most buckets are as long as the longest: a load, no atomic
@@ -695,8 +704,6 @@ struct AsmArgs {
 // contacts, each by index), the vertices of each incidence's element, the
 // column candidates (the element neighbours of the row's vertex) and the
 // row's distinct columns.
-constexpr int RG = 16, RG_ROWS = 4, RG_NI = 32;
-constexpr int WIDE_NI = 512;
 // Which pass assembles a row: the row group pass, the wide-row pass, or
 // neither because the row exceeds the capacities (found by the row group
 // pass: more than MAX_COLS columns; by the wide-row pass: more than WIDE_NI
