@@ -195,8 +195,8 @@ pc_status pc_get_hinges(pc_ctx *ctx, int32_t *hinges_host, double *coef_host);
 
 /* Assemble A and b at state (x, v) (paper Sec. 3.2.2 and Eq. 3): derive the
  * block pattern from the element list (with contacts; without, it is the
- * mesh's, laid out by pc_create and pc_set_instances), sum the element blocks of
- * each block
+ * mesh's, laid out by the first such assembly and again after a change of
+ * contacts, instances or schedule), sum the element blocks of each block
  * (deterministic order: triangles then hinges, by index), eliminate pinned
  * vertices, and form b and the Jacobi diagonal.  Block values are stored as
  * `dtype`; diag_out (optional, device nv*3 doubles) receives diag(A).

@@ -271,7 +271,6 @@ pc_status pc_create(const pc_mesh *mesh, const pc_params *params, pc_ctx **out) 
         ctx->err = "initialisation failed";
         return fail(PC_ERR_HIP);
     }
-    if ((st = mesh_pattern(ctx, true))) return fail(st);
     *out = h;
     return PC_OK;
 }
@@ -470,8 +469,7 @@ pc_status pc_set_instances(pc_ctx *h, const int32_t *vertex_begin, int32_t ninst
         return PC_ERR_ARG;
     }
     ctx->inst_row0_h.assign(vertex_begin, vertex_begin + ninst + 1);
-    if ((cst = build_schedule(ctx))) return cst;
-    return ctx->nc == 0 ? mesh_pattern(ctx, false) : PC_OK;
+    return build_schedule(ctx);
 }
 
 pc_status pc_get_instance_info(pc_ctx *h, pc_solve_info *infos, int32_t n) {

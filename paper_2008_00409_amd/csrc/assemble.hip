@@ -533,11 +533,11 @@ __global__ void __launch_bounds__(EVAL_THREADS) k_tri_eval(int nt, const int *tr
                                                            const double *x, const double *v, DevParams P,
                                                            double *rec, int *status, int *wide_count,
                                                            int nslices, unsigned long long *f16_max) {
-    // the row-limit bits, the wide rows (unless the pattern is the mesh's as
-    // laid out before) and the largest magnitudes describe this assembly only
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    // the row-limit bits and the wide rows are the pattern's (wide_count: it is
+    // about to be laid out), the largest magnitudes this assembly's
+    if (wide_count && blockIdx.x == 0 && threadIdx.x == 0) {
         *status &= ~(ST_INC_OVERFLOW | ST_COL_OVERFLOW);
-        if (wide_count) *wide_count = 0;
+        *wide_count = 0;
     }
     if (f16_max)
         for (int k = blockIdx.x * EVAL_THREADS + threadIdx.x; k < nslices; k += gridDim.x * EVAL_THREADS) f16_max[k] = 0ull;
@@ -1928,24 +1928,6 @@ static pc_status pattern_pass(Ctx *ctx, const AsmArgs &a, hipStream_t s) {
     return scan_excl(ctx, ctx->slice_psize, ctx->slice_vbase, ctx->nslices, s);
 }
 
-// Lays out the pattern of the mesh without contacts for the assemblies to come
-// (1.65M triangles: 0.43 ms, which each of them spent).  Not held when a row
-// is past the limits: those bits are reported by every assembly.
-pc_status mesh_pattern(Ctx *ctx, bool create) {
-    pc_status st;
-    if ((st = pattern_buffers(ctx))) return st;
-    hipStream_t s = nullptr;
-    AsmArgs a = pattern_args(ctx);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, a.wide_count, 0, (int64_t)1);
-    if ((st = pattern_pass(ctx, a, s))) return st;
-    PC_HIP(hipGetLastError());
-    PC_HIP(hipMemcpyAsync(ctx->status_host, ctx->status, sizeof(int), hipMemcpyDeviceToHost, s));
-    PC_HIP(hipStreamSynchronize(s));
-    if (create) ctx->mesh_fits = (*ctx->status_host & (ST_INC_OVERFLOW | ST_COL_OVERFLOW)) == 0;
-    ctx->pattern_held = ctx->mesh_fits;
-    return PC_OK;
-}
-
 pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtype, double *b,
                        double *diag_out, hipStream_t s) {
     const int nv = ctx->nv, nt = ctx->nt, nh = ctx->nh;
@@ -1997,11 +1979,12 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
         ctx->f16_cap = ctx->nslices;
     }
     if ((st = pattern_buffers(ctx))) return st;
-    // The pattern without contacts is the mesh's: it is laid out when the mesh
-    // or its instances are set, and again here after an assembly with contacts
-    // or a change of the schedule.  A captured assembly always lays it out,
-    // since what ran before its replays is not known here; after the capture of
-    // one with contacts every assembly does.
+    // The pattern without contacts is the mesh's: the first such assembly lays it
+    // out (1.65M triangles: 0.43 ms), and so does the first after an assembly with
+    // contacts or a change of the schedule or the instances; the others hold it.
+    // The status word's row-limit bits are the pattern's and stay with it.  A
+    // captured assembly always lays it out, since what ran before its replays is
+    // not known here; after the capture of one with contacts every assembly does.
     bool capturing = false;
     if (s) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -2009,7 +1992,7 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
         capturing = cs == hipStreamCaptureStatusActive;
     }
     ctx->asm_captured = ctx->asm_captured || capturing;
-    if (capturing && nc > 0) ctx->mesh_fits = false;
+    if (capturing && nc > 0) ctx->never_hold = true;
     const bool held = nc == 0 && ctx->pattern_held && !capturing;
     const int slot_all = ctx->prof.begin(PK_ASM_ALL, s);
     // 1. elements, each evaluated once
@@ -2052,7 +2035,7 @@ pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtyp
     if (!held) {
         ctx->pattern_held = false;
         if ((st = pattern_pass(ctx, a, s))) return st;
-        ctx->pattern_held = nc == 0 && ctx->mesh_fits && !capturing;
+        ctx->pattern_held = nc == 0 && !ctx->never_hold && !capturing;
     }
     ctx->prof.end(slot, s);
     // 5. values

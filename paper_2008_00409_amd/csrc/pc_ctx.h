@@ -214,7 +214,7 @@ struct Ctx {
     int *inc_ptr = nullptr;   // nv + 1
     int *mesh_ptr = nullptr, *mesh_inc = nullptr;   // the mesh's incidences: nv + 1 starts, sorted codes
     int mesh_longest = 0;     // largest number of them at a vertex
-    bool mesh_fits = false;      // no row of the mesh is past the row limits, and no captured assembly has contacts
+    bool never_hold = false;     // an assembly with contacts has been captured: its replays replace the pattern
     bool pattern_held = false;   // the pattern arrays and the solver layout are those of the mesh without contacts
     bool asm_captured = false;   // an assembly has been captured: its replays may change the pattern at any time
     int *inc = nullptr;       // ninc
@@ -352,7 +352,6 @@ struct Ctx {
 // launch-side entry points implemented in the .hip files
 pc_status topo_build(Ctx *ctx, const pc_mesh *mesh, hipStream_t s);
 pc_status mesh_incidences(Ctx *ctx, hipStream_t s);   // after topo_build
-pc_status mesh_pattern(Ctx *ctx, bool create);        // after build_schedule, without contacts
 pc_status assemble_run(Ctx *ctx, const double *x, const double *v, pc_dtype dtype, double *b,
                        double *diag_out, hipStream_t s);
 pc_status export_blocks(Ctx *ctx, double *vals, double *D, bool solver, hipStream_t s);
