@@ -438,10 +438,15 @@ pc_status pc_mfma_probe(pc_ctx *ctx, float *out_host);
  *   r.P^-1 r over the r.P^-1 r the old direction was built from (residual
  *   replacement), with a default inner reduction of 0.5.  It saves
  *   iterations on small sheets and costs them on large ones at some steps.
- *   BF16 blocks always restart. */
+ *   BF16 blocks always restart.
+ * PC_OPT_RESIDENT_POLLS: how often (about 1 us each) a workgroup of a launch
+ *   that runs a sweep's iterations (see PC_OPT_LDS_WINDOW) looks for the others'
+ *   sums before the launch gives up, because something else holds the compute
+ *   units; the sweep is then restarted from where it stands with launches per
+ *   iteration.  In [0, 2^31), default 2,000,000. */
 typedef enum { PC_OPT_GRAPH_CHUNK = 0, PC_OPT_SPMV_SLICES_PER_BLOCK = 1, PC_OPT_VECTOR_ROWS_PER_BLOCK = 2,
                PC_OPT_LDS_WINDOW = 3, PC_OPT_NARROW_COLUMNS = 4, PC_OPT_SPMV_NARROW_ACTIVE = 5,
-               PC_OPT_INNER_FP32 = 6, PC_OPT_KEEP_DIRECTION = 7 } pc_option;
+               PC_OPT_INNER_FP32 = 6, PC_OPT_KEEP_DIRECTION = 7, PC_OPT_RESIDENT_POLLS = 8 } pc_option;
 pc_status pc_set_option(pc_ctx *ctx, int32_t option, int64_t value);
 pc_status pc_get_option(pc_ctx *ctx, int32_t option, int64_t *value);
 

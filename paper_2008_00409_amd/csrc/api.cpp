@@ -361,6 +361,13 @@ pc_status pc_set_option(pc_ctx *h, int32_t option, int64_t value) {
             }
             ctx->use_keep_dir = value != 0;
             return PC_OK;
+        case PC_OPT_RESIDENT_POLLS:
+            if (value < 0 || value > 0x7fffffff) {
+                ctx->err = "polls of a resident launch must be in [0, 2^31)";
+                return PC_ERR_ARG;
+            }
+            ctx->res_polls = (int)value;
+            return PC_OK;
         case PC_OPT_SPMV_SLICES_PER_BLOCK: {
             if (value != 1 && value != 2 && value != 4 && value != 8 && value != 16) {
                 ctx->err = "slices per block must be 1, 2, 4, 8 or 16";
@@ -403,6 +410,7 @@ pc_status pc_get_option(pc_ctx *h, int32_t option, int64_t *value) {
             return PC_OK;
         case PC_OPT_INNER_FP32: *value = ctx->use_inner32 ? 1 : 0; return PC_OK;
         case PC_OPT_KEEP_DIRECTION: *value = ctx->use_keep_dir ? 1 : 0; return PC_OK;
+        case PC_OPT_RESIDENT_POLLS: *value = ctx->res_polls; return PC_OK;
         default: ctx->err = "unknown option"; return PC_ERR_ARG;
     }
 }

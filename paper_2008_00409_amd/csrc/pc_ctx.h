@@ -335,6 +335,7 @@ struct Ctx {
     // each instance}, and its pinned copy
     int *win_info = nullptr, *win_info_h = nullptr;
     ResPlan res;
+    int res_polls = 2000000;      // PC_OPT_RESIDENT_POLLS: about 2 s
 
     BellState bell;
 };

@@ -36,10 +36,12 @@
 // workgroup barrier), so a workgroup that has seen it also finds those
 // stores.  Slots hold EMPTY until written; each set of slots has two buffers,
 // and the buffer of the next iteration is emptied at a point where every
-// workgroup is known to have read it.  Every wait is bounded (SPIN_LIMIT
-// polls); a workgroup that gives up marks the instance (flag 4) and leaves
-// without writing its results, and so do the others in turn; the solver then
-// restarts the instance from its iterate with the three launches.  Teams of
+// workgroup is known to have read it.  Every wait is bounded (
+// PC_OPT_RESIDENT_POLLS); a workgroup that gives up marks the instance (flag 4)
+// and leaves without writing its results, and so do the others in turn, except
+// that workgroups which have the last meeting's values finish and write theirs;
+// the solver then restarts the instance from what its iterate holds with the
+// three launches.  Teams of
 // more than one workgroup are launched cooperatively, so all of them are
 // resident at once.
 #include <hip/hip_runtime.h>
@@ -56,7 +58,6 @@ typedef unsigned long long u64;
 constexpr u64 EMPTY = 0xfff7a5a5a5a5a5a5ull;   // a NaN that publish() never writes
 constexpr int REPLICAS = 8;                    // copies of the slots: 256 workgroups polling one copy measured
                                                // 3.7-4.2 us per meeting, eight copies 2.8 us
-constexpr int SPIN_LIMIT = 2000000;            // polls of about 1 us
 
 __device__ __forceinline__ void agent_store(u64 *p, u64 v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -110,6 +111,7 @@ struct ResArgs {
     int slot_rep;          // distance between copies
     int slot_rz;           // first (r.z, r.r) slot
     int par, max_iters;
+    int polls;             // of a wait, before it gives up
 };
 
 // One stored block of a lane as it lies in memory, with its column (row of
@@ -262,9 +264,9 @@ __device__ __forceinline__ void apply_block(const RawBlock<TB> &B, const float3 
 // where the lane has none (its value is 0).  Polls until all are there; false
 // when the wait gave up.
 template <int N, typename F>
-__device__ __forceinline__ bool poll(F at, double (&v)[N]) {
+__device__ __forceinline__ bool poll(F at, int polls, double (&v)[N]) {
     u64 b[N];
-    for (int spin = 0; spin < SPIN_LIMIT; ++spin) {
+    for (int spin = 0; spin < polls; ++spin) {
 #pragma unroll
         for (int c = 0; c < N; ++c) {
             const u64 *p = at(c);
@@ -280,6 +282,8 @@ __device__ __forceinline__ bool poll(F at, double (&v)[N]) {
             return true;
         }
     }
+#pragma unroll
+    for (int c = 0; c < N; ++c) v[c] = 0.0;
     return false;
 }
 
@@ -552,7 +556,7 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
                         const int s = 64 * (w + nw * c) + lane;
                         return s < I.nsl ? mine + buf + I.pq_off + 2 * (16 * (s / 32) + s % 16) + (s / 16 & 1) : nullptr;
                     },
-                    v))
+                    A.polls, v))
                 bad = 1;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -572,7 +576,7 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
                     [&](int) {
                         return t < I.ngroups ? mine + buf + I.pq_off + ((t & ~3) | (t & 1) << 1 | (t >> 1 & 1)) : nullptr;
                     },
-                    v))
+                    A.polls, v))
                 bad = 1;
             if (64 * w < I.ngroups) {
                 const double s = wave_sum(0.0 + v[0]);
@@ -708,7 +712,7 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
                     const bool on = e < ne && (SPLIT ? 32 * i + k / 2 < I.nsl : k < 2 || 32 * i + 7 + k / 2 < I.nsl);
                     return on ? mine + buf + A.slot_rz + I.rz_off + 32 * i + (SPLIT || k < 2 ? k : 14 + k) : nullptr;
                 },
-                v))
+                A.polls, v))
             bad = 1;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -825,8 +829,9 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
         T.rzp[par] = rz;
         T.live[0] = T.live[1] = 0;
         T.iters = iters;
-        T.flags |= flags;
-        T.done = done;
+        // a workgroup that gave up at the last meeting may be setting both now
+        if (flags) atomicOr(&T.flags, flags);
+        if (done) T.done = 1;
     }
 }
 
@@ -1111,6 +1116,7 @@ pc_status resident_launch(Ctx *ctx, const SpmvArgs &M, int max_iters, hipStream_
     A.slot_rz = P.slot_rz;
     A.par = ctx->cg_par;
     A.max_iters = max_iters;
+    A.polls = ctx->res_polls;
     A.x = ctx->inner32 ? (void *)ctx->e32 : (void *)ctx->x;
     A.r = ctx->inner32 ? (void *)ctx->r32 : (void *)ctx->r;
     constexpr bool low = std::is_same<TB, f16_t>::value || std::is_same<TB, bf16_t>::value;
