@@ -367,6 +367,7 @@ pc_status pc_set_option(pc_ctx *h, int32_t option, int64_t value) {
                 return PC_ERR_ARG;
             }
             ctx->res_polls = (int)value;
+            ctx->res_off = ctx->res_lost = 0;
             return PC_OK;
         case PC_OPT_SPMV_SLICES_PER_BLOCK: {
             if (value != 1 && value != 2 && value != 4 && value != 8 && value != 16) {

@@ -336,6 +336,8 @@ struct Ctx {
     int *win_info = nullptr, *win_info_h = nullptr;
     ResPlan res;
     int res_polls = 2000000;      // PC_OPT_RESIDENT_POLLS: about 2 s
+    int res_off = 0;              // solves to go without resident launches after some gave up,
+    int res_lost = 0;             // and how many solves in a row had one that did
 
     BellState bell;
 };

@@ -965,7 +965,16 @@ static void launch_one(Ctx *ctx, const SpmvArgs &M, const Sched &S, const Grids 
 // resident kernel reproduces, with some instance's windows fitting its LDS.
 // Other schedules keep the order of sums their options ask for.
 static bool use_resident(const Ctx *ctx) {
-    return ctx->method == 0 && ctx->use_win && ctx->use_narrow && ctx->spb == 8 && ctx->rpb == 2048 && resident_fits(ctx);
+    return ctx->method == 0 && ctx->use_win && ctx->use_narrow && ctx->spb == 8 && ctx->rpb == 2048 &&
+           ctx->res_off == 0 && resident_fits(ctx);
+}
+
+// A resident launch gave up, after up to 2 s: what holds the compute units may
+// stay, so the next solves do without; twice as many after each loss in a row,
+// which bounds what the losses cost by the time of the solves between them.
+static void resident_lost(Ctx *ctx) {
+    ctx->res_off = 64 << std::min(ctx->res_lost, 16);
+    ctx->res_lost += 1;
 }
 
 // Plain launches of n iterations continuing the context's parity.
@@ -1272,12 +1281,14 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
     PC_HIP(hipGetLastError());
     for (int i = 0; i < ninst; ++i) sweeps[i] = 1;
     bool inner_hi = false, lost = false;   // lost: a resident launch's wait gave up (its device was shared)
+    const bool may_reside = use_resident(ctx);
+    if (ctx->res_off > 0) ctx->res_off -= 1;
     int guard = 0;
     long long nchunk = 0;
     for (;;) {
         // iterate until every instance is done
         const int variant = inner_hi ? 1 : 0;
-        const bool resident = use_resident(ctx) && !lost;
+        const bool resident = may_reside && !lost;
         const bool graph = ctx->graph_chunk > 0 && !(resident && ctx->res.all);
         if (graph) {
             const SpmvArgs &Mv = inner_hi ? Mhi : M;
@@ -1354,12 +1365,12 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
             const PcgState &h = ctx->st_host[i];
             const bool was_active = active[i] != 0;
             active[i] = 0;
+            if (was_active && (h.flags & 4)) lost = any_lost = true;
             const bool ok = res2[2 * i] <= tol * tol * res2[2 * i + 1];
             if (ok || res2[2 * i + 1] == 0.0 || (h.flags & 2) || iters[i] >= maxit) continue;
             if (h.flags & 4) {
                 // part of the launch's rows may hold its results: a start like
                 // any other, continued with three launches per iteration
-                lost = any_lost = true;
             } else if (h.flags & 1) {
                 if (!inner_hi && ctx->hi_valid) {
                     any_breakdown = true;
@@ -1383,6 +1394,7 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
             active[i] = 1;
             any = true;
         }
+        if (any_lost) resident_lost(ctx);
         if (!any || ++guard > max_sweeps + 8) break;
         if (any_breakdown) inner_hi = true;  // low-precision operator lost definiteness or stopped contracting: FP64 blocks from here on
         for (int i = 0; i < ninst; ++i) {
@@ -1402,6 +1414,7 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
                             s);
         PC_HIP(hipGetLastError());
     }
+    if (may_reside && !lost) ctx->res_lost = 0;
     // b = 0: the solution is 0 whatever the start
     std::vector<uint8_t> zero(ninst, 0);
     bool anyzero = false;
@@ -1503,6 +1516,15 @@ static pc_status time_iters(Ctx *ctx, const double *b, int iters, float *ms, hip
     PC_HIP(hipEventElapsedTime(ms, e0, e1));
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    if (resident) {
+        pc_status st = read_states(ctx, s);
+        if (st) return st;
+        for (int i = 0; i < ninst; ++i)
+            if (ctx->st_host[i].flags & 4) {   // not the iterations' time
+                resident_lost(ctx);
+                return time_iters<TB>(ctx, b, iters, ms, s);
+            }
+    }
     return PC_OK;
 }
 

@@ -73,6 +73,40 @@ def test_solves_whose_launches_give_up(torch, B, shape, dtype, precond):
         ctx.close()
 
 
+def test_a_loss_is_remembered(torch, B):
+    """The solves after a loss run without resident launches (their first sweep
+    does its work) until 64 have, then 128 after the second loss in a row; setting
+    the option lets the next one try again."""
+    c = sheet(43, 31, seed=5)
+    ctx, b = system(torch, B, c, "f64")
+    try:
+        sweeps = lambda: ctx.cloth_pcg_solve(b, tol=1e-2)[1]["sweeps"]
+        assert sweeps() == 1
+        ctx.set_option(B.PC_OPT_RESIDENT_POLLS, 0)
+        for between in (64, 128):
+            assert sweeps() == 2
+            assert all(sweeps() == 1 for _ in range(between))
+        assert sweeps() == 2
+        ctx.set_option(B.PC_OPT_RESIDENT_POLLS, 0)
+        assert sweeps() == 2 and sweeps() == 1
+    finally:
+        ctx.close()
+
+
+def test_autotuner_does_not_time_a_loss(torch, B):
+    """64 iterations that were not run would be the fastest of all; three launches
+    an iteration take more than 3 us."""
+    c = sheet(43, 31, seed=5)
+    ctx, b = system(torch, B, c, "f64")
+    try:
+        ctx.set_option(B.PC_OPT_RESIDENT_POLLS, 0)
+        assert ctx.autotune(b, iters=64)["ms_per_iter"] > 3e-3
+        dv, _ = ctx.cloth_pcg_solve(b, tol=TOL)
+        assert residual(ctx, b, dv, [0, c.nv]) <= TOL * (1 + 1e-6)
+    finally:
+        ctx.close()
+
+
 def test_option_range(torch, B):
     ctx = B.Context.from_cloth(sheet(5, 4))
     try:
