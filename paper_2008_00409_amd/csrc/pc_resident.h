@@ -17,8 +17,10 @@ void resident_free(Ctx *ctx);
 pc_status resident_windows(Ctx *ctx, int *inst_win, hipStream_t s);
 bool resident_fits(const Ctx *ctx);
 // Run every unfinished instance whose window fits for up to max_iters
-// iterations from its state at parity ctx->cg_par (left unchanged).
+// iterations from its state at parity ctx->cg_par (left unchanged).  *taken:
+// false when the runtime refused a launch; instances of the rounds before it run,
+// the others' states are as they were.
 template <typename TB>
-pc_status resident_launch(Ctx *ctx, const SpmvArgs &M, int max_iters, hipStream_t s);
+pc_status resident_launch(Ctx *ctx, const SpmvArgs &M, int max_iters, bool *taken, hipStream_t s);
 
 }  // namespace pc

@@ -1280,7 +1280,7 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
     }
     PC_HIP(hipGetLastError());
     for (int i = 0; i < ninst; ++i) sweeps[i] = 1;
-    bool inner_hi = false, lost = false;   // lost: a resident launch's wait gave up (its device was shared)
+    bool inner_hi = false, lost = false;   // lost: a resident launch's wait gave up (its device was shared), or was refused
     const bool may_reside = use_resident(ctx);
     if (ctx->res_off > 0) ctx->res_off -= 1;
     int guard = 0;
@@ -1288,7 +1288,7 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
     for (;;) {
         // iterate until every instance is done
         const int variant = inner_hi ? 1 : 0;
-        const bool resident = may_reside && !lost;
+        bool resident = may_reside && !lost;
         const bool graph = ctx->graph_chunk > 0 && !(resident && ctx->res.all);
         if (graph) {
             const SpmvArgs &Mv = inner_hi ? Mhi : M;
@@ -1299,13 +1299,20 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
                 if (st) return st;
             }
         }
-        const bool whole = resident && ctx->res.all && ctx->prof.every == 0;   // one launch to the end of the sweep
-        if (whole) {
-            st = inner_hi ? resident_launch<double>(ctx, Mhi, 1 << 30, s) : resident_launch<TB>(ctx, M, 1 << 30, s);
-            if (st) return st;
-        } else if ((st = read_states(ctx, s))) {
-            return st;
-        }
+        bool whole = resident && ctx->res.all && ctx->prof.every == 0;   // one launch to the end of the sweep
+        auto launch_resident = [&](int n) -> pc_status {
+            bool taken = true;
+            const pc_status e = inner_hi ? resident_launch<double>(ctx, Mhi, n, &taken, s)
+                                         : resident_launch<TB>(ctx, M, n, &taken, s);
+            if (e == PC_OK && !taken) {
+                resident_lost(ctx);
+                lost = true;
+                whole = resident = false;
+            }
+            return e;
+        };
+        if (whole && (st = launch_resident(1 << 30))) return st;
+        if (!whole && (st = read_states(ctx, s))) return st;
         while (!whole) {
             bool all_done = true;
             int most = 0;
@@ -1327,9 +1334,7 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
             if (fits && !sample) {
                 // to the end of the sweep; with profiling on, about seven chunks' iterations
                 const int most_iters = ctx->prof.every > 0 ? 7 * std::min(256, std::max(16, most / 4)) : 1 << 30;
-                st = inner_hi ? resident_launch<double>(ctx, Mhi, most_iters, s)
-                              : resident_launch<TB>(ctx, M, most_iters, s);
-                if (st) return st;
+                if ((st = launch_resident(most_iters))) return st;
                 if (ctx->prof.every > 0) nchunk += 6;
             } else if (graph && !sample && ctx->cg_par == 0) {
                 PC_HIP(hipGraphLaunch(ctx->gexec[variant], s));
@@ -1492,6 +1497,7 @@ static pc_status time_iters(Ctx *ctx, const double *b, int iters, float *ms, hip
     ctx->cg_par = 0;
     launch_start_zero(ctx, S, g, nullptr, b, s);
     const bool resident = use_resident(ctx) && ctx->res.all;
+    bool gave_up = false;
     if (!resident && ctx->graph_chunk > 0 && graph_stale(ctx, 0, M, dtype_code<TB>())) {
         pc_status st = capture_chunk<TB>(ctx, M, S, g, ctx->graph_chunk, 0);
         if (st) return st;
@@ -1501,8 +1507,10 @@ static pc_status time_iters(Ctx *ctx, const double *b, int iters, float *ms, hip
     PC_HIP(hipEventCreate(&e1));
     PC_HIP(hipEventRecord(e0, s));
     if (resident) {
-        pc_status st = resident_launch<TB>(ctx, M, iters, s);
+        bool taken = true;
+        pc_status st = resident_launch<TB>(ctx, M, iters, &taken, s);
         if (st) return st;
+        gave_up = !taken;
     } else if (ctx->graph_chunk > 0) {
         for (int done = 0; done < iters; done += ctx->graph_chunk) PC_HIP(hipGraphLaunch(ctx->gexec[0], s));
     } else {
@@ -1519,11 +1527,11 @@ static pc_status time_iters(Ctx *ctx, const double *b, int iters, float *ms, hip
     if (resident) {
         pc_status st = read_states(ctx, s);
         if (st) return st;
-        for (int i = 0; i < ninst; ++i)
-            if (ctx->st_host[i].flags & 4) {   // not the iterations' time
-                resident_lost(ctx);
-                return time_iters<TB>(ctx, b, iters, ms, s);
-            }
+        for (int i = 0; i < ninst; ++i) gave_up = gave_up || (ctx->st_host[i].flags & 4);
+        if (gave_up) {   // not the iterations' time
+            resident_lost(ctx);
+            return time_iters<TB>(ctx, b, iters, ms, s);
+        }
     }
     return PC_OK;
 }

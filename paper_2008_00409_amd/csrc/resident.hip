@@ -1041,34 +1041,40 @@ pc_status resident_windows(Ctx *ctx, int *inst_win, hipStream_t s) {
 }
 
 template <typename TB, typename TV, int NS, int NT, int KIND, bool FAR>
-static pc_status launch_kind(Ctx *ctx, ResArgs &A, hipStream_t s) {
+static pc_status launch_kind(Ctx *ctx, ResArgs &A, bool *taken, hipStream_t s) {
     const ResPlan &P = ctx->res;
     const size_t lds = sizeof(float4) * (size_t)P.win_rows + sizeof(TV) * (size_t)(3 * NS * NT * res_vectors(NS)) +
                        sizeof(double) * RAW;
     const void *fn = (const void *)k_pcg_resident<TB, TV, NS, NT, KIND, FAR>;
-    PC_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     const size_t nslots = (size_t)REPLICAS * P.slot_rep;
-    hipLaunchKernelGGL(k_res_clear, dim3((nslots + 255) / 256), dim3(256), 0, s, A.slots, nslots);
-    for (const auto &round : P.rounds) {
-        A.wg0 = round.first;
+    if (e == hipSuccess)
+        hipLaunchKernelGGL(k_res_clear, dim3((nslots + 255) / 256), dim3(256), 0, s, A.slots, nslots);
+    for (size_t k = 0; k < P.rounds.size() && e == hipSuccess; ++k) {
+        A.wg0 = P.rounds[k].first;
+        const dim3 grid(P.rounds[k].second), block(P.threads);
         if (P.coop) {
             void *args[] = {&A};
-            PC_HIP(hipLaunchCooperativeKernel(fn, dim3(round.second), dim3(P.threads), args, (unsigned)lds, s));
+            e = hipLaunchCooperativeKernel(fn, grid, block, args, (unsigned)lds, s);
         } else {
-            hipLaunchKernelGGL((k_pcg_resident<TB, TV, NS, NT, KIND, FAR>), dim3(round.second), dim3(P.threads), lds, s, A);
+            hipLaunchKernelGGL((k_pcg_resident<TB, TV, NS, NT, KIND, FAR>), grid, block, lds, s, A);
+            e = hipGetLastError();
         }
-        PC_HIP(hipGetLastError());
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *taken = false;
     }
     return PC_OK;
 }
 
 template <typename TB, typename TV, int NS, int NT>
-static pc_status launch_ns(Ctx *ctx, ResArgs &A, hipStream_t s) {
+static pc_status launch_ns(Ctx *ctx, ResArgs &A, bool *taken, hipStream_t s) {
     if (ctx->res.placed)
-        return ctx->precond == 0 ? launch_kind<TB, TV, NS, NT, 0, true>(ctx, A, s)
-                                 : launch_kind<TB, TV, NS, NT, 1, true>(ctx, A, s);
-    return ctx->precond == 0 ? launch_kind<TB, TV, NS, NT, 0, false>(ctx, A, s)
-                             : launch_kind<TB, TV, NS, NT, 1, false>(ctx, A, s);
+        return ctx->precond == 0 ? launch_kind<TB, TV, NS, NT, 0, true>(ctx, A, taken, s)
+                                 : launch_kind<TB, TV, NS, NT, 1, true>(ctx, A, taken, s);
+    return ctx->precond == 0 ? launch_kind<TB, TV, NS, NT, 0, false>(ctx, A, taken, s)
+                             : launch_kind<TB, TV, NS, NT, 1, false>(ctx, A, taken, s);
 }
 
 int resident_win_max(const Ctx *ctx) {
@@ -1089,7 +1095,8 @@ bool resident_fits(const Ctx *ctx) {
 }
 
 template <typename TB>
-pc_status resident_launch(Ctx *ctx, const SpmvArgs &M, int max_iters, hipStream_t s) {
+pc_status resident_launch(Ctx *ctx, const SpmvArgs &M, int max_iters, bool *taken, hipStream_t s) {
+    *taken = true;
     const ResPlan &P = ctx->res;
     ResArgs A{};
     A.slice_vbase = M.slice_vbase;
@@ -1124,28 +1131,28 @@ pc_status resident_launch(Ctx *ctx, const SpmvArgs &M, int max_iters, hipStream_
     if constexpr (low || f64) {
         if (ctx->inner32) {
             if constexpr (f64) {   // 512 registers where 256 threads do
-                if (P.threads <= 256) return launch_ns<TB, float, 1, 256>(ctx, A, s);
+                if (P.threads <= 256) return launch_ns<TB, float, 1, 256>(ctx, A, taken, s);
             }
-            if (P.ns == 1) return launch_ns<TB, float, 1, 512>(ctx, A, s);
-            if (P.ns == 2) return launch_ns<TB, float, 2, 512>(ctx, A, s);
+            if (P.ns == 1) return launch_ns<TB, float, 1, 512>(ctx, A, taken, s);
+            if (P.ns == 2) return launch_ns<TB, float, 2, 512>(ctx, A, taken, s);
         }
     }
     if constexpr (!low) {
         if (!ctx->inner32) {
             if constexpr (f64) {
-                if (P.threads <= 256) return launch_ns<TB, double, 1, 256>(ctx, A, s);
+                if (P.threads <= 256) return launch_ns<TB, double, 1, 256>(ctx, A, taken, s);
             }
-            if (P.ns == 1) return launch_ns<TB, double, 1, 512>(ctx, A, s);
-            if (P.ns == 2) return launch_ns<TB, double, 2, 512>(ctx, A, s);
+            if (P.ns == 1) return launch_ns<TB, double, 1, 512>(ctx, A, taken, s);
+            if (P.ns == 2) return launch_ns<TB, double, 2, 512>(ctx, A, taken, s);
         }
     }
     ctx->err = "internal: resident CG variant";
     return PC_ERR_ARG;
 }
 
-template pc_status resident_launch<double>(Ctx *, const SpmvArgs &, int, hipStream_t);
-template pc_status resident_launch<float>(Ctx *, const SpmvArgs &, int, hipStream_t);
-template pc_status resident_launch<bf16_t>(Ctx *, const SpmvArgs &, int, hipStream_t);
-template pc_status resident_launch<f16_t>(Ctx *, const SpmvArgs &, int, hipStream_t);
+template pc_status resident_launch<double>(Ctx *, const SpmvArgs &, int, bool *, hipStream_t);
+template pc_status resident_launch<float>(Ctx *, const SpmvArgs &, int, bool *, hipStream_t);
+template pc_status resident_launch<bf16_t>(Ctx *, const SpmvArgs &, int, bool *, hipStream_t);
+template pc_status resident_launch<f16_t>(Ctx *, const SpmvArgs &, int, bool *, hipStream_t);
 
 }  // namespace pc
