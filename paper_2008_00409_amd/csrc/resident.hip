@@ -1046,7 +1046,8 @@ static pc_status launch_kind(Ctx *ctx, ResArgs &A, bool *taken, hipStream_t s) {
     const size_t lds = sizeof(float4) * (size_t)P.win_rows + sizeof(TV) * (size_t)(3 * NS * NT * res_vectors(NS)) +
                        sizeof(double) * RAW;
     const void *fn = (const void *)k_pcg_resident<TB, TV, NS, NT, KIND, FAR>;
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    // the function's attribute is the process's: every context and thread sets the same
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, RES_LDS);
     const size_t nslots = (size_t)REPLICAS * P.slot_rep;
     if (e == hipSuccess)
         hipLaunchKernelGGL(k_res_clear, dim3((nslots + 255) / 256), dim3(256), 0, s, A.slots, nslots);
