@@ -113,9 +113,10 @@ __device__ __forceinline__ void state_start(PcgState &T, int par, const double t
 // sums: the start's values (the check that ended the previous sweep has
 // already formed its residual and direction), else k_fin_start brings them.
 // `flags` and maxit may lie in pinned host memory; the flags are kept in
-// `restart` for the kernels that follow.
+// `restart` for the kernels that follow.  status: the assembly's status word; a
+// matrix that it refuses is not iterated on.
 __global__ void k_state_init(int ninst, PcgState *st, const uint8_t *flags, uint8_t *restart, double tol, double rho,
-                             const int *maxit, int par, const double *sums) {
+                             const int *maxit, int par, const double *sums, const int *status) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= ninst) return;
     if (flags) {
@@ -135,7 +136,7 @@ __global__ void k_state_init(int ninst, PcgState *st, const uint8_t *flags, uint
     S.live[0] = S.live[1] = 0;
     S.iters = 0;
     S.maxit = maxit[i];
-    S.done = 0;
+    S.done = status && *status != 0 ? 1 : 0;
     S.flags = 0;
     if (sums) {
         const double tot[3] = {sums[3 * i], sums[3 * i + 1], sums[3 * i + 2]};
@@ -1269,7 +1270,7 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
 
     // first start of every instance
     hipLaunchKernelGGL(k_state_init, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, ctx->st,
-                       (const uint8_t *)nullptr, ctx->restart, tol, rho, maxit_h, 0, (const double *)nullptr);
+                       (const uint8_t *)nullptr, ctx->restart, tol, rho, maxit_h, 0, (const double *)nullptr, ctx->status);
     if (warm_kind) {
         // the start is used as given: its residual norm is no guide to the
         // CG iterations it saves (a start accurate in the slowly converging
@@ -1411,7 +1412,8 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
         }
         for (int i = 0; i < ninst; ++i) ctx->restart_h[i] = again[i];
         hipLaunchKernelGGL(k_state_init, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, ctx->st, ctx->restart_h,
-                           ctx->restart, tol, rho, maxit_h, ctx->cg_par, chained ? ctx->res2 : (const double *)nullptr);
+                           ctx->restart, tol, rho, maxit_h, ctx->cg_par, chained ? ctx->res2 : (const double *)nullptr,
+                           (const int *)nullptr);
         // a breakdown, the switch to the FP64 blocks or a lost launch restarts
         // from P^-1 r
         if (!chained)
@@ -1491,7 +1493,8 @@ static pc_status time_iters(Ctx *ctx, const double *b, int iters, float *ms, hip
     std::vector<int> big(ninst, 1 << 30);
     PC_HIP(hipMemcpyAsync(ctx->maxit_d, big.data(), sizeof(int) * ninst, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_state_init, dim3((ninst + 63) / 64), dim3(64), 0, s, ninst, ctx->st,
-                       (const uint8_t *)nullptr, ctx->restart, 0.0, 0.0, ctx->maxit_d, 0, (const double *)nullptr);
+                       (const uint8_t *)nullptr, ctx->restart, 0.0, 0.0, ctx->maxit_d, 0, (const double *)nullptr,
+                       (const int *)nullptr);
     pc_status wst = ensure_windows(ctx, s);
     if (wst) return wst;
     ctx->cg_par = 0;
