@@ -139,6 +139,7 @@ struct ResPlan {
     int16_t *place = nullptr;                  // with contacts: columns as rows of the windows
     size_t place_bytes = 0;
     bool placed = false;
+    bool have_windows = false;                 // the windows (and places) of the current pattern are there
     size_t inst_bytes = 0, wg_bytes = 0, win_bytes = 0, slot_bytes = 0;
     const int *inst_win = nullptr;             // per instance: largest window (in Ctx::win_info)
     int win_rows = 0;                          // LDS rows of the launches (0: no instance fits)

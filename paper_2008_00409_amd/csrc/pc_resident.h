@@ -14,7 +14,7 @@ int resident_win_max(const Ctx *ctx);
 
 pc_status resident_plan(Ctx *ctx);
 void resident_free(Ctx *ctx);
-pc_status resident_windows(Ctx *ctx, int *inst_win, hipStream_t s);
+pc_status resident_windows(Ctx *ctx, int *inst_win, bool *fits, hipStream_t s);
 bool resident_fits(const Ctx *ctx);
 // Run every unfinished instance whose window fits for up to max_iters
 // iterations from its state at parity ctx->cg_par (left unchanged).  *taken:

@@ -870,7 +870,7 @@ static pc_status ensure_windows(Ctx *ctx, hipStream_t s) {
         hipLaunchKernelGGL(k_item_windows, dim3(ctx->n_sitems), dim3(256), 0, s, S, ctx->slice_row0, ctx->rowptr,
                            ctx->colidx, ctx->sitem_win, PC_WIN_MAX, ctx->win_info);
         if (ctx->res.valid) {
-            pc_status st = resident_windows(ctx, ctx->win_info + 2, s);
+            pc_status st = resident_windows(ctx, ctx->win_info + 2, &ctx->res.have_windows, s);
             if (st) return st;
         }
         PC_HIP(hipGetLastError());
@@ -884,9 +884,10 @@ static pc_status ensure_windows(Ctx *ctx, hipStream_t s) {
     ResPlan &P = ctx->res;
     P.inst_win = ctx->win_info + 2;
     P.win_rows = 0;
-    P.all = P.valid;
-    const int rmax = P.valid ? resident_win_max(ctx) : 0;
-    for (int i = 0; i < ctx->ninst && P.valid; ++i) {
+    const bool windows = P.valid && P.have_windows;
+    P.all = windows;
+    const int rmax = windows ? resident_win_max(ctx) : 0;
+    for (int i = 0; i < ctx->ninst && windows; ++i) {
         if (ctx->win_info_h[2 + i] <= rmax)
             P.win_rows = std::max(P.win_rows, ctx->win_info_h[2 + i]);
         else

@@ -1018,9 +1018,11 @@ void resident_free(Ctx *ctx) {
 }
 
 // Without contacts one near range is the whole window and the 16-bit offsets
-// serve; with contacts the columns are placed per assembly (16 bits a block).
-pc_status resident_windows(Ctx *ctx, int *inst_win, hipStream_t s) {
+// serve; with contacts the columns are placed per assembly (16 bits a block),
+// and where there is no memory for that the solve does without.
+pc_status resident_windows(Ctx *ctx, int *inst_win, bool *fits, hipStream_t s) {
     ResPlan &P = ctx->res;
+    *fits = true;
     P.placed = ctx->nc > 0;
     hipLaunchKernelGGL(k_res_windows, dim3(P.nwg), dim3(256), 0, s, P.inst, P.wg, ctx->rowptr, ctx->colidx,
                        P.placed ? RES_REACH : 1 << 30, P.win, inst_win);
@@ -1030,8 +1032,10 @@ pc_status resident_windows(Ctx *ctx, int *inst_win, hipStream_t s) {
             dev_free(ctx, P.place);
             P.place = nullptr;
             P.place_bytes = 0;
-            pc_status st = dev_alloc(ctx, (void **)&P.place, bytes);
-            if (st) return st;
+            if (dev_alloc(ctx, (void **)&P.place, bytes)) {
+                *fits = false;
+                return PC_OK;
+            }
             P.place_bytes = bytes;
         }
         hipLaunchKernelGGL(k_res_place, dim3(P.nwg), dim3(512), 0, s, P.inst, P.wg, P.win, ctx->slice_vbase,
