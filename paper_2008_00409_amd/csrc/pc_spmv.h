@@ -142,18 +142,15 @@ struct SlotGroup {
 // slots cost wavefronts (80 registers with 2, 130 with 4) and measured the same
 // or slower.  FP16 and BF16 blocks are slower this way (828k rows: 40.1 -> 40.7
 // us), FP32 blocks the same.
-template <typename TB, typename V, bool NARROW, int C = 2>
+template <typename V, bool NARROW, int C = 2>
 __device__ __forceinline__ int spmv_row_ahead(const SpmvArgs &M, int slice, int lane, const V &x, double y[3],
                                               double xi[3]) {
-    typedef typename BlockIO<TB>::R R;
-    typedef typename std::conditional<std::is_same<V, VecD3>::value, double, typename SpmvAcc<TB>::T>::type A;
     const int row = M.lane_row[slice * WAVE + lane];
     const int my_cnt = (int)M.slot_cnt[slice * WAVE + lane];
     const int my_off = M.slice_vbase[slice] + wave_excl_scan(slot_width(my_cnt));
     const int r0 = NARROW ? M.slice_row0[slice] : 0;
     const int nslots = __popcll(__ballot(my_cnt > 0));  // counts are non-increasing in the slot
-    A x0 = 0, x1 = 0, x2 = 0, a0 = 0, a1 = 0, a2 = 0;
-    double m = 0.0;
+    double x0 = 0.0, x1 = 0.0, x2 = 0.0, a0 = 0.0, a1 = 0.0, a2 = 0.0, m = 0.0;
     if (row >= 0) {
         x.load(row, x0, x1, x2);
         m = M.mass[row];
@@ -173,8 +170,7 @@ __device__ __forceinline__ int spmv_row_ahead(const SpmvArgs &M, int slice, int 
     };
     if (nslots > 0) columns(0);
     for (int k = 0; k < nslots; k += C) {
-        R v[C][9];
-        A d[C][3];
+        double v[C][9], d[C][3];
         int col[C];
         bool act[C];
 #pragma unroll
@@ -182,7 +178,7 @@ __device__ __forceinline__ int spmv_row_ahead(const SpmvArgs &M, int slice, int 
             const int kk = min(k + u, nslots - 1);
             const int c = __builtin_amdgcn_readlane(my_cnt, kk), off = __builtin_amdgcn_readlane(my_off, kk);
             act[u] = (k + u < nslots) && lane < c;
-            BlockIO<TB>::load((const TB *)M.jval + 9 * (int64_t)off, slot_width(c), min(lane, c - 1), v[u]);
+            BlockIO<double>::load((const double *)M.jval + 9 * (int64_t)off, slot_width(c), min(lane, c - 1), v[u]);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -195,25 +191,20 @@ __device__ __forceinline__ int spmv_row_ahead(const SpmvArgs &M, int slice, int 
 #pragma unroll
         for (int u = 0; u < C; ++u) {
             const bool off_diag = col[u] != row;
-            A d0 = d[u][0] - (off_diag ? x0 : A(0)), d1 = d[u][1] - (off_diag ? x1 : A(0)),
-              d2 = d[u][2] - (off_diag ? x2 : A(0));
-            d0 = act[u] ? d0 : A(0);
-            d1 = act[u] ? d1 : A(0);
-            d2 = act[u] ? d2 : A(0);
-            a0 += dot3((A)v[u][0], d0, (A)v[u][1], d1, (A)v[u][2], d2);
-            a1 += dot3((A)v[u][3], d0, (A)v[u][4], d1, (A)v[u][5], d2);
-            a2 += dot3((A)v[u][6], d0, (A)v[u][7], d1, (A)v[u][8], d2);
+            double d0 = d[u][0] - (off_diag ? x0 : 0.0), d1 = d[u][1] - (off_diag ? x1 : 0.0),
+                   d2 = d[u][2] - (off_diag ? x2 : 0.0);
+            d0 = act[u] ? d0 : 0.0;
+            d1 = act[u] ? d1 : 0.0;
+            d2 = act[u] ? d2 : 0.0;
+            a0 += dot3(v[u][0], d0, v[u][1], d1, v[u][2], d2);
+            a1 += dot3(v[u][3], d0, v[u][4], d1, v[u][5], d2);
+            a2 += dot3(v[u][6], d0, v[u][7], d1, v[u][8], d2);
         }
     }
     if (row >= 0) {
-        double s0 = (double)a0, s1 = (double)a1, s2 = (double)a2;
-        if constexpr (BlockIO<TB>::SCALED) {
-            const double vi = M.vscale[2 * slice + 1];   // a power of two: exact
-            s0 *= vi; s1 *= vi; s2 *= vi;
-        }
-        y[0] = __builtin_fma(m, (double)x0, s0);
-        y[1] = __builtin_fma(m, (double)x1, s1);
-        y[2] = __builtin_fma(m, (double)x2, s2);
+        y[0] = __builtin_fma(m, x0, a0);
+        y[1] = __builtin_fma(m, x1, a1);
+        y[2] = __builtin_fma(m, x2, a2);
     } else {
         y[0] = y[1] = y[2] = 0.0;
     }
@@ -224,7 +215,7 @@ __device__ __forceinline__ int spmv_row_ahead(const SpmvArgs &M, int slice, int 
 template <typename TB, typename V, bool NARROW = false, int UNROLL = PC_SPMV_UNROLL>
 __device__ __forceinline__ int spmv_row(const SpmvArgs &M, int slice, int lane, const V &x, double y[3],
                                         double xi[3]) {
-    if constexpr (std::is_same<TB, double>::value) return spmv_row_ahead<TB, V, NARROW>(M, slice, lane, x, y, xi);
+    if constexpr (std::is_same<TB, double>::value) return spmv_row_ahead<V, NARROW>(M, slice, lane, x, y, xi);
     const int row = M.lane_row[slice * WAVE + lane];
     const int my_cnt = (int)M.slot_cnt[slice * WAVE + lane];
     const int my_off = M.slice_vbase[slice] + wave_excl_scan(slot_width(my_cnt));
