@@ -125,11 +125,7 @@ static void free_all(Ctx *c) {
                     c->cols_tmp, c->pairs_tmp, c->starts_tmp, c->win_info};
     for (void *p : ptrs) dev_free(c, p);
     resident_free(c);
-    if (c->win_info_h) (void)hipHostFree(c->win_info_h);
     if (c->st_host) (void)hipHostFree(c->st_host);
-    if (c->restart_h) (void)hipHostFree(c->restart_h);
-    if (c->res2_h) (void)hipHostFree(c->res2_h);
-    if (c->maxit_h) (void)hipHostFree(c->maxit_h);
     if (c->status_host) (void)hipHostFree(c->status_host);
     bell_free(c, c->bell);
 }
@@ -190,6 +186,7 @@ pc_status pc_create(const pc_mesh *mesh, const pc_params *params, pc_ctx **out) 
     ALLOC(ctx->mass, sizeof(double) * (size_t)nv);
     ALLOC(ctx->pinned, (size_t)nv);
     ALLOC(ctx->status, sizeof(int));
+    ALLOC(ctx->counter, sizeof(unsigned) * 4);
     ALLOC(ctx->inc_cnt, sizeof(int) * (size_t)nv);
     ALLOC(ctx->inc_ptr, sizeof(int) * (size_t)(nv + 1));
     ALLOC(ctx->tmp, sizeof(double) * 3 * (size_t)nv);
@@ -254,7 +251,6 @@ pc_status pc_create(const pc_mesh *mesh, const pc_params *params, pc_ctx **out) 
     ALLOC(ctx->q, sizeof(double) * 3 * (size_t)nv);
     ALLOC(ctx->bbuf, sizeof(double) * 3 * (size_t)nv);
     ALLOC(ctx->p, sizeof(float) * 3 * (size_t)nv);
-    ALLOC(ctx->counter, sizeof(unsigned) * 4);
 #undef ALLOC
     (void)nsl;
     if (hipHostMalloc((void **)&ctx->status_host, sizeof(int), hipHostMallocDefault) != hipSuccess) {

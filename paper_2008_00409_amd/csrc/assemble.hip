@@ -388,14 +388,10 @@ pc_status mesh_incidences(Ctx *ctx, hipStream_t s) {
     const int nv = ctx->nv, nt = ctx->nt, nh = ctx->nh, TB = 256;
     const int64_t ni = 3 * (int64_t)nt + 4 * (int64_t)nh;
     pc_status st;
-    int *list = nullptr, *longest = nullptr;
+    int *list = nullptr, *const longest = (int *)ctx->counter;
     if ((st = dev_alloc(ctx, (void **)&ctx->mesh_ptr, sizeof(int) * (size_t)(nv + 1)))) return st;
     if ((st = dev_alloc(ctx, (void **)&ctx->mesh_inc, sizeof(int) * (size_t)ni))) return st;
     if ((st = dev_alloc(ctx, (void **)&list, sizeof(int) * (size_t)ni))) return st;
-    if ((st = dev_alloc(ctx, (void **)&longest, sizeof(int)))) {
-        dev_free(ctx, list);
-        return st;
-    }
     const dim3 grid((unsigned)((ni + TB - 1) / TB));
     hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, longest, 0, (int64_t)1);
     hipLaunchKernelGGL(k_mesh_inc_count, grid, dim3(TB), 0, s, nt, nh, ctx->tri, ctx->hinge, ctx->inc_cnt);
@@ -407,7 +403,6 @@ pc_status mesh_incidences(Ctx *ctx, hipStream_t s) {
     const hipError_t e1 = hipMemcpyAsync(&ctx->mesh_longest, longest, sizeof(int), hipMemcpyDeviceToHost, s);
     const hipError_t e2 = hipStreamSynchronize(s);
     dev_free(ctx, list);
-    dev_free(ctx, longest);
     if (st) return st;
     PC_HIP(e1);
     PC_HIP(e2);

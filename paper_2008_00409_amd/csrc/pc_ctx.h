@@ -125,10 +125,10 @@ struct ResWin {
     int lo, n, blo, bn, alo, an;
 };
 
-// Teams of all instances (built with the schedule) and, per assembly, their
+// Teams of all instances (made for the first solve of a schedule) and, per assembly, their
 // block-column windows.
 struct ResPlan {
-    bool valid = false, coop = false;
+    bool planned = false, valid = false, coop = false;
     int ns = 1, threads = 1024, nwg = 0;
     int slot_n = 0, slot_rep = 0, slot_rz = 0;
     std::vector<std::pair<int, int>> rounds;   // (first workgroup, workgroups) of each launch
@@ -140,7 +140,8 @@ struct ResPlan {
     size_t place_bytes = 0;
     bool placed = false;
     bool have_windows = false;                 // the windows (and places) of the current pattern are there
-    size_t inst_bytes = 0, wg_bytes = 0, win_bytes = 0, slot_bytes = 0;
+    char *mem = nullptr;                       // the arrays above but `place`
+    size_t mem_bytes = 0;
     const int *inst_win = nullptr;             // per instance: largest window (in Ctx::win_info)
     int win_rows = 0;                          // LDS rows of the launches (0: no instance fits)
     bool all = false;                          // every instance fits

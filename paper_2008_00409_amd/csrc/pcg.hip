@@ -792,22 +792,17 @@ pc_status build_schedule(Ctx *ctx) {
         if ((st = realloc((void **)&ctx->res2, sizeof(double) * 3 * ninst))) return st;
         if ((st = realloc((void **)&ctx->restart, (size_t)ninst))) return st;
         if ((st = realloc((void **)&ctx->maxit_d, sizeof(int) * ninst))) return st;
-        if (ctx->st_host) (void)hipHostFree(ctx->st_host);
-        if (ctx->restart_h) (void)hipHostFree(ctx->restart_h);
-        if (ctx->win_info_h) (void)hipHostFree(ctx->win_info_h);
-        if (ctx->res2_h) (void)hipHostFree(ctx->res2_h);
-        if (ctx->maxit_h) (void)hipHostFree(ctx->maxit_h);
-        ctx->st_host = nullptr;
-        ctx->restart_h = nullptr;
-        ctx->win_info_h = nullptr;
-        ctx->res2_h = nullptr;
-        ctx->maxit_h = nullptr;
         if ((st = realloc((void **)&ctx->win_info, sizeof(int) * (2 + (size_t)ninst)))) return st;
-        PC_HIP(hipHostMalloc((void **)&ctx->win_info_h, sizeof(int) * (2 + (size_t)ninst), hipHostMallocDefault));
-        PC_HIP(hipHostMalloc((void **)&ctx->st_host, sizeof(PcgState) * ninst, hipHostMallocDefault));
-        PC_HIP(hipHostMalloc((void **)&ctx->restart_h, (size_t)ninst, hipHostMallocDefault));
-        PC_HIP(hipHostMalloc((void **)&ctx->res2_h, sizeof(double) * 2 * (size_t)ninst, hipHostMallocDefault));
-        PC_HIP(hipHostMalloc((void **)&ctx->maxit_h, sizeof(int) * (size_t)ninst, hipHostMallocDefault));
+        // the pinned staging in one block (each allocation of one costs about 25 us)
+        if (ctx->st_host) (void)hipHostFree(ctx->st_host);
+        ctx->st_host = nullptr;
+        const size_t n = (size_t)ninst;
+        PC_HIP(hipHostMalloc((void **)&ctx->st_host, (sizeof(PcgState) + 2 * sizeof(double) + 2 * sizeof(int) + 1) * n + 2 * sizeof(int),
+                             hipHostMallocDefault));
+        ctx->res2_h = (double *)(ctx->st_host + n);
+        ctx->maxit_h = (int *)(ctx->res2_h + 2 * n);
+        ctx->win_info_h = ctx->maxit_h + n;
+        ctx->restart_h = (uint8_t *)(ctx->win_info_h + 2 + n);
     }
     if (!ctx->row_slice && (st = dev_alloc(ctx, (void **)&ctx->row_slice, sizeof(int) * (size_t)ctx->nv))) return st;
     PC_HIP(hipMemcpy(ctx->slice_row0, slice_row0.data(), sizeof(int) * slice_row0.size(), hipMemcpyHostToDevice));
@@ -825,7 +820,8 @@ pc_status build_schedule(Ctx *ctx) {
     ctx->sched_version += 1;
     ctx->win_valid = ctx->win_known = false;
     ctx->assembled = false;  // the solver layout depends on the slices
-    return resident_plan(ctx);
+    ctx->res.planned = false;
+    return PC_OK;
 }
 
 struct Grids {
@@ -863,6 +859,10 @@ static pc_status ensure_windows(Ctx *ctx, hipStream_t s) {
             pc_status st = dev_alloc(ctx, (void **)&ctx->sitem_win, sizeof(int2) * (size_t)ctx->n_sitems);
             if (st) return st;
             ctx->win_items = ctx->n_sitems;
+        }
+        if (!ctx->res.planned) {
+            pc_status st = resident_plan(ctx);
+            if (st) return st;
         }
         const Sched S = sched_args(ctx);
         const int ni = 2 + ctx->ninst;

@@ -929,6 +929,7 @@ __global__ void k_res_clear(u64 *slots, size_t n) {
 // batch in two such rounds 73 us against 62 us.)
 pc_status resident_plan(Ctx *ctx) {
     ResPlan &P = ctx->res;
+    P.planned = true;
     P.valid = false;
     P.rounds.clear();
     const int ninst = (int)ctx->inst_row0_h.size() - 1;
@@ -986,22 +987,25 @@ pc_status resident_plan(Ctx *ctx) {
     P.slot_rep = 2 * P.slot_n + 32;
     P.coop = false;
     for (const ResInst &I : inst) P.coop = P.coop || I.team > 1;
-    pc_status st;
-    auto grow = [&](void **p, size_t &have, size_t bytes) -> pc_status {
-        if (bytes <= have) return PC_OK;
-        if (*p) dev_free(ctx, *p);
-        *p = nullptr;
-        have = 0;
-        pc_status s = dev_alloc(ctx, p, bytes);
-        if (s == PC_OK) have = bytes;
-        return s;
-    };
-    if ((st = grow((void **)&P.inst, P.inst_bytes, sizeof(ResInst) * ninst))) return st;
-    if ((st = grow((void **)&P.wg, P.wg_bytes, sizeof(int4) * wg.size()))) return st;
-    if ((st = grow((void **)&P.win, P.win_bytes, sizeof(ResWin) * wg.size()))) return st;
-    if ((st = grow((void **)&P.slots, P.slot_bytes, sizeof(u64) * (size_t)REPLICAS * P.slot_rep))) return st;
-    PC_HIP(hipMemcpy(P.inst, inst.data(), sizeof(ResInst) * ninst, hipMemcpyHostToDevice));
-    PC_HIP(hipMemcpy(P.wg, wg.data(), sizeof(int4) * wg.size(), hipMemcpyHostToDevice));
+    // one block: the instances and workgroups, in one copy, then windows and slots
+    const size_t inst_bytes = (sizeof(ResInst) * ninst + 15) / 16 * 16, wg_bytes = sizeof(int4) * wg.size();
+    const size_t win_at = inst_bytes + wg_bytes, slots_at = (win_at + sizeof(ResWin) * wg.size() + 127) / 128 * 128;
+    const size_t bytes = slots_at + sizeof(u64) * (size_t)REPLICAS * P.slot_rep;
+    if (bytes > P.mem_bytes) {
+        dev_free(ctx, P.mem);
+        P.mem = nullptr;
+        P.mem_bytes = 0;
+        if (dev_alloc(ctx, (void **)&P.mem, bytes)) return PC_OK;   // the three launches need none of it
+        P.mem_bytes = bytes;
+    }
+    std::vector<char> up(win_at);
+    std::copy_n((const char *)inst.data(), sizeof(ResInst) * ninst, up.data());
+    std::copy_n((const char *)wg.data(), wg_bytes, up.data() + inst_bytes);
+    PC_HIP(hipMemcpy(P.mem, up.data(), win_at, hipMemcpyHostToDevice));
+    P.inst = (ResInst *)P.mem;
+    P.wg = (int4 *)(P.mem + inst_bytes);
+    P.win = (ResWin *)(P.mem + win_at);
+    P.slots = (u64 *)(P.mem + slots_at);
     P.nwg = (int)wg.size();
     P.valid = true;
     return PC_OK;
@@ -1009,10 +1013,7 @@ pc_status resident_plan(Ctx *ctx) {
 
 void resident_free(Ctx *ctx) {
     ResPlan &P = ctx->res;
-    dev_free(ctx, P.inst);
-    dev_free(ctx, P.wg);
-    dev_free(ctx, P.win);
-    dev_free(ctx, P.slots);
+    dev_free(ctx, P.mem);
     dev_free(ctx, P.place);
     P = ResPlan{};
 }
