@@ -444,8 +444,8 @@ pc_status pc_mfma_probe(pc_ctx *ctx, float *out_host);
  *   sums before the launch gives up, because something else holds the compute
  *   units; the sweep is then restarted from where it stands with launches per
  *   iteration, and so run the context's next 64 solves (twice as many after each
- *   further loss in a row).  In [0, 2^31), default 2,000,000; setting it lets the
- *   next solve try again. */
+ *   further loss in a row).  In [0, 2^31), default 2,000,000; 0: every launch
+ *   gives up.  Setting it lets the next solve try again. */
 typedef enum { PC_OPT_GRAPH_CHUNK = 0, PC_OPT_SPMV_SLICES_PER_BLOCK = 1, PC_OPT_VECTOR_ROWS_PER_BLOCK = 2,
                PC_OPT_LDS_WINDOW = 3, PC_OPT_NARROW_COLUMNS = 4, PC_OPT_SPMV_NARROW_ACTIVE = 5,
                PC_OPT_INNER_FP32 = 6, PC_OPT_KEEP_DIRECTION = 7, PC_OPT_RESIDENT_POLLS = 8 } pc_option;

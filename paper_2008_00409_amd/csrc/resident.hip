@@ -262,11 +262,13 @@ __device__ __forceinline__ void apply_block(const RawBlock<TB> &B, const float3 
 
 // The lane's N published values: `at(c)` gives the slot of value c, or null
 // where the lane has none (its value is 0).  Polls until all are there; false
-// when the wait gave up.
+// when the wait gave up (v is then not set).  The count runs down from a kernel
+// argument and at least one poll is made: tested before the first, with v set to
+// 0 on the way out, it cost 0.6 us an iteration of the small FP64 systems.
 template <int N, typename F>
 __device__ __forceinline__ bool poll(F at, int polls, double (&v)[N]) {
     u64 b[N];
-    for (int spin = 0; spin < polls; ++spin) {
+    do {
 #pragma unroll
         for (int c = 0; c < N; ++c) {
             const u64 *p = at(c);
@@ -281,9 +283,7 @@ __device__ __forceinline__ bool poll(F at, int polls, double (&v)[N]) {
             for (int c = 0; c < N; ++c) v[c] = __builtin_bit_cast(double, b[c]);
             return true;
         }
-    }
-#pragma unroll
-    for (int c = 0; c < N; ++c) v[c] = 0.0;
+    } while (--polls > 0);
     return false;
 }
 
@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
     const ResWin W = A.win[A.wg0 + (int)blockIdx.x];
     const int lo = W.lo, wn = W.n, hi = lo + wn, nfar = FAR ? W.bn + W.an : 0;   // near rows [lo, hi), then the far ones
     auto far_row = [&](int f) { return f < W.bn ? W.blo + f : W.alo + f - W.bn; };
-    if (t0 == 0) bad = 0;
+    if (t0 == 0) bad = A.polls == 0;   // 0: give up at the first meeting
     for (int k = t0; k < wn + nfar; k += nt) pwin[k] = ld3(A.p, !FAR || k < wn ? lo + k : far_row(k - wn));
     // rows of this workgroup: [a0, a1) and [b0, b1); the other rows of its
     // window are its halo
@@ -830,8 +830,8 @@ __global__ void __launch_bounds__(NT) k_pcg_resident(ResArgs A) {
         T.live[0] = T.live[1] = 0;
         T.iters = iters;
         // a workgroup that gave up at the last meeting may be setting both now
-        if (flags) atomicOr(&T.flags, flags);
-        if (done) T.done = 1;
+        atomicOr(&T.flags, flags);
+        atomicOr(&T.done, done);
     }
 }
 
