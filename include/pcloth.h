@@ -14,7 +14,8 @@
  *
  * The matrix is rebuilt every step from the element list (Sec. 3.2.2: the
  * block pattern is derived from the elements, duplicates removed, values
- * summed per block), and solved by Jacobi-preconditioned CG (Sec. 3.1).
+ * summed per block; without contacts the pattern is the mesh's and is derived
+ * once), and solved by Jacobi-preconditioned CG (Sec. 3.1).
  *
  * Conventions (all entry points):
  *  - Vectors (x, v, b, dv) are DEVICE arrays of nv*3 doubles, vertex-major

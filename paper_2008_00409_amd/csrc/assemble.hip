@@ -1,7 +1,8 @@
 // Topology, rest data and per-step assembly of A and b (paper Sec. 2.5, Eq. 3;
 // Sec. 3.2.2 for the dynamic block pattern and value filling).
 //
-// Per step, from the element list (triangles and hinges):
+// From the element list (triangles and hinges); without contacts 2 and 3 are
+// functions of the mesh and its instances, done by the first assembly and held:
 //   1. the element corners incident to each vertex: the mesh's own, which
 //      never change, are laid out when the context is created; an assembly
 //      with contacts counts, scans and adds theirs (integer atomics only: the

@@ -114,7 +114,7 @@ struct MlpState;
 struct ResInst {
     int row0, nrows, slice0, nsl;
     int ngroups, nitems;   // 8-slice SpMV items, 32-slice vector items
-    int k;                 // pairs of slices per workgroup: 1, 2, 4 or 8
+    int k;                 // pairs of slices per workgroup: 2, 4 or 8
     int team;              // workgroups
     int pq_off, rz_off;    // first slots
 };
@@ -246,7 +246,8 @@ struct Ctx {
     uint8_t *pairs_tmp = nullptr;    // 3 ninc: each row's pairs grouped by column slot
     uint8_t *starts_tmp = nullptr;   // 3 ninc + nv: first pair of each column slot
     int64_t pair_incs = 0;        // incidences the two buffers above can hold
-    // element records of the last assembly (FP64 SoA planes; sizes in doubles)
+    // element records of the last assembly (FP64: one record per triangle and hinge,
+    // two planes for contacts; sizes in doubles)
     double *trec = nullptr, *hrec = nullptr, *crec = nullptr;
     size_t trec_elems = 0, hrec_elems = 0, crec_elems = 0;
     int *slice_row0 = nullptr;    // nslices + 1: first row of each slice

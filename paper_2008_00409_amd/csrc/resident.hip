@@ -9,15 +9,16 @@
 // blocks that do not fit the registers.  Three launches per iteration (SpMV,
 // update, direction) pay each launch's fill and drain, move every vector
 // through memory between them and stream all blocks.  Per iteration, three
-// launches -> resident, with the solve's other work spread over 64-96
-// iterations (FP16 and FP32 blocks with block Jacobi and Jacobi, in us):
+// launches -> resident, in solves of one sweep of 96 iterations with the solve's
+// other work spread over them (FP16 blocks with block Jacobi, FP32 and FP64 with
+// Jacobi), in us:
 //   rows       256        2,560       33k         66k         131k        262k
-//   FP16   15.0 ->  8.0  18.4 ->  9.8  19.7 -> 10.7  24.7 -> 15.2  25.5 -> 15.9  30.9 -> 20.0
-//   FP32   14.8 ->  7.2  21.5 -> 10.4  22.7 -> 11.6  26.5 -> 12.6  32.5 -> 23.3  40.1 -> 27.4
-//   FP64   14.8 ->  7.4  22.0 ->  9.5  27.0 -> 10.4  29.7 -> 17.6  42.3 -> 33.5  61.3 -> 41.2
-// An iteration of the 262k-row FP16 case (15.9 us of its own) is 4.3 product,
-// 1.3 wait for the workgroup's slowest wavefront, 2-4 p.q meeting, 1 update,
-// 1.5 sums and stores, 3.5 (r.z, r.r) meeting, 1.8 direction.
+//   FP16   12.7 ->  5.8  16.5 ->  6.7  18.1 ->  7.9  17.8 ->  9.4  22.0 -> 11.3  28.3 -> 14.0
+//   FP32   13.9 ->  6.3  19.8 ->  7.6  21.4 ->  9.9  23.5 -> 12.2  27.9 -> 14.7  38.8 -> 23.3
+//   FP64   13.7 ->  6.5  20.0 ->  8.2  23.2 -> 10.5  26.1 -> 12.9  34.7 -> 20.9  55.6 -> 37.8
+// Where an iteration's time goes, of a frame of 262k rows in FP16 (15.9 us): 4.3
+// product, 1.3 wait for the workgroup's slowest wavefront, 2-4 p.q meeting, 1
+// update, 1.5 sums and stores, 3.5 (r.z, r.r) meeting, 1.8 direction.
 //
 // The sums are formed in exactly the order of the three-launch iteration at
 // its default schedule (8-slice SpMV items, 2048-row vector items), so both
