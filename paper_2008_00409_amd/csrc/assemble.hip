@@ -1344,8 +1344,8 @@ __device__ __forceinline__ void row_values_g(RowGroupLDS<NI> &L, const AsmArgs &
 //
 // What bounds it is the latency of its three rounds of dependent loads (the
 // row's state, its lists, the records) at 12 wavefronts a compute unit, and
-// behind it the memory traffic (2 GB) and the vector instructions (1,120 a
-// wavefront, 45% of its time).  Reading the records pair by pair from
+// behind it the memory traffic (2 GB) and the vector instructions (1,160 a
+// wavefront, 44% of its time).  Reading the records pair by pair from
 // planes took 420 accesses to the L1 a row (1.35 ms for 828k rows; also 64 or
 // 16 rows side by side per load, with 2 to 4 pairs in flight, 1.55 to 1.65
 // ms); so the parts of the records that the group needs come once, 16 bytes a
@@ -1355,8 +1355,7 @@ __device__ __forceinline__ void row_values_g(RowGroupLDS<NI> &L, const AsmArgs &
 // sources: with each chunk's row, incidence and part found from its number
 // there were 1,680 vector instructions a wavefront; and every value that the
 // slots need is requested before the one wait for the records: 0.85 ms, or
-// 0.90 where the lists were laid out with the mesh and are not fresh in the
-// caches.  Workgroups that stay and fetch the next group's lists ahead measured 1.5 to 1.85 ms: their waits include the stores.
+// 0.89 on a held pattern, whose lists are not fresh in the caches.  Workgroups that stay and fetch the next group's lists ahead measured 1.5 to 1.85 ms: their waits include the stores.
 constexpr int REC_CHUNKS = 704;   // 16-byte chunks of records a group keeps in LDS; the incidences beyond are read directly
 constexpr int TRI_CHUNKS = 12;    // of a triangle: the two blocks and the force of the row's corner
 struct RowPairsLDS {
