@@ -445,7 +445,7 @@ pc_status pc_mfma_probe(pc_ctx *ctx, float *out_host);
  *   sums before the launch gives up, because something else holds the compute
  *   units; the sweep is then restarted from where it stands with launches per
  *   iteration, and so run the context's next 64 solves (twice as many after each
- *   further loss in a row).  In [0, 2^31), default 2,000,000; 0: every launch
+ *   further loss in a row).  In [0, 2,000,000], default the most; 0: every launch
  *   gives up.  Setting it lets the next solve try again. */
 typedef enum { PC_OPT_GRAPH_CHUNK = 0, PC_OPT_SPMV_SLICES_PER_BLOCK = 1, PC_OPT_VECTOR_ROWS_PER_BLOCK = 2,
                PC_OPT_LDS_WINDOW = 3, PC_OPT_NARROW_COLUMNS = 4, PC_OPT_SPMV_NARROW_ACTIVE = 5,

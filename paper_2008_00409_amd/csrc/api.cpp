@@ -358,8 +358,8 @@ pc_status pc_set_option(pc_ctx *h, int32_t option, int64_t value) {
             ctx->use_keep_dir = value != 0;
             return PC_OK;
         case PC_OPT_RESIDENT_POLLS:
-            if (value < 0 || value > 0x7fffffff) {
-                ctx->err = "polls of a resident launch must be in [0, 2^31)";
+            if (value < 0 || value > RES_POLLS) {
+                ctx->err = "polls of a resident launch must be in [0, 2000000]";
                 return PC_ERR_ARG;
             }
             ctx->res_polls = (int)value;

@@ -110,7 +110,9 @@ struct Prof {
 
 struct MlpState;
 
-// Resident CG (resident.hip): one instance's rows, slices, teams and slots.
+// Resident CG (resident.hip): most polls of a wait, about 2 s; and one instance's
+// rows, slices, teams and slots.
+constexpr int RES_POLLS = 2000000;
 struct ResInst {
     int row0, nrows, slice0, nsl;
     int ngroups, nitems;   // 8-slice SpMV items, 32-slice vector items
@@ -338,7 +340,7 @@ struct Ctx {
     // each instance}, and its pinned copy
     int *win_info = nullptr, *win_info_h = nullptr;
     ResPlan res;
-    int res_polls = 2000000;      // PC_OPT_RESIDENT_POLLS: about 2 s
+    int res_polls = RES_POLLS;    // PC_OPT_RESIDENT_POLLS
     int res_off = 0;              // solves to go without resident launches after some gave up,
     int res_lost = 0;             // and how many solves in a row had one that did
 

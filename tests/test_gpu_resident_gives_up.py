@@ -111,7 +111,7 @@ def test_option_range(torch, B):
     ctx = B.Context.from_cloth(sheet(5, 4))
     try:
         assert ctx.get_option(B.PC_OPT_RESIDENT_POLLS) == 2_000_000
-        for value in (-1, 1 << 31):
+        for value in (-1, 2_000_001, 1 << 40):
             with pytest.raises(B.PclothError, match="PC_ERR_ARG"):
                 ctx.set_option(B.PC_OPT_RESIDENT_POLLS, value)
     finally:
