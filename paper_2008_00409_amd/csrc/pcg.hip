@@ -1407,8 +1407,10 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
         for (int i = 0; i < ninst; ++i) {
             if (again[i]) {
                 sweeps[i] += 1;
+                // a lost sweep's budget serves the one that does its work
+                const int later = ctx->st_host[i].flags & 4 ? maxit_h[i] : std::max(256, 3 * longest[i]);
                 maxit_h[i] = maxit - iters[i];
-                if (sweep_budget && !inner_hi) maxit_h[i] = std::min(maxit_h[i], std::max(256, 3 * longest[i]));
+                if (sweep_budget && !inner_hi) maxit_h[i] = std::min(maxit_h[i], later);
             }
         }
         for (int i = 0; i < ninst; ++i) ctx->restart_h[i] = again[i];

@@ -73,6 +73,28 @@ def test_solves_whose_launches_give_up(torch, B, shape, dtype, precond):
         ctx.close()
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_a_lost_sweep_keeps_its_budget(torch, B, dtype):
+    """A refinement sweep that was lost is run again with the iterations it had: the
+    budget of later sweeps (three times the longest so far, at least 256) would end
+    it early, for a sweep more, or on FP64 blocks where its residual has not halved.
+    The first sweep of this sheet at rest takes about 1,600 iterations."""
+    c = mg.config_medium()
+    ctx = B.Context.from_cloth(c)
+    try:
+        x = to_dev(torch, c.x0)
+        b = ctx.cloth_assemble(x, torch.zeros_like(x), dtype)
+        kw = dict(tol=1e-6, precond="block")
+        _, want = ctx.cloth_pcg_solve(b, **kw)
+        assert want["fallback"] == 0
+        ctx.set_option(B.PC_OPT_RESIDENT_POLLS, 0)
+        dv, info = ctx.cloth_pcg_solve(b, **kw)
+        assert info["fallback"] == 0 and info["sweeps"] == want["sweeps"] + 1, (info, want)
+        assert residual(ctx, b, dv, [0, c.nv]) <= 1e-6 * (1 + 1e-6)
+    finally:
+        ctx.close()
+
+
 def test_a_loss_is_remembered(torch, B):
     """The solves after a loss run without resident launches (their first sweep
     does its work) until 64 have, then 128 after the second loss in a row; setting
