@@ -446,10 +446,13 @@ pc_status pc_mfma_probe(pc_ctx *ctx, float *out_host);
  *   units; the sweep is then restarted from where it stands with launches per
  *   iteration, and so run the context's next 64 solves (twice as many after each
  *   further loss in a row).  In [0, 2,000,000], default the most; 0: every launch
- *   gives up.  Setting it lets the next solve try again. */
+ *   gives up.  Setting it lets the next solve try again.
+ * PC_OPT_RESIDENT_OFF (read only, pc_get_option): how many of the context's next
+ *   solves will go without such launches. */
 typedef enum { PC_OPT_GRAPH_CHUNK = 0, PC_OPT_SPMV_SLICES_PER_BLOCK = 1, PC_OPT_VECTOR_ROWS_PER_BLOCK = 2,
                PC_OPT_LDS_WINDOW = 3, PC_OPT_NARROW_COLUMNS = 4, PC_OPT_SPMV_NARROW_ACTIVE = 5,
-               PC_OPT_INNER_FP32 = 6, PC_OPT_KEEP_DIRECTION = 7, PC_OPT_RESIDENT_POLLS = 8 } pc_option;
+               PC_OPT_INNER_FP32 = 6, PC_OPT_KEEP_DIRECTION = 7, PC_OPT_RESIDENT_POLLS = 8,
+               PC_OPT_RESIDENT_OFF = 9 } pc_option;
 pc_status pc_set_option(pc_ctx *ctx, int32_t option, int64_t value);
 pc_status pc_get_option(pc_ctx *ctx, int32_t option, int64_t *value);
 

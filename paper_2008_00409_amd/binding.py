@@ -43,7 +43,7 @@ WARM = {"zero": 0, "prev": 1, "given": 1, "learned": 2}
 METHOD = {"cg": 0, "chronopoulos-gear": 1}
 PC_OPT_GRAPH_CHUNK, PC_OPT_SPMV_SLICES_PER_BLOCK, PC_OPT_VECTOR_ROWS_PER_BLOCK, PC_OPT_LDS_WINDOW, \
     PC_OPT_NARROW_COLUMNS, PC_OPT_SPMV_NARROW_ACTIVE, PC_OPT_INNER_FP32, PC_OPT_KEEP_DIRECTION, \
-    PC_OPT_RESIDENT_POLLS = 0, 1, 2, 3, 4, 5, 6, 7, 8
+    PC_OPT_RESIDENT_POLLS, PC_OPT_RESIDENT_OFF = 0, 1, 2, 3, 4, 5, 6, 7, 8, 9
 PROFILE_KINDS = ["spmv", "cg_update", "cg_dir", "row_assemble", "row_pattern", "assemble_all", "elements", "k7"]
 
 

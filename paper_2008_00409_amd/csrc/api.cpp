@@ -408,6 +408,7 @@ pc_status pc_get_option(pc_ctx *h, int32_t option, int64_t *value) {
         case PC_OPT_INNER_FP32: *value = ctx->use_inner32 ? 1 : 0; return PC_OK;
         case PC_OPT_KEEP_DIRECTION: *value = ctx->use_keep_dir ? 1 : 0; return PC_OK;
         case PC_OPT_RESIDENT_POLLS: *value = ctx->res_polls; return PC_OK;
+        case PC_OPT_RESIDENT_OFF: *value = ctx->res_off; return PC_OK;
         default: ctx->err = "unknown option"; return PC_ERR_ARG;
     }
 }

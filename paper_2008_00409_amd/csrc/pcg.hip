@@ -1406,9 +1406,10 @@ static pc_status pcg_typed(Ctx *ctx, const double *b, double *dv, const pc_solve
         if (any_breakdown) inner_hi = true;  // low-precision operator lost definiteness or stopped contracting: FP64 blocks from here on
         for (int i = 0; i < ninst; ++i) {
             if (again[i]) {
-                sweeps[i] += 1;
-                // a lost sweep's budget serves the one that does its work
-                const int later = ctx->st_host[i].flags & 4 ? maxit_h[i] : std::max(256, 3 * longest[i]);
+                // a lost sweep does not count, and its budget serves the one that does its work
+                const bool gave_up = (ctx->st_host[i].flags & 4) != 0;
+                sweeps[i] += gave_up ? 0 : 1;
+                const int later = gave_up ? maxit_h[i] : std::max(256, 3 * longest[i]);
                 maxit_h[i] = maxit - iters[i];
                 if (sweep_budget && !inner_hi) maxit_h[i] = std::min(maxit_h[i], later);
             }

@@ -67,8 +67,9 @@ def test_solves_whose_launches_give_up(torch, B, shape, dtype, precond):
             # the library's own check is <= TOL; the product here rounds in FP64
             assert residual(ctx, b, dv, bounds) <= TOL * (1 + 1e-6), polls
             assert info["fallback"] == want["fallback"]
-            if polls == 0 and dtype in ("f32", "f64"):
-                assert info["sweeps"] == want["sweeps"] + 1      # the first one did nothing
+            if polls == 0:
+                assert ctx.get_option(B.PC_OPT_RESIDENT_OFF) == 64
+                assert info["sweeps"] == want["sweeps"]          # the lost one does not count
     finally:
         ctx.close()
 
@@ -89,28 +90,51 @@ def test_a_lost_sweep_keeps_its_budget(torch, B, dtype):
         assert want["fallback"] == 0
         ctx.set_option(B.PC_OPT_RESIDENT_POLLS, 0)
         dv, info = ctx.cloth_pcg_solve(b, **kw)
-        assert info["fallback"] == 0 and info["sweeps"] == want["sweeps"] + 1, (info, want)
+        assert ctx.get_option(B.PC_OPT_RESIDENT_OFF) == 64
+        assert info["fallback"] == 0 and info["sweeps"] == want["sweeps"], (info, want)
         assert residual(ctx, b, dv, [0, c.nv]) <= 1e-6 * (1 + 1e-6)
     finally:
         ctx.close()
 
 
+@pytest.mark.parametrize("dtype,max_sweeps", [("f16", 3), ("f64", 1)])
+def test_a_lost_sweep_does_not_count(torch, B, dtype, max_sweeps):
+    """The sweeps a caller allows are those that do their work: the iterations of an
+    undisturbed solve with the same limit."""
+    ctx, b = system(torch, B, sheet(43, 31, seed=5), dtype)
+    try:
+        kw = dict(tol=1e-9, precond="block", max_sweeps=max_sweeps, maxit=1000, raise_on_error=False)
+        _, want = ctx.cloth_pcg_solve(b, **kw)
+        ctx.set_option(B.PC_OPT_RESIDENT_POLLS, 0)
+        _, info = ctx.cloth_pcg_solve(b, **kw)
+        assert ctx.get_option(B.PC_OPT_RESIDENT_OFF) == 64
+        assert info["sweeps"] == want["sweeps"] and info["status"] == want["status"], (info, want)
+        assert abs(info["iters"] - want["iters"]) <= 2 + 0.02 * want["iters"], (info, want)
+    finally:
+        ctx.close()
+
+
 def test_a_loss_is_remembered(torch, B):
-    """The solves after a loss run without resident launches (their first sweep
-    does its work) until 64 have, then 128 after the second loss in a row; setting
-    the option lets the next one try again."""
+    """The solves after a loss run without resident launches until 64 have, then 128
+    after the second loss in a row; setting the option lets the next one try again."""
     c = sheet(43, 31, seed=5)
     ctx, b = system(torch, B, c, "f64")
     try:
-        sweeps = lambda: ctx.cloth_pcg_solve(b, tol=1e-2)[1]["sweeps"]
-        assert sweeps() == 1
+        def solve():
+            assert ctx.cloth_pcg_solve(b, tol=1e-2)[1]["sweeps"] == 1
+            return ctx.get_option(B.PC_OPT_RESIDENT_OFF)
+
+        assert solve() == 0
         ctx.set_option(B.PC_OPT_RESIDENT_POLLS, 0)
         for between in (64, 128):
-            assert sweeps() == 2
-            assert all(sweeps() == 1 for _ in range(between))
-        assert sweeps() == 2
+            assert [solve() for _ in range(between + 1)] == list(range(between, -1, -1))
+        assert solve() == 256
         ctx.set_option(B.PC_OPT_RESIDENT_POLLS, 0)
-        assert sweeps() == 2 and sweeps() == 1
+        assert ctx.get_option(B.PC_OPT_RESIDENT_OFF) == 0 and solve() == 64 and solve() == 63
+        ctx.set_option(B.PC_OPT_RESIDENT_POLLS, 2_000_000)
+        assert solve() == 0
+        with pytest.raises(B.PclothError, match="PC_ERR_ARG"):
+            ctx.set_option(B.PC_OPT_RESIDENT_OFF, 0)
     finally:
         ctx.close()
 
